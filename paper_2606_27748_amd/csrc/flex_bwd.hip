@@ -305,11 +305,10 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
   StX sq, sk;
   StV sv, sdo;
   float2 gs_next = make_float2(0.f, 0.f);
-  bool gs_ok = false;
   if (c0 < c1) {
     const int t1 = (c1 - 1) * SH::CH;
     sq.fetch(Q, t1, a.N); sk.fetch(K, t1, a.N); sv.fetch(V, t1, a.N); sdo.fetch(dO, t1, a.N);
-    gs_next = load_gs(gst, t1, a.N, SH::CH, gs_ok);
+    gs_next = load_gs(gst, t1, a.N, SH::CH);
   }
   const Frag<T>* wproj = FragBlock<T, D, FW, NS>::proj(a.wfrag_kv, h, NW, w);
   const auto inv_c = inv_c_of<T>(a.tau[h]);
@@ -376,12 +375,12 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
     const int par = NBUF == 2 ? i & 1 : 0, kp = i % NKB;
     sq.store(XQ2[par], SSQ2[par]); sk.store(XK2[kp], SSK2[kp]); sv.store(XV2[par]); sdo.store(XDO2[par]);
     if (threadIdx.x < SH::CH) {
-      GS2[par][threadIdx.x][0] = gs_ok ? gs_next.x : 0.f;
-      GS2[par][threadIdx.x][1] = gs_ok ? gs_next.y : 0.f;
+      GS2[par][threadIdx.x][0] = gs_next.x;
+      GS2[par][threadIdx.x][1] = gs_next.y;
     }
     const int t1 = (cn - 1 >= c0 ? cn - 1 : cn) * SH::CH;
     sq.fetch(Q, t1, a.N); sk.fetch(K, t1, a.N); sv.fetch(V, t1, a.N); sdo.fetch(dO, t1, a.N);
-    gs_next = load_gs(gst, t1, a.N, SH::CH, gs_ok);
+    gs_next = load_gs(gst, t1, a.N, SH::CH);
   };
   // Projection fragments, reloaded per chunk (held for the whole sweep they
   // would not fit the registers).
@@ -413,27 +412,25 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
     // of the other waves' LDS blocks (dP, dV partials, g shares), which this
     // chunk writes again before its dP barrier.
     if (EARLY) __syncthreads();
-    // an earlier group's dK and dV of this chunk (rows past N read row N-1, unused)
+    const RowBuf dkb(dK, D, tok0, a.N, SH::CH), dvb(dV, SH::DV, tok0, a.N, SH::CH);
+    // an earlier group's dK and dV of this chunk (rows past N read zero)
     f32x4 old_k[ACC ? NDK : 1][ACC ? NTK : 1];
-    float4 old_v[ACC ? SH::TT / QG : 1][ACC ? NIT : 1];
+    f32x4 old_v[ACC ? SH::TT / QG : 1][ACC ? NIT : 1];
     if (ACC) {
 #pragma unroll
       for (int kd = 0; kd < NDK; ++kd)
 #pragma unroll
         for (int kt = 0; kt < NTK; ++kt) {
           const int dt = w % DT + kd * NW, tt = (DT < NW ? w / DT : 0) + kt * TT0STEP;
-          const int tok = min(tok0 + tt * 16 + r, a.N - 1);
-          if (dt < DT && tt < SH::TT)
-            old_k[kd][kt] = *reinterpret_cast<const f32x4*>(dK + (size_t)tok * D + dt * 16 + 4 * g);
+          if (dt < DT && tt < SH::TT) old_k[kd][kt] = dkb.load_f4(((tt * 16 + r) * D + dt * 16 + 4 * g) * 4);
         }
 #pragma unroll
       for (int q = 0; q < SH::TT / QG; ++q)
 #pragma unroll
         for (int k = 0; k < NIT; ++k) {
           const int it = threadIdx.x + k * SH::NT;
-          const int tok = min(tok0 + q * QG * 16 + it / C4, a.N - 1);
           if (it < QG * 16 * C4)
-            old_v[q][k] = *reinterpret_cast<const float4*>(dV + (size_t)tok * SH::DV + 4 * (it % C4));
+            old_v[q][k] = dvb.load_f4(((q * QG * 16 + it / C4) * SH::DV + 4 * (it % C4)) * 4);
         }
     }
     if (!EARLY) {
@@ -493,7 +490,8 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const bool keep = tq > tk || 4 * g + i >= r;
-              m[tq][i] = keep ? m[tq][i] - GS[tq * 16 + 4 * g + i][1] : 0.f;
+              const float md = m[tq][i] - GS[tq * 16 + 4 * g + i][1];
+              m[tq][i] = keep ? md : 0.f;
               at[tq][i] = keep ? at[tq][i] : 0.f;
             }
           }
@@ -589,15 +587,11 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
         const int it = threadIdx.x + k * SH::NT;
         if (it >= QG * 16 * C4) break;
         const int t = it / C4, c4 = it % C4;
-        const int tok = tok0 + q0 * 16 + t;
-        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        f32x4 s = zero4();
         if (ACC) s = old_v[q0 / QG][k];   // later frequency groups add their share
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-          const float4 v = *reinterpret_cast<const float4*>(&RED(ww)[t][4 * c4]);
-          s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
-        if (tok < a.N) *reinterpret_cast<float4*>(dV + (size_t)tok * SH::DV + 4 * c4) = s;
+        for (int ww = 0; ww < NW; ++ww) s += *reinterpret_cast<const f32x4*>(&RED(ww)[t][4 * c4]);
+        dvb.store_f4(((q0 * 16 + t) * SH::DV + 4 * c4) * 4, s);
       }
     };
     if (DEFER_DV) {
@@ -693,23 +687,22 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
       for (int kt = 0; kt < NTK; ++kt) {
         const int tt = (DT < NW ? w / DT : 0) + kt * TT0STEP;
         if (tt >= SH::TT) continue;
-        const int tl = tt * 16 + r, tok = tok0 + tl;
+        const int tl = tt * 16 + r;
         float gg = 0.f;
 #pragma unroll
         for (int ww = 0; ww < NW; ++ww) {
           const float4 v = *reinterpret_cast<const float4*>(&GP[tl][ww][0]);
           gg += (v.x + v.y) + (v.z + v.w);
         }
-        if (tok < a.N) {
-          const float k2 = 2.0f * inv_c * gg;
-          const IO* kr = XK + tl * StX::LD + dt * 16 + 4 * g;
-          f32x4 s;
+        const float k2 = 2.0f * inv_c * gg;
+        const IO* kr = XK + tl * StX::LD + dt * 16 + 4 * g;
+        f32x4 s;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) s[i] = acc[kt][i] + k2 * io_to_float(kr[i]);
-          if (ACC) s += old_k[kd][kt];   // later frequency groups add their share
-          *reinterpret_cast<f32x4*>(dK + (size_t)tok * D + dt * 16 + 4 * g) = s;
-          if (dt == 0 && g == 0) dtau_acc -= gg * SSK[tl] * inv_c;
-        }
+        for (int i = 0; i < 4; ++i) s[i] = acc[kt][i] + k2 * io_to_float(kr[i]);
+        if (ACC) s += old_k[kd][kt];   // later frequency groups add their share
+        dkb.store_f4((tl * D + dt * 16 + 4 * g) * 4, s);
+        const float dt_term = gg * SSK[tl] * inv_c;
+        dtau_acc -= (dt == 0 && g == 0 && tok0 + tl < a.N) ? dt_term : 0.f;
       }
     }
     if (EARLY) fs.load_frags(wproj);   // the next chunk's (the last step's are unused)

@@ -76,13 +76,10 @@ __device__ __forceinline__ Frag<T> delta_rows(const float (*GS)[2], int ks) {
   return f;
 }
 
-// Per-token (1/den, delta) of token tok0 + (thread mod ch), loaded from a
-// clamped in-range index so that the load is unconditional (ok: the thread
-// holds a token of the chunk below n; others are zeroed where they are stored).
-__device__ __forceinline__ float2 load_gs(const float* gst, int tok0, int n, int ch, bool& ok) {
-  const int t = tok0 + (int)(threadIdx.x % ch);
-  ok = (int)threadIdx.x < ch && t < n;
-  return *reinterpret_cast<const float2*>(gst + (size_t)min(t, n - 1) * 2);
+// Per-token (1/den, delta) of token tok0 + thread of a chunk of ch tokens: zero
+// for tokens past n and for threads past the chunk.
+__device__ __forceinline__ float2 load_gs(const float* gst, int tok0, int n, int ch) {
+  return RowBuf(gst, 2, tok0, n, ch).load_f2((int)threadIdx.x * 8);
 }
 
 // Register-dump layout of the [dv' x features] states: tile (dt, global feature

@@ -66,16 +66,15 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
   float dn_next[WPER];
 #pragma unroll
   for (int i = 0; i < WPER; ++i) dn_next[i] = 0.f;
-  auto den_rows = [&](int t0) {   // rows past N (and threads past the rows) unused
+  auto den_rows = [&](int t0) {   // rows past N (and threads past the rows) read zero, unused
+    const RowBuf b(den, 1, t0, a.N, SH::CH);
 #pragma unroll
-    for (int i = 0; i < WPER; ++i)
-      dn_next[i] = den[min(t0 + (int)(threadIdx.x + i * SH::NT) / StV::VPR, a.N - 1)];
+    for (int i = 0; i < WPER; ++i) dn_next[i] = b.load_f1((int)(threadIdx.x + i * SH::NT) / StV::VPR * 4);
   };
 
   StX sq, sk;
   StV sv, sdo, so;
   float2 gs_next = make_float2(0.f, 0.f);
-  bool gs_ok = false;
   if (c0 < c1) {
     sq.fetch(Q, c0 * SH::CH, a.N); sk.fetch(K, c0 * SH::CH, a.N);
     sv.fetch(V, c0 * SH::CH, a.N); sdo.fetch(dO, c0 * SH::CH, a.N);
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
       so.fetch(Ob, c0 * SH::CH, a.N);
       den_rows(c0 * SH::CH);
     } else {
-      gs_next = load_gs(gst, c0 * SH::CH, a.N, SH::CH, gs_ok);
+      gs_next = load_gs(gst, c0 * SH::CH, a.N, SH::CH);
     }
   }
   const Frag<T>* wproj = FragBlock<T, D, FW, NS>::proj(a.wfrag, h, NW, w);
@@ -153,14 +152,14 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
     float* SCK = SCK2[par];
     const int tok0 = c * SH::CH;
     if (!KEEP_FS) fs.load_frags(wproj);
-    // an earlier group's dQ of this chunk (rows past N read row N-1, unused)
+    const RowBuf dqb(dQ, D, tok0, a.N, SH::CH);
+    // an earlier group's dQ of this chunk (rows past N read zero)
     f32x4 old_q[ACC ? NOT : 1];
     if (ACC) {
 #pragma unroll
       for (int k = 0; k < NOT; ++k) {
         const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
-        const int tok = min(tok0 + tt * 16 + r, a.N - 1);
-        if (ot < DT * SH::TT) old_q[k] = *reinterpret_cast<const f32x4*>(dQ + (size_t)tok * D + dt * 16 + 4 * g);
+        if (ot < DT * SH::TT) old_q[k] = dqb.load_f4(((tt * 16 + r) * D + dt * 16 + 4 * g) * 4);
       }
     }
     if (NBUF == 1) __syncthreads();   // single buffer: the previous chunk's reads are done
@@ -168,7 +167,9 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
     sk.store(XK, SCK, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tok0 + t < a.N); });
     sv.store(XV); sdo.store(XDO);
     if constexpr (WR) {
-      // 1/den and delta of this thread's rows (rows past N: zero vectors, delta 0)
+      // 1/den and delta of this thread's rows (rows past N: zero vectors, delta 0,
+      // and their stores to memory are dropped)
+      const RowBuf gb(gst, 2, tok0, a.N, SH::CH);
 #pragma unroll
       for (int i = 0; i < WPER; ++i) {
         const int v = threadIdx.x + i * SH::NT, t = v / StV::VPR;
@@ -181,15 +182,16 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
 #pragma unroll
         for (int j = 0; j < StV::VEC; ++j) dsum += io_to_float(ex[j]) * io_to_float(ey[j]);
         dsum = lane_sum<StV::VPR>(dsum);
+        const float rcp = 1.0f / dn_next[i];
+        const float inv = ok ? rcp : 0.f;
         if (mine && v % StV::VPR == 0) {
-          const float inv = ok ? 1.0f / dn_next[i] : 0.f;
           GS[t][0] = inv;
-          GS[t][1] = ok ? dsum : 0.f;
-          if (ok) { gst[(size_t)(tok0 + t) * 2] = inv; gst[(size_t)(tok0 + t) * 2 + 1] = dsum; }
+          GS[t][1] = dsum;
+          gb.store_f2(t * 8, make_float2(inv, dsum));
         }
       }
     } else {
-      if (threadIdx.x < SH::CH) { GS[threadIdx.x][0] = gs_ok ? gs_next.x : 0.f; GS[threadIdx.x][1] = gs_ok ? gs_next.y : 0.f; }
+      if (threadIdx.x < SH::CH) { GS[threadIdx.x][0] = gs_next.x; GS[threadIdx.x][1] = gs_next.y; }
     }
     {
       const int t1 = c + 1 < c1 ? tok0 + SH::CH : tok0;   // the last chunk refetches itself (unused)
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
         so.fetch(Ob, t1, a.N);
         den_rows(t1);
       } else {
-        gs_next = load_gs(gst, t1, a.N, SH::CH, gs_ok);
+        gs_next = load_gs(gst, t1, a.N, SH::CH);
       }
     }
     __syncthreads();
@@ -265,7 +267,8 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const bool keep = tk < tq || 4 * g + i <= r;
-              m[tk][i] = keep ? m[tk][i] - dl : 0.f;
+              const float md = m[tk][i] - dl;
+              m[tk][i] = keep ? md : 0.f;
             }
           }
         }
@@ -371,11 +374,8 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
       const int ot = w + k * NW;
       if (ot >= DT * SH::TT) continue;
       const int dt = ot % DT, tt = ot / DT;
-      const int tok = tok0 + tt * 16 + r;
-      if (tok < a.N) {
-        if (ACC) acc[k] += old_q[k];   // later frequency groups add their share
-        *reinterpret_cast<f32x4*>(dQ + (size_t)tok * D + dt * 16 + 4 * g) = acc[k];
-      }
+      if (ACC) acc[k] += old_q[k];   // later frequency groups add their share
+      dqb.store_f4(((tt * 16 + r) * D + dt * 16 + 4 * g) * 4, acc[k]);
     }
     // frequency gradient partial: dW'[rows][d] += dP^T Q
     {

@@ -529,8 +529,10 @@ __device__ __forceinline__ Frag<T> features(const P (&p)[NS ? 2 * FT : FT], int 
 }
 
 // Row scale s * exp(||x||^2 / exp(tau)) for valid rows, 0 otherwise.
+// Formed for every row and then selected, so that no branch splits the code.
 __device__ __forceinline__ float row_scale(float ssq, float inv_c, float s_const, bool ok) {
-  return ok ? s_const * __expf(ssq * inv_c) : 0.0f;
+  const float v = s_const * __expf(ssq * inv_c);
+  return ok ? v : 0.0f;
 }
 // fp32 path: the squared norm and 1/exp(tau) in float64, one rounding at the end.
 __device__ __forceinline__ float row_scale(double ssq, double inv_c, float s_const, bool ok) {

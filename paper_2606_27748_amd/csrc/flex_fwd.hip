@@ -544,14 +544,11 @@ void k_fwd_readout(FwdArgs a) {
     // normaliser tile holds den in its row 0 (lane r of lane group 0)
     const float dn = __shfl(acc[DVT][0], r);
     const float inv = __builtin_amdgcn_rcpf(dn);   // den = 0 gives inf/NaN as num/0 does
-    if (tok < a.N) {
+    const RowBuf ob(O, D, tok0, a.N, CHUNK);
 #pragma unroll
-      for (int dt = 0; dt < DVT; ++dt) {
-        const float v[4] = {acc[dt][0] * inv, acc[dt][1] * inv, acc[dt][2] * inv, acc[dt][3] * inv};
-        store4<IO>(O + (size_t)tok * D + dt * 16 + 4 * g, v);
-      }
-      if (den && g == 0) den[tok] = dn;
-    }
+    for (int dt = 0; dt < DVT; ++dt)
+      ob.store_io4(O, ((w * 16 + r) * D + dt * 16 + 4 * g) * (int)sizeof(IO), acc[dt] * inv);
+    if (den && g == 0) RowBuf(den, 1, tok0, a.N, CHUNK).store_f1((w * 16 + r) * 4, dn);
   }
 }
 

@@ -8,6 +8,58 @@
 
 namespace flex {
 
+// A window of consecutive rows of a row-major matrix as a raw buffer resource
+// (CDNA descriptor word 3): accesses past its last row read zero and drop
+// their stores, so ragged chunks need neither a mask nor a branch.  The base
+// and the extent are uniform across the workgroup (scalar registers); a
+// lane's byte offset into the window does not change from chunk to chunk.
+// The sweeps are bound by vector issue, and this takes the 64-bit addresses,
+// the zeroing selects and the exec-mask branches around ragged rows out of
+// their chunk loops (dK/dV at d = 64, m = 128: 1947 to 1753 instructions per
+// chunk).  Before and after, us per pass: d = 64, m = 128 training step (B*H =
+// 32, N = 8192) 500 to 480, d = 128, m = 256 2813 to 2626, distillation 250 to
+// 232, non-causal m = 64 forward (B*H = 128, N = 16384) 279 to 263.
+constexpr int BUF_FLAGS = 0x00020000;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+struct RowBuf {
+  __amdgpu_buffer_rsrc_t rs;
+  // rows tok0 .. min(n, tok0 + nrows) - 1 of `base` (row_elems elements each); n > tok0
+  template <class E>
+  __device__ __forceinline__ RowBuf(const E* base, int row_elems, int tok0, int n, int nrows) {
+    const int rows = n - tok0 < nrows ? n - tok0 : nrows;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<E*>(base) + (size_t)tok0 * row_elems, 0,
+                                           rows * row_elems * (int)sizeof(E), BUF_FLAGS);
+  }
+  __device__ __forceinline__ uint4 load16(int off) const {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+  }
+  __device__ __forceinline__ f32x4 load_f4(int off) const {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+  }
+  __device__ __forceinline__ float load_f1(int off) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+  }
+  __device__ __forceinline__ float2 load_f2(int off) const {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+  }
+  __device__ __forceinline__ void store_f4(int off, f32x4 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off, 0, 0);
+  }
+  __device__ __forceinline__ void store_f2(int off, float2 v) const {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, off, 0, 0);
+  }
+  __device__ __forceinline__ void store_f1(int off, float v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rs, off, 0, 0);
+  }
+  // four consecutive values of a row in the io dtype
+  __device__ __forceinline__ void store_io4(const u16*, int off, const f32x4& v) const {
+    const bf16x4 b = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, b), rs, off, 0, 0);
+  }
+  __device__ __forceinline__ void store_io4(const float*, int off, const f32x4& v) const { store_f4(off, v); }
+};
+
 // Row-major staging of a [64 x COLS] io-typed block with a padded row.
 template <class IO, int COLS, int NT, int ROWS = CHUNK>
 struct RowStage {
@@ -18,39 +70,31 @@ struct RowStage {
   static constexpr int LD = COLS + VEC;                  // LDS row stride (elements), keeps 16 B alignment
   static constexpr int LDS_ELEMS = ROWS * LD;
   uint4 r[PER];
-  uint32_t okm;   // bit i: vector i belongs to this thread and to a row below n
 
-  // rows: this (b,h) slice's [N, COLS] rows; rows at or beyond n read as zero.
-  // The loads are unconditional, from a clamped in-range row, so that nothing
-  // writes their destination registers while they are in flight (a zeroing
-  // branch would make the compiler wait for each load right away); the
-  // out-of-range vectors are zeroed when they are stored.  n >= 1.
+  // rows: this (b,h) slice's [N, COLS] rows; rows at or beyond n (and the
+  // vectors of threads past the chunk) read as zero.  n > tok0.  The chunk's
+  // rows are consecutive in memory, so vector v sits 16 v bytes into it: one
+  // lane offset for every chunk, and no branch or select on the destination
+  // registers, which would make the compiler wait for each load right away.
   __device__ __forceinline__ void fetch(const IO* __restrict__ rows, int tok0, int n) {
-    okm = 0u;
+    const RowBuf b(rows, COLS, tok0, n, ROWS);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int v0 = threadIdx.x + i * NT;
-      const int v = v0 < NV ? v0 : NV - 1;
-      const int t = v / VPR, c = v % VPR;
-      const int row = tok0 + t < n ? tok0 + t : n - 1;
-      r[i] = *reinterpret_cast<const uint4*>(rows + (size_t)row * COLS + c * VEC);
-      if (v0 < NV && tok0 + t < n) okm |= 1u << i;
-    }
+    for (int i = 0; i < PER; ++i) r[i] = b.load16(((int)threadIdx.x + i * NT) * 16);
   }
-  __device__ __forceinline__ uint4 vec(int i) const {
-    return ((okm >> i) & 1u) ? r[i] : make_uint4(0u, 0u, 0u, 0u);
-  }
+  __device__ __forceinline__ uint4 vec(int i) const { return r[i]; }
   // keeps the fetched rows' loads without storing them anywhere (loads whose
   // only purpose is to bring the rows into the caches for a later kernel)
   __device__ __forceinline__ void touch() const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) asm volatile("" ::"v"(r[i].x), "v"(r[i].y), "v"(r[i].z), "v"(r[i].w));
   }
+  // whether vector index v (of thread threadIdx.x) is part of the chunk
+  static __device__ __forceinline__ bool mine(int v) { return NV % NT == 0 || v < NV; }
   __device__ __forceinline__ void store(IO* lds) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int v = threadIdx.x + i * NT;
-      if (v < NV) {
+      if (mine(v)) {
         const int t = v / VPR, c = v % VPR;
         *reinterpret_cast<uint4*>(lds + t * LD + c * VEC) = vec(i);
       }
@@ -77,7 +121,7 @@ struct RowStage {
     for (int i = 0; i < PER; ++i) {
       const int v = threadIdx.x + i * NT;
       Ssq s = 0;
-      if (v < NV) {
+      if (mine(v)) {
         const int t = v / VPR, c = v % VPR;
         const uint4 x = vec(i);
         *reinterpret_cast<uint4*>(lds + t * LD + c * VEC) = x;
@@ -91,7 +135,7 @@ struct RowStage {
 #pragma unroll
         for (int o = 1; o < VPR; o <<= 1) s += __shfl_xor(s, o);
       }
-      if (v < NV && v % VPR == 0) out[v / VPR] = f(i, v / VPR, s);
+      if (mine(v) && v % VPR == 0) out[v / VPR] = f(i, v / VPR, s);
     }
   }
   // transposed store: ldsT[col][token] with row stride LDT (operand type T)
@@ -100,7 +144,7 @@ struct RowStage {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int v = threadIdx.x + i * NT;
-      if (v < NV) {
+      if (mine(v)) {
         const int t = v / VPR, c = v % VPR;
         const uint4 x = vec(i);
         const IO* e = reinterpret_cast<const IO*>(&x);
