@@ -524,11 +524,10 @@ int32_t run_fwd(const flex_desc* desc, const void* Q, const void* K, const void*
     if (!group_rows(desc, G, pr, g, W1, W2, stream, &a.W1, &a.W2, &a.w_stride, &a.fvalid)) return FLEX_ERR_HIP;
     a.state = reinterpret_cast<float*>(base + g * sb);
     a.state_f0 = group_off(G, g);
-    a.acc = G.n == 1 ? 0 : (g == 0 ? 1 : 2);
+    a.acc = G.n == 1 ? 0 : (g == 0 ? 1 : (g + 1 < G.n ? 2 : 3));
     const hipError_t e = launch_fwd(a, ks, false, stream);
     if (e != hipSuccess) return FLEX_ERR_HIP;
   }
-  if (G.n > 1 && launch_fwd_finish(a, ks.bf16, desc->dv, stream) != hipSuccess) return FLEX_ERR_HIP;
   return FLEX_OK;
 }
 

@@ -89,19 +89,6 @@ __device__ __forceinline__ void tile_products(const typename Io<T>::type* XL, co
     }
   }
 }
-
-// Two accumulator tiles as one operand fragment split into a high and a low
-// part (bf16 hi + lo carries about 16 significant bits; fp32 keeps the value).
-template <class T>
-__device__ __forceinline__ void split_pair(const f32x4& a, const f32x4& b, Frag<T>& hi, Frag<T>& lo) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    hi.set(i, a[i]);
-    hi.set(4 + i, b[i]);
-    lo.set(i, a[i] - hi.get(i));
-    lo.set(4 + i, b[i] - hi.get(4 + i));
-  }
-}
 }  // namespace
 
 // z[bh][f] = sum_j phi(K_j)_f in a fixed order: 16-byte column vectors per

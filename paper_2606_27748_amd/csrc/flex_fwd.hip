@@ -6,10 +6,9 @@
 // owns frequencies [w*FW, (w+1)*FW), i.e. 2*FW of the d' = 2m features, and
 // keeps its rows of the state S' = sum_j phi(K_j) [V_j ; 1]^T (d' x (dv+1),
 // fp32) as MFMA accumulators.  Per chunk a wave forms phi(Q), phi(K) for its
-// features on chip (projection + fused trig, never written to memory), adds
-// its partial readout phi(Q) S' plus the intra-chunk masked term
-// tril(phi(Q) phi(K)^T) [V;1], and the partials of the NW waves are summed in
-// LDS before O = num / den is written.
+// features on chip (projection + fused trig, never written to memory); the
+// sweep hands them and the state to the other waves as operand fragments in
+// LDS, and each wave then reads out whole output tiles over all features.
 //
 // Causal sequences are split into segments for occupancy:
 //   k_fwd_state  : segment-local states (one pass over K, V),
@@ -62,7 +61,7 @@ void k_fwd_state(FwdArgs a) {
   for (int fc = 0; fc < SH::FC; ++fc)
 #pragma unroll
     for (int dt = 0; dt < SH::DVT1; ++dt) S[fc][dt] = zero4();
-  const Frag<T> ones = ones_col0<T>();
+  const Frag<T> ones = ones_all<T>();
   const int g = (threadIdx.x % WAVE) / 16;
 
   // projection fragments: held for the whole sweep where registers allow
@@ -154,6 +153,24 @@ __global__ __launch_bounds__(256) void k_state_scan(float* state0, float* state1
 // ---------------------------------------------------------------------------
 // Sweep: carry-in state, then per chunk the readout (and, causal, the
 // intra-chunk term and the state update).  Writes O and den.
+//
+// A chunk has two phases.  In the first the waves split the frequencies: each
+// forms phi(Q) and phi(K) of its slice for the chunk's tokens, writes them and
+// its bf16 copy of the state to LDS as operand fragments, and updates its
+// state.  In the second they split the output: a wave takes one 16-token tile
+// (and, with more waves than tiles, a part of the value columns) over all
+// features.  So no partial sum crosses waves, the intra-chunk kernel matrix of
+// a tile is formed once over all features (not once per slice), and the
+// division and the store follow from the accumulators.
+//
+// Bound by vector issue and the latency of the two phases.  With the readout's
+// partial sums, their reduction and the per-slice kernel matrices gone, 8
+// waves of 16 frequencies at d = 64, m = 128 fit two waves per SIMD with no
+// accumulator moves, and at m = 64 two workgroups share a CU.  us per sweep,
+// before (4 waves of 32 frequencies, partials reduced through LDS) and after:
+// d = 64, m = 128 nonstationary, B*H = 32, N = 8192: 97 and 81; stationary,
+// B*H = 96, N = 1024: 44 and 39; d = 128, m = 256 (four groups, and the last
+// one divides, where a pass of its own took 35): 620 and 559.
 // ---------------------------------------------------------------------------
 // ADD: add this frequency group's numerator and denominator to the sums the
 // earlier groups stored; the old sums are loaded at the start of each chunk,
@@ -162,13 +179,25 @@ __global__ __launch_bounds__(256) void k_state_scan(float* state0, float* state1
 // term covers j <= i within a chunk, earlier tokens enter through the carried
 // state).  Token contractions run in 32-token MFMA k-steps; a 16-token chunk
 // pads its k-step with zero rows (staged once, never written).
-template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, int QG, bool ADD, int CH, bool MASK = false>
-__global__ __launch_bounds__(NW * WAVE) void k_fwd_sweep(FwdArgs a) {
+template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ADD, int CH, bool MASK = false>
+struct SweepShape {
   typedef Shape<T, D, FW, NW, NS, CH> SH;
+  static constexpr int TT = CH / 16;                  // token tiles per chunk
+  static constexpr int NFT = SH::M / 16;              // frequency tiles of all waves
+  static constexpr int WPT = NW > TT ? NW / TT : 1;   // waves per token tile in the second phase
+  static constexpr int NDT = (SH::DVT + WPT - 1) / WPT;   // value tiles of one of them
+  static_assert(TT <= NW && NW % TT == 0, "whole token tiles per wave");
+};
+
+template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ADD, int CH, bool MASK = false>
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu(IsBf16<T>::value, D, FW * NW, CAUSAL, CH))))
+void k_fwd_sweep(FwdArgs a) {
+  typedef SweepShape<T, D, FW, NW, NS, CAUSAL, ADD, CH, MASK> SS;
+  typedef typename SS::SH SH;
   typedef typename Io<T>::type IO;
   typedef RowStage<IO, D, SH::NT, CH> StX;
   typedef RowStage<IO, SH::DV, SH::NT, CH> StV;
-  constexpr int TT = CH / 16;                  // token tiles per chunk
+  constexpr int TT = SS::TT, NFT = SS::NFT, NDT = SS::NDT, WPT = SS::WPT;
   constexpr int KT = (CH + 31) / 32;           // 32-token k-steps per chunk
   constexpr int ROWS = KT * 32;                // token rows of the k-step operands
   static_assert(CH == 16 || CH == 32 || CH == 64, "chunk of 16, 32 or 64 tokens");
@@ -176,21 +205,21 @@ __global__ __launch_bounds__(NW * WAVE) void k_fwd_sweep(FwdArgs a) {
   constexpr int XV_N = CAUSAL ? ROWS * StV::LD : 8;
   constexpr int LDP = SH::FC * 16 + 4;     // [token][feature] rows of a wave's phi(K) block
   constexpr int PT_N = CAUSAL ? ROWS * LDP : 8;
-  constexpr int C4 = SH::DV / 4;                                // float4 columns of a row
-  constexpr int NIT = (QG * 16 * C4 + SH::NT - 1) / SH::NT;    // readout items per thread and round
-  static_assert(TT % QG == 0, "whole reduction rounds per chunk");
   __shared__ __attribute__((aligned(16))) IO XQ[StX::LDS_ELEMS];
   __shared__ __attribute__((aligned(16))) IO XK[CAUSAL ? StX::LDS_ELEMS : 8];
-  __shared__ typename StX::Ssq SSQ[CH], SSK[CH];
+  __shared__ __attribute__((aligned(16))) float SCQ[CH], SCK[CH];   // staged: per-token scales s e(x)
   __shared__ __attribute__((aligned(16))) IO XV[XV_N];   // [token][value col]
   __shared__ __attribute__((aligned(16))) T PT[NW][PT_N];
-  __shared__ __attribute__((aligned(16))) float RED[NW][QG * 16][SH::RPAD];
+  __shared__ Frag<T> PQ[TT][NFT][WAVE];        // phi(Q), operand fragments
+  __shared__ Frag<T> SB[SH::DVT][NFT][WAVE];   // state, operand fragments (rows = value columns)
+  __shared__ Frag<T> SZ[NFT][4];               // normaliser rows of the state, all columns alike
 
   // causal: one workgroup per segment; non-causal: per group of chunks (every
   // chunk reads the same total state)
   const WgCoord wc = wg_coord(a.sweep_groups, a.H, a.BH);
   const int seg = wc.seg, bh = wc.bh, h = bh % a.H;
-  const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
   const int fv = slice_valid<MASK, FW>(a.fvalid, w);
   const int nch = (a.N + CH - 1) / CH;
   const int c0 = seg * a.sweep_cps;
@@ -200,6 +229,11 @@ __global__ __launch_bounds__(NW * WAVE) void k_fwd_sweep(FwdArgs a) {
   const IO* V = static_cast<const IO*>(a.V) + (size_t)bh * a.N * SH::DV;
   IO* O = static_cast<IO*>(a.O) + (size_t)bh * a.N * SH::DV;
   float* den = a.den ? a.den + (size_t)bh * a.N : nullptr;
+  // second phase: this wave's token tile and its part of the value columns.
+  // The waves of one SIMD (w and w + 4) take tiles from both ends, so their
+  // causal work adds up alike.
+  const int part = w / TT;
+  const int tq = part % 2 ? TT - 1 - w % TT : w % TT;
 
   StX sq, sk;
   StV sv;
@@ -243,27 +277,33 @@ __global__ __launch_bounds__(NW * WAVE) void k_fwd_sweep(FwdArgs a) {
           S[fc][dt] = *reinterpret_cast<const f32x4*>(in + ((fc * SH::DVT1 + dt) * WAVE + l) * 4);
     }
   }
-  const Frag<T> ones = ones_col0<T>();
+  const Frag<T> ones = ones_all<T>();
   // projection fragments, held for the whole sweep: built from W by each wave
   FreqSlice<T, D, FW, NS> fs;
   fs.load(a.W1 + (size_t)h * a.w_stride, NS ? a.W2 + (size_t)h * a.w_stride : nullptr, w * FW);
-  Frag<T> sf[SH::DVT1][SH::FT];
-  if (!CAUSAL) {
+  // this wave's rows of the state as operand fragments, for every wave
+  auto store_state = [&]() {
 #pragma unroll
-    for (int dt = 0; dt < SH::DVT1; ++dt)
+    for (int ft = 0; ft < SH::FT; ++ft) {
 #pragma unroll
-      for (int ft = 0; ft < SH::FT; ++ft) sf[dt][ft] = pair_tiles<T>(S[2 * ft][dt], S[2 * ft + 1][dt]);
-  }
+      for (int dt = 0; dt < SH::DVT; ++dt)
+        SB[dt][w * SH::FT + ft][l] = pair_tiles<T>(S[2 * ft][dt], S[2 * ft + 1][dt]);
+      const Frag<T> z = pair_tiles<T>(S[2 * ft][SH::DVT], S[2 * ft + 1][SH::DVT]);
+      if (r == 0) SZ[w * SH::FT + ft][g] = z;
+    }
+  };
+  if (!CAUSAL) store_state();   // ordered by the first staging barrier
 
   for (int c = c0; c < c1; ++c) {
     const int tok0 = c * CH;
     // no barrier before the staging stores: every read of the staging buffers
-    // (projections, value fragments) precedes the previous chunk's last
-    // readout barrier
-    sq.store(XQ, SSQ);
-    if (CAUSAL) sk.store(XK, SSK);
-    if (CAUSAL) sv.store(XV);
-    __syncthreads();
+    // is in the first phase, which the previous chunk's second barrier ends
+    sq.store(XQ, SCQ, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tok0 + t < a.N); });
+    if (CAUSAL) {
+      sk.store(XK, SCK, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tok0 + t < a.N); });
+      sv.store(XV);
+    }
+    __syncthreads();   // rows staged; the previous chunk's fragments are read
     // next chunk's rows
     {
       const int t1 = c + 1 < c1 ? tok0 + CH : tok0;   // the last chunk refetches itself (unused)
@@ -271,155 +311,141 @@ __global__ __launch_bounds__(NW * WAVE) void k_fwd_sweep(FwdArgs a) {
       if (CAUSAL) sk.fetch(K, t1, a.N);
       if (CAUSAL) sv.fetch(V, t1, a.N);
     }
-    // the earlier groups' sums for this chunk (rows past N read row N-1, unused)
-    float4 old_n[ADD ? TT / QG : 1][ADD ? NIT : 1];
-    float old_d[ADD ? TT / QG : 1][ADD ? NIT : 1];
+    // the earlier groups' sums for this wave's rows (rows past N read zero)
+    const RowBuf nb(a.acc_num + (size_t)bh * a.N * SH::DV, SH::DV, ADD ? tok0 : 0, a.N, CH);
+    const RowBuf db(a.acc_den + (size_t)bh * a.N, 1, ADD ? tok0 : 0, a.N, CH);
+    f32x4 old_n[ADD ? NDT : 1];
+    float old_d = 0.f;
     if (ADD) {
 #pragma unroll
-      for (int q = 0; q < TT / QG; ++q)
-#pragma unroll
-        for (int k = 0; k < NIT; ++k) {
-          const int it = threadIdx.x + k * SH::NT;
-          const size_t row = (size_t)bh * a.N + min(tok0 + q * QG * 16 + it / C4, a.N - 1);
-          if (it < QG * 16 * C4) {
-            old_n[q][k] = *reinterpret_cast<const float4*>(a.acc_num + row * SH::DV + 4 * (it % C4));
-            old_d[q][k] = a.acc_den[row];
-          }
-        }
+      for (int k = 0; k < NDT; ++k)
+        if (part * NDT + k < SH::DVT)
+          old_n[k] = nb.load_f4(((tq * 16 + r) * SH::DV + (part * NDT + k) * 16 + 4 * g) * 4);
+      old_d = db.load_f1((tq * 16 + r) * 4);
     }
 
-    Frag<T> pq[SH::FT][TT];
-    Frag<T> pk[CAUSAL ? SH::FT : 1][TT];
+    if (CAUSAL) store_state();   // the state before this chunk
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       ProjT<T> p[SH::PR];
-      typename StX::Ssq ssq;
-      project_tile_lds<T, D, FW, NS, StX::LD>(fs, XQ, SSQ, tt, p, ssq);
-      float sc = row_scale(ssq, inv_c, a.s_const, tok0 + tt * 16 + r < a.N);
+      float sc;
+      project_tile_lds<T, D, FW, NS, StX::LD>(fs, XQ, SCQ, tt, p, sc);
 #pragma unroll
-      for (int ft = 0; ft < SH::FT; ++ft) pq[ft][tt] = features<T, SH::FT, NS>(p, ft, sc, fv);
-      if (CAUSAL) {
-        project_tile_lds<T, D, FW, NS, StX::LD>(fs, XK, SSK, tt, p, ssq);
-        sc = row_scale(ssq, inv_c, a.s_const, tok0 + tt * 16 + r < a.N);
+      for (int ft = 0; ft < SH::FT; ++ft) PQ[tt][w * SH::FT + ft][l] = features<T, SH::FT, NS>(p, ft, sc, fv);
+    }
+    Frag<T> vf[CAUSAL ? NDT : 1][KT];
+    if (CAUSAL) {
 #pragma unroll
-        for (int ft = 0; ft < SH::FT; ++ft) {
-          pk[ft][tt] = features<T, SH::FT, NS>(p, ft, sc, fv);
-          store_frag_nm<T>(PT[w], LDP, tt * 16, (2 * ft) * 16, (2 * ft + 1) * 16, pk[ft][tt]);
+      for (int tt = 0; tt < TT; ++tt) {
+        ProjT<T> p[SH::PR];
+        float sc;
+        project_tile_lds<T, D, FW, NS, StX::LD>(fs, XK, SCK, tt, p, sc);
+#pragma unroll
+        for (int ft = 0; ft < SH::FT; ++ft)
+          store_frag_nm<T>(PT[w], LDP, tt * 16, (2 * ft) * 16, (2 * ft + 1) * 16, features<T, SH::FT, NS>(p, ft, sc, fv));
+      }
+      // state update S' += phi(K)^T [V | 1] with this wave's transposed phi(K)
+#pragma unroll
+      for (int ks = 0; ks < KT; ++ks) {
+        Frag<T> va[SH::DVT];
+#pragma unroll
+        for (int dt = 0; dt < SH::DVT; ++dt)
+          va[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XV), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
+#pragma unroll
+        for (int fc = 0; fc < SH::FC; ++fc) {
+          const Frag<T> pkt = lds_tr_frag<T>(PT[w], LDP, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, fc * 16);
+#pragma unroll
+          for (int dt = 0; dt < SH::DVT; ++dt) mma(S[fc][dt], pkt, va[dt]);
+          mma(S[fc][SH::DVT], pkt, ones);
         }
       }
+      // this wave's value columns for the second phase
+#pragma unroll
+      for (int k = 0; k < NDT; ++k)
+#pragma unroll
+        for (int ks = 0; ks < KT; ++ks) {
+          const int dt = part * NDT + k < SH::DVT ? part * NDT + k : 0;
+          vf[k][ks] = lds_tr_frag<T>(reinterpret_cast<const T*>(XV), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
+        }
     }
+    __syncthreads();   // every wave's fragments complete
 
-    // state operand for the readout: rows = value columns, k = this wave's
-    // features (the non-causal total state is converted once, before the loop)
-    if (CAUSAL) {
+    if (part * NDT < SH::DVT) {
+      Frag<T> pq[NFT];
 #pragma unroll
-      for (int dt = 0; dt < SH::DVT1; ++dt)
+      for (int ft = 0; ft < NFT; ++ft) pq[ft] = PQ[tq][ft][l];
+      // intra-chunk kernel matrix, transposed: rows = key tokens, cols = query tokens
+      // (as a high and a low operand: rounded once, a whole row of it would
+      // carry more error than the features it is made of)
+      Frag<T> ap[CAUSAL ? KT : 1], al[CAUSAL ? KT : 1];
+      if (CAUSAL) {
+        f32x4 at[2 * KT];
 #pragma unroll
-        for (int ft = 0; ft < SH::FT; ++ft) sf[dt][ft] = pair_tiles<T>(S[2 * ft][dt], S[2 * ft + 1][dt]);
-    }
-
-    // intra-chunk kernel matrix, transposed: rows = key tokens, cols = query tokens
-    Frag<T> ap[CAUSAL ? KT : 1][TT];
-    if (CAUSAL) {
-#pragma unroll
-      for (int tq = 0; tq < TT; ++tq) {
-        f32x4 at[TT];
-#pragma unroll
-        for (int tk = 0; tk < TT; ++tk) {
+        for (int tk = 0; tk < 2 * KT; ++tk) {
           at[tk] = zero4();
-          if (tk <= tq) {
+          if (tk < TT && tk <= tq) {
 #pragma unroll
-            for (int ft = 0; ft < SH::FT; ++ft) mma(at[tk], pk[ft][tk], pq[ft][tq]);
+            for (int ft = 0; ft < NFT; ++ft)
+              mma(at[tk],
+                  load_frag_nm<T>(PT[ft / SH::FT], LDP, tk * 16, (2 * (ft % SH::FT)) * 16, (2 * (ft % SH::FT) + 1) * 16),
+                  pq[ft]);
             if (tk == tq) {
 #pragma unroll
-              for (int i = 0; i < 4; ++i)
-                if (4 * g + i > r) at[tk][i] = 0.f;
+              for (int i = 0; i < 4; ++i) at[tk][i] = 4 * g + i > r ? 0.f : at[tk][i];
             }
           }
         }
 #pragma unroll
-        for (int ks = 0; ks < KT; ++ks) ap[ks][tq] = pair_tiles<T>(at[2 * ks], 2 * ks + 1 < TT ? at[(2 * ks + 1) % TT] : zero4());
+        for (int ks = 0; ks < KT; ++ks) split_pair<T>(at[2 * ks], at[2 * ks + 1], ap[ks], al[ks]);
       }
-    }
-
-    Frag<T> vf[CAUSAL ? SH::DVT : 1][KT];
-    if (CAUSAL) {
+      f32x4 acc[NDT], zn = zero4();
 #pragma unroll
-      for (int dt = 0; dt < SH::DVT; ++dt)
+      for (int k = 0; k < NDT; ++k) acc[k] = zero4();
 #pragma unroll
-        for (int ks = 0; ks < KT; ++ks) vf[dt][ks] = lds_tr_frag<T>(reinterpret_cast<const T*>(XV), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
-    }
-
-    // readout partials, reduced across waves in groups of QG query tiles
+      for (int ft = 0; ft < NFT; ++ft) {
 #pragma unroll
-    for (int q0 = 0; q0 < TT; q0 += QG) {
-      if (q0 > 0) __syncthreads();
-#pragma unroll
-      for (int qq = 0; qq < QG; ++qq) {
-        const int tq = q0 + qq;
-#pragma unroll
-        for (int dt = 0; dt < SH::DVT1; ++dt) {
-          f32x4 acc = zero4();
-          if (CAUSAL) {
-#pragma unroll
-            for (int ks = 0; ks < KT; ++ks)
-              if (32 * ks <= 16 * tq + 15) mma(acc, dt < SH::DVT ? vf[dt][ks] : ones, ap[ks][tq]);
-          }
-#pragma unroll
-          for (int ft = 0; ft < SH::FT; ++ft) mma(acc, sf[dt][ft], pq[ft][tq]);
-          *reinterpret_cast<f32x4*>(&RED[w][qq * 16 + r][dt * 16 + 4 * g]) = acc;
-        }
+        for (int k = 0; k < NDT; ++k)
+          if (SH::DVT % NDT == 0 || part * NDT + k < SH::DVT) mma(acc[k], SB[part * NDT + k][ft][l], pq[ft]);
+        mma(zn, SZ[ft][g], pq[ft]);
       }
-      if (CAUSAL && q0 + QG >= TT) {
-        // state update S' += phi(K)^T [V | 1] with this wave's transposed phi(K)
+      if (CAUSAL) {
 #pragma unroll
         for (int ks = 0; ks < KT; ++ks)
+          if (32 * ks <= 16 * tq + 15) {
 #pragma unroll
-          for (int fc = 0; fc < SH::FC; ++fc) {
-            const Frag<T> pkt = lds_tr_frag<T>(PT[w], LDP, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, fc * 16);
-#pragma unroll
-            for (int dt = 0; dt < SH::DVT; ++dt) mma(S[fc][dt], pkt, vf[dt][ks]);
-            mma(S[fc][SH::DVT], pkt, ones);
+            for (int k = 0; k < NDT; ++k) {
+              mma(acc[k], vf[k][ks], ap[ks]);
+              if (IsBf16<T>::value) mma(acc[k], vf[k][ks], al[ks]);
+            }
+            mma(zn, ones, ap[ks]);
+            if (IsBf16<T>::value) mma(zn, ones, al[ks]);
           }
       }
-      __syncthreads();
+      // acc[k]: rows = value columns, column = token r; every row of the
+      // normaliser tile holds den of token r
+      float dn = zn[0];
+      if (ADD) dn += old_d;
+      if (ADD ? a.acc == 2 : a.acc != 0) {
+        // one frequency group's share of the numerator and denominator
 #pragma unroll
-      for (int k = 0; k < NIT; ++k) {
-        const int it = threadIdx.x + k * SH::NT;
-        if (it >= QG * 16 * C4) break;
-        const int t = it / C4, c4 = it % C4;
-        const int tok = tok0 + q0 * 16 + t;
-        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-        float dn = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-          const float4 v = *reinterpret_cast<const float4*>(&RED[ww][t][4 * c4]);
-          num.x += v.x; num.y += v.y; num.z += v.z; num.w += v.w;
-          dn += RED[ww][t][SH::DV];
-        }
-        if (tok < a.N) {
-          if (ADD || a.acc) {
-            // one frequency group's share of the numerator and denominator
-            float4* an = reinterpret_cast<float4*>(a.acc_num + ((size_t)bh * a.N + tok) * SH::DV + 4 * c4);
-            float* ad = a.acc_den + (size_t)bh * a.N + tok;
-            if (ADD) {
-              const float4 p = old_n[q0 / QG][k];
-              num.x += p.x; num.y += p.y; num.z += p.z; num.w += p.w;
-              dn += old_d[q0 / QG][k];
-            }
-            *an = num;
-            if (c4 == 0) *ad = dn;
-          } else {
-            // one reciprocal per row (v_rcp_f32, 1 ulp); den = 0 gives inf/NaN as num/0 does
-            const float inv = __builtin_amdgcn_rcpf(dn);
-            IO* o = O + (size_t)tok * SH::DV + 4 * c4;
-            o[0] = float_to_io<IO>(num.x * inv);
-            o[1] = float_to_io<IO>(num.y * inv);
-            o[2] = float_to_io<IO>(num.z * inv);
-            o[3] = float_to_io<IO>(num.w * inv);
-            if (den && c4 == 0) den[tok] = dn;
+        for (int k = 0; k < NDT; ++k)
+          if (SH::DVT % NDT == 0 || part * NDT + k < SH::DVT) {
+            if (ADD) acc[k] += old_n[k];
+            RowBuf(a.acc_num + (size_t)bh * a.N * SH::DV, SH::DV, tok0, a.N, CH)
+                .store_f4(((tq * 16 + r) * SH::DV + (part * NDT + k) * 16 + 4 * g) * 4, acc[k]);
           }
-        }
+        if (part == 0 && g == 0) RowBuf(a.acc_den + (size_t)bh * a.N, 1, tok0, a.N, CH).store_f1((tq * 16 + r) * 4, dn);
+      } else {
+        // one reciprocal per row (v_rcp_f32, 1 ulp); den = 0 gives inf/NaN as num/0 does
+        const float inv = __builtin_amdgcn_rcpf(dn);
+        const RowBuf ob(O, SH::DV, tok0, a.N, CH);
+#pragma unroll
+        for (int k = 0; k < NDT; ++k)
+          if (SH::DVT % NDT == 0 || part * NDT + k < SH::DVT) {
+            if (ADD) acc[k] += old_n[k];
+            ob.store_io4(O, ((tq * 16 + r) * SH::DV + (part * NDT + k) * 16 + 4 * g) * (int)sizeof(IO), acc[k] * inv);
+          }
+        if (den && part == 0 && g == 0) RowBuf(den, 1, tok0, a.N, CH).store_f1((tq * 16 + r) * 4, dn);
       }
     }
   }
@@ -428,7 +454,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_fwd_sweep(FwdArgs a) {
     // sequence (an empty trailing segment holds it as its carry-in).  Tile
     // (fc, dt) has rows = features 4g+i of feature tile fc (fc = 2ft: cos of
     // frequency tile ft, 2ft+1: its sin) and cols = value columns; the
-    // normaliser tile holds z in column 0.
+    // normaliser tile holds z in every column.
     const size_t F2 = 2 * (size_t)a.state_m;
     const int sdv = a.state_dv;   // value columns of the state layout, <= SH::DV
     float* so = a.state_out + (size_t)bh * F2 * (sdv + 1);
@@ -540,9 +566,9 @@ void k_fwd_readout(FwdArgs a) {
 #pragma unroll
       for (int dt = 0; dt < DVT1; ++dt) mma(acc[dt], sf[dt][ft], pq);
     }
-    // acc[dt]: rows = value columns dt*16 + 4g + i, column = token r; the
-    // normaliser tile holds den in its row 0 (lane r of lane group 0)
-    const float dn = __shfl(acc[DVT][0], r);
+    // acc[dt]: rows = value columns dt*16 + 4g + i, column = token r; every
+    // row of the normaliser tile holds den
+    const float dn = acc[DVT][0];
     const float inv = __builtin_amdgcn_rcpf(dn);   // den = 0 gives inf/NaN as num/0 does
     const RowBuf ob(O, D, tok0, a.N, CHUNK);
 #pragma unroll
@@ -625,29 +651,6 @@ __global__ __launch_bounds__(NW * WAVE) void k_feature_map(FwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// After the last frequency group: O = num / den from the fp32 sums, den out.
-// One thread per 4 value columns of one row.
-// ---------------------------------------------------------------------------
-template <class IO>
-__global__ __launch_bounds__(256) void k_fwd_finish(FwdArgs a, int dv) {
-  const size_t rows = (size_t)a.BH * a.N;
-  const int c4n = dv / 4;
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows * c4n) return;
-  const size_t row = i / c4n;
-  const int c4 = (int)(i % c4n);
-  const float4 num = *reinterpret_cast<const float4*>(a.acc_num + row * dv + 4 * c4);
-  const float dn = a.acc_den[row];
-  const float inv = __builtin_amdgcn_rcpf(dn);
-  IO* o = static_cast<IO*>(a.O) + row * dv + 4 * c4;
-  o[0] = float_to_io<IO>(num.x * inv);
-  o[1] = float_to_io<IO>(num.y * inv);
-  o[2] = float_to_io<IO>(num.z * inv);
-  o[3] = float_to_io<IO>(num.w * inv);
-  if (a.den && c4 == 0) a.den[row] = dn;
-}
-
-// ---------------------------------------------------------------------------
 // Frequency rows of a padded group: dst[h][rows][d] holds the group's
 // rows_valid rows of W, then zero rows (their features are masked to zero).
 // One thread per 4 elements.
@@ -698,30 +701,9 @@ hipError_t launch_copy_cols(const void* src, int cols_src, void* dst, int cols_d
   return hipGetLastError();
 }
 
-hipError_t launch_fwd_finish(const FwdArgs& a, bool bf16, int dv, hipStream_t st) {
-  const size_t n = (size_t)a.BH * a.N * (dv / 4);
-  const dim3 grid((unsigned)((n + 255) / 256));
-  if (bf16)
-    k_fwd_finish<u16><<<grid, 256, 0, st>>>(a, dv);
-  else
-    k_fwd_finish<float><<<grid, 256, 0, st>>>(a, dv);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Host-side dispatch.
 // ---------------------------------------------------------------------------
-// Causal sweep launch for one chunk length CH (token tiles per cross-wave
-// reduction round: fewer rounds where LDS allows).
-template <class T, int D, int FW, int NW, bool NS, bool ADD, int CH, bool MASK>
-static void launch_causal_sweep(const FwdArgs& a, dim3 grid, hipStream_t st) {
-  typedef Shape<T, D, FW, NW, NS, CH> SH;
-  constexpr int TTc = CH / 16;
-  constexpr int QG0 = (SH::DV >= 128) ? 1 : (NW >= 8 ? 2 : TTc);
-  constexpr int QG = QG0 < TTc ? QG0 : TTc;
-  k_fwd_sweep<T, D, FW, NW, NS, true, QG, ADD, CH, MASK><<<grid, SH::NT, 0, st>>>(a);
-}
-
 // The token-split readout serves bf16 shapes whose projection onto all m
 // frequencies fits one wave's registers (m_eff <= 64, state split 4 x 16).
 template <class T, int D, int FW, int NW, bool NS>
@@ -739,14 +721,13 @@ static void launch_sweep(const FwdArgs& a, bool causal, dim3 grid, hipStream_t s
     }
   }
   if (!causal) {
-    // one token tile per round: the non-causal sweep then fits several workgroups per CU
-    k_fwd_sweep<T, D, FW, NW, NS, false, 1, ADD, CHUNK, MASK><<<grid, SH::NT, 0, st>>>(a);
+    k_fwd_sweep<T, D, FW, NW, NS, false, ADD, CHUNK, MASK><<<grid, SH::NT, 0, st>>>(a);
   } else if (a.sweep_chunk == 16) {
-    launch_causal_sweep<T, D, FW, NW, NS, ADD, 16, MASK>(a, grid, st);
+    k_fwd_sweep<T, D, FW, NW, NS, true, ADD, 16, MASK><<<grid, SH::NT, 0, st>>>(a);
   } else if (a.sweep_chunk == 32) {
-    launch_causal_sweep<T, D, FW, NW, NS, ADD, 32, MASK>(a, grid, st);
+    k_fwd_sweep<T, D, FW, NW, NS, true, ADD, 32, MASK><<<grid, SH::NT, 0, st>>>(a);
   } else {
-    launch_causal_sweep<T, D, FW, NW, NS, ADD, 64, MASK>(a, grid, st);
+    k_fwd_sweep<T, D, FW, NW, NS, true, ADD, 64, MASK><<<grid, SH::NT, 0, st>>>(a);
   }
 }
 
@@ -763,7 +744,7 @@ static hipError_t run_fwd_t(const FwdArgs& a, bool causal, hipStream_t st) {
   // runs first, so it never adds) takes the masking kernel variants
   const bool masked = a.fvalid < FW * NW;
   constexpr bool CAN_MASK = FW * NW == 64;
-  if (masked && (!CAN_MASK || a.acc == 2)) return hipErrorInvalidValue;
+  if (masked && (!CAN_MASK || a.acc >= 2)) return hipErrorInvalidValue;
   if (pgrid.x > 0) {
     if constexpr (CAN_MASK) {
       if (masked) k_fwd_state<T, D, FW, NW, NS, true><<<pgrid, SH::NT, 0, st>>>(a);
@@ -779,20 +760,13 @@ static hipError_t run_fwd_t(const FwdArgs& a, bool causal, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   timing_mark(KC_FWD_SWEEP, st, true);
-  // At d = 64, m = 128 the sweep runs 4 waves of 32 frequencies (one wave per
-  // SIMD; the readout's cross-wave reduction then covers a whole 64-token
-  // chunk in one round), the state pre-pass 8 waves of 16.  Both keep the
-  // states in the same layout: feature tile 2f + (0: cos, 1: sin) of
-  // frequency tile f, whatever wave holds it.
-  constexpr int FWS = (D == 64 && FW * NW == 128) ? 32 : FW;
-  constexpr int NWS = FW * NW / FWS;
   // a later frequency group adds to the earlier groups' sums
-  if (a.acc == 2) {
-    launch_sweep<T, D, FWS, NWS, NS, true, false>(a, causal, grid, st);
+  if (a.acc >= 2) {
+    launch_sweep<T, D, FW, NW, NS, true, false>(a, causal, grid, st);
   } else if (masked) {
-    if constexpr (CAN_MASK) launch_sweep<T, D, FWS, NWS, NS, false, true>(a, causal, grid, st);
+    if constexpr (CAN_MASK) launch_sweep<T, D, FW, NW, NS, false, true>(a, causal, grid, st);
   } else {
-    launch_sweep<T, D, FWS, NWS, NS, false, false>(a, causal, grid, st);
+    launch_sweep<T, D, FW, NW, NS, false, false>(a, causal, grid, st);
   }
   timing_mark(KC_FWD_SWEEP, st, false);
   return hipGetLastError();

@@ -45,7 +45,8 @@ struct FwdArgs {
   // Frequency groups: W1/W2 point at this group's rows, w_stride is the
   // element stride between heads.  acc = 0 writes O (and den) directly; 1 and
   // 2 write / add the group's numerator and denominator into acc_num
-  // [BH][N][dv] and acc_den [BH][N] (fp32), which k_fwd_finish divides.
+  // [BH][N][dv] and acc_den [BH][N] (fp32); 3 (the last group) adds to those
+  // sums and writes O and den.
   // fvalid: rows of this group that are frequencies (the rest of the group's
   // rows are zero padding whose features the kernels mask to zero).
   int w_stride;
@@ -181,6 +182,10 @@ int fwd_state_waves(const KernelShape& ks);
 // registers.
 constexpr int state_waves_per_eu(int d, bool ns) { return (d <= 64 || !ns) ? 2 : 1; }
 int fwd_state_wgs_per_cu(const KernelShape& ks);
+// Waves per SIMD the forward sweep is compiled for.
+constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
+  return bf16 && (m > 64 || d < 128 || ch < 64 || !causal) ? 2 : 1;
+}
 
 // state (or NULL): [BH][P*sub][E]; writes the exclusive prefix (causal) into
 // slot p*sub of every segment p, or the total (non-causal) into slot 0.
@@ -192,8 +197,6 @@ int fwd_state_wgs_per_cu(const KernelShape& ks);
 hipError_t launch_state_scan(float* state, float* state_rev, int BH, int P, int sub, int E, bool causal,
                              hipStream_t st, int nread);
 hipError_t launch_fwd(const FwdArgs& a, const KernelShape& ks, bool feature_map_only, hipStream_t st);
-// O = acc_num / acc_den (io dtype), den = acc_den, after the last frequency group.
-hipError_t launch_fwd_finish(const FwdArgs& a, bool bf16, int dv, hipStream_t st);
 // dst[h][rows][d] = the first rows_valid rows of src[h] (src_stride elements
 // apart per head), zero after them: the frequency rows of a padded group.
 hipError_t launch_pad_rows(const float* src, float* dst, int H, int rows_valid, int rows, int d, int src_stride,

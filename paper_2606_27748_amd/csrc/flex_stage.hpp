@@ -238,14 +238,14 @@ struct Shape {
   static constexpr int RPAD = DVT1 * 16 + 4;
 };
 
-// Fragment with 1 in row/column 0 and 0 elsewhere: as the value operand it
-// appends the ones column of [V | 1] that produces the normaliser.
+// Fragment of ones: as the value operand it appends the ones column of
+// [V | 1] that produces the normaliser, in all 16 columns of its tile alike
+// (so every lane of a readout holds its token's denominator).
 template <class T>
-__device__ __forceinline__ Frag<T> ones_col0() {
+__device__ __forceinline__ Frag<T> ones_all() {
   Frag<T> f;
-  const float v = (threadIdx.x % 16) == 0 ? 1.0f : 0.0f;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) f.set(j, v);
+  for (int j = 0; j < 8; ++j) f.set(j, 1.0f);
   return f;
 }
 
@@ -283,6 +283,18 @@ __device__ __forceinline__ Frag<T> pair_tiles(const f32x4& a, const f32x4& b) {
   return f;
 }
 
+// Two accumulator tiles as one operand fragment split into a high and a low
+// part (bf16 hi + lo carries about 16 significant bits; fp32 keeps the value).
+template <class T>
+__device__ __forceinline__ void split_pair(const f32x4& a, const f32x4& b, Frag<T>& hi, Frag<T>& lo) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    hi.set(i, a[i]);
+    hi.set(4 + i, b[i]);
+    lo.set(i, a[i] - hi.get(i));
+    lo.set(4 + i, b[i] - hi.get(4 + i));
+  }
+}
 // Projection of one 16-token tile with the tokens as rows: p[pr] holds rows =
 // tokens tt*16 + 4g + i and cols = frequency (lane % 16) of projection tile
 // pr.  The operands of project_tile_lds are swapped (the register layouts of
