@@ -354,7 +354,7 @@ size_t ws_bytes_of(const flex_desc* d, int pass) {
   return 2 * align256(bh * P * bwd_state_floats(ks) * sizeof(float)) +
          align256(bh * (size_t)d->N * 2 * sizeof(float)) +
          align256(bh * P * bwd_dw_floats(ks) * sizeof(float)) + align256(bh * P * sizeof(float)) +
-         (bwd_split_differs(ks) ? 2 : 1) * wf + pad_bytes(d);
+         wf + pad_bytes(d);
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -620,7 +620,6 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
   a.dwpart = reinterpret_cast<float*>(base + 2 * sb + gb);
   a.dtaupart = reinterpret_cast<float*>(base + 2 * sb + gb + align256(bh * P * bwd_dw_floats(ks) * sizeof(float)));
   a.wfrag = base + 2 * sb + gb + align256(bh * P * bwd_dw_floats(ks) * sizeof(float)) + align256(bh * P * sizeof(float));
-  a.wfrag_kv = bwd_split_differs(ks) ? static_cast<char*>(a.wfrag) + align256(wfrag_bytes(ks, desc->H)) : a.wfrag;
   a.dw_stride = desc->m * desc->d;
   const PadRows pr = pad_rows_of(desc, base + ws_bytes_of(desc, FLEX_PASS_BWD));
   for (int g = 0; g < G.n; ++g) {

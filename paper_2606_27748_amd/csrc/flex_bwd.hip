@@ -236,60 +236,81 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
 
 // ---------------------------------------------------------------------------
 // dK, dV: descending sweep with the query-side suffix state R'.
+//
+// A chunk has three intervals between two barriers, the last one running on
+// into the next chunk's first:
+//   1  (waves split the frequencies) phi(Q)/den, phi(K) and the bf16 copy of R'
+//      to LDS; the R' share of dphi(K); three waves form the tiles of the
+//      intra-chunk matrix M = dO V^T - delta
+//   2  (frequencies) the M share of dphi(K), the R' update, the chain rule, dP
+//      to LDS, the next chunk's rows to LDS; (output tiles) the R' share of dV
+//      over all features; three waves form the tiles of the intra-chunk matrix
+//      A = phi(Q)/den phi(K)^T
+//   3  (output tiles) the A share of dV, dK = dP W'; (frequencies) dW' += dP^T K
+// So M and A are formed once per workgroup and no partial sum of dV crosses
+// waves; dW' stays in registers for the whole sweep.
+//
+// Bound by latency and LDS traffic: matrix and vector issue each take a third
+// of the time, and leaving any one product out gains about 7 %.  So what counts
+// is two waves per SIMD (8 waves of 16 frequencies at d = 64, m = 128; two
+// workgroups of 4 at m = 64) within 256 registers, and few LDS accesses.  us per
+// pass before (dV partials of every wave summed through LDS, dW' there too, 4
+// waves of 32 frequencies at m = 128) and after: training step d = 64, m = 128
+// (B*H = 32, N = 8192) 469 and 424, d = 128, m = 256 2561 and 2439, encoder
+// training (non-causal m = 64, B*H = 64, N = 4000) 253 and 232.
 // ---------------------------------------------------------------------------
 // ACC: add dK and dV to the values an earlier frequency group stored.  The
-// old values are loaded at the start of each chunk, ahead of the next chunk's
-// prefetch, so waiting for them never waits for that prefetch.
+// old values are loaded ahead of the next chunk's prefetch, so waiting for
+// them never waits for that prefetch.
 template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ACC, bool MASK = false>
-__global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(dkv_waves_per_eu(IsBf16<T>::value, D))))
+void k_bwd_dkv(BwdArgs a) {
   typedef Shape<T, D, FW, NW, NS, BWD_CHUNK> SH;
   typedef typename Io<T>::type IO;
-  typedef RowStage<IO, D, SH::NT, SH::CH> StX;
-  typedef RowStage<IO, SH::DV, SH::NT, SH::CH> StV;
+  // With at least two threads per 16-byte vector of a chunk's rows, half of the
+  // waves stage K and Q and the other half V and dO.
+  constexpr int HALVES = 2 * SH::CH * D * (int)sizeof(IO) / 16 <= SH::NT ? 2 : 1;
+  constexpr int NTH = SH::NT / HALVES;
+  typedef RowStage<IO, D, NTH, SH::CH> StX;
+  typedef StX StV;
+  static_assert(D == SH::DV, "one stage type");
   typedef WTSlice<T, D, FW, NS> WTS;
   constexpr int DT = D / 16;
-  constexpr int KG = (SH::DVT1 + 1) / 2;
-  constexpr int QG = (NW >= 8 || D >= 128) ? 1 : 2;
-  constexpr int RP = SH::DV + 4;                 // row stride of the dV reduction rows
-  constexpr int C4 = SH::DV / 4;                 // float4 columns of a dV row
-  constexpr int NIT = (QG * 16 * C4 + SH::NT - 1) / SH::NT;   // dV items per thread and round
-  constexpr int TT0STEP = DT < NW ? NW / DT : 1; // token-tile step of a wave's dK tiles
-  constexpr int NDK = (DT + NW - 1) / NW;        // d tiles per wave (at most)
-  constexpr int NTK = DT < NW ? (SH::TT + TT0STEP - 1) / TT0STEP : SH::TT;   // token tiles per d tile
+  constexpr int NFT = SH::M / 16;                // frequency tiles of all waves
+  constexpr int KG = (SH::DVT1 + 1) / 2;         // k-steps over [V | 1]
+  constexpr int NOT = (DT * SH::TT + NW - 1) / NW;   // dV (and dK) tiles per wave (at most)
   constexpr int RLP = SH::DV + 4;                // row stride of the bf16 R' copy, [feature][value col]
-  constexpr int LDP = SH::FC * 16 + 4;           // row stride of the per-wave [token][row] blocks
-  // Each wave owns one slot of REDRL: its bf16 copy of R' and, once its own
-  // reads of that copy are done, its dV partials.  No other wave touches the
-  // slot between the chunk's staging barrier and its dV reduction, so neither the
-  // copy nor the partials need a barrier before they are written.
-  constexpr int RED_W = QG * 16 * RP * 4;
-  constexpr int RL_W = SH::FC * 16 * RLP * (int)sizeof(T);
-  constexpr int SLOT = RED_W > RL_W ? RED_W : RL_W;
-  // Staging is double-buffered by chunk parity where LDS allows (d <= 64).
-  // There the next chunk is staged before this chunk's dP barrier, which then
-  // also orders those stores before the next chunk's reads.  K rows and norms
-  // are read after the dP barrier too (dK, dW', dtau), so they take three
-  // buffers.
-  constexpr int NBUF = D <= 64 ? 2 : 1;
-  constexpr bool EARLY = NBUF == 2;
-  constexpr int NKB = EARLY ? 3 : 1;
-  __shared__ __attribute__((aligned(16))) IO XQ2[NBUF][StX::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) IO XK2[NKB][StX::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) IO XV2[NBUF][StV::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) IO XDO2[NBUF][StV::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) T PT[NW][SH::CH * LDP];   // phi(Q)/den, then dP: [token][row]
-  __shared__ __attribute__((aligned(16))) char REDRL[NW * SLOT];
-  __shared__ __attribute__((aligned(16))) float DWL[NW][SH::PR * DT * WAVE * 4];
-  __shared__ float GS2[NBUF][SH::CH][2];
-  __shared__ typename StX::Ssq SSQ2[NBUF][SH::CH], SSK2[NKB][SH::CH];
+  constexpr int NDX = FragBlock<T, D, FW, NS>::NT_ * WAVE;   // dX fragments per wave
+  static_assert(SH::TT == 2 && SH::KT == 1 && NW >= 4, "32-token chunks, three waves for the intra-chunk tiles");
+  // rows read in interval 1 only (Q, V) need one staging buffer (stored in
+  // interval 2), those read in interval 3 too (K, dO) two, by chunk parity
+  __shared__ __attribute__((aligned(16))) IO XQ[CAUSAL ? StX::LDS_ELEMS : 8];
+  __shared__ __attribute__((aligned(16))) IO XK2[2][StX::LDS_ELEMS];
+  __shared__ __attribute__((aligned(16))) IO XV[StV::LDS_ELEMS];
+  __shared__ __attribute__((aligned(16))) IO XDO2[CAUSAL ? 2 : 1][CAUSAL ? StV::LDS_ELEMS : 8];
+  __shared__ Frag<T> PT[CAUSAL ? SH::TT : 1][CAUSAL ? NFT : 1][WAVE];   // phi(Q)/den, operand fragments
+  __shared__ Frag<T> DP[SH::TT][NW * WTS::KP][WAVE];   // dP, operand fragments (k = pairs of projection row tiles)
+  __shared__ __attribute__((aligned(16))) T RL[NW][SH::FC * 16 * RLP];   // R' copy
+  __shared__ Frag<T> PK[SH::TT][NFT][WAVE];      // phi(K), operand fragments
+  __shared__ Frag<T> MP[SH::TT][WAVE], AP[SH::TT][WAVE];   // M and A: [key tile], k = query tokens
+  // dX fragments of every wave's projection rows: held in registers with four
+  // waves (each then has DT / 4 d tiles), in LDS with eight
+  constexpr bool DX_LDS = NW > 4;
+  constexpr int NDK = DT > NW ? DT / NW : 1;     // d tiles of one wave
+  static_assert(DT <= NW ? NW % DT == 0 : DT % NW == 0, "a wave keeps its d tiles");
+  __shared__ Frag<T> DXL[DX_LDS ? NW : 1][DX_LDS ? NDX : 1];
+  __shared__ __attribute__((aligned(16))) float SCQ[SH::CH], SCK[SH::CH], INV[SH::CH], DEL[SH::CH];
+  // -delta as a (hi, lo) pair of operand rows and a row of zeros (delta_frag)
+  constexpr int DLD = SH::CH + 8;
+  __shared__ __attribute__((aligned(16))) T DLT2[2][3 * DLD];
+  __shared__ typename StX::Ssq SSK2[2][SH::CH];
   __shared__ float TRED[SH::NT];
-  __shared__ __attribute__((aligned(16))) float GP[SH::CH][NW][4];   // per-lane-group shares of g
-  typedef float RedRow[QG * 16][RP];
-  auto RED = [&](int ww) -> RedRow& { return *reinterpret_cast<RedRow*>(REDRL + ww * SLOT); };
+  __shared__ __attribute__((aligned(16))) float GP[SH::CH][NW + 4];   // every wave's share of g
 
   const WgCoord wc = wg_coord(a.segments, a.H, a.BH);
   const int seg = wc.seg, bh = wc.bh, h = bh % a.H;
-  const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  int l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
   const int fv = slice_valid<MASK, FW>(a.fvalid, w);
   const int c0 = seg * a.chunks_per_seg;
   const int c1 = min(c0 + a.chunks_per_seg, a.nchunks);
@@ -299,18 +320,24 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
   const IO* dO = static_cast<const IO*>(a.dO) + (size_t)bh * a.N * SH::DV;
   const float* gst = a.gstats + (size_t)bh * a.N * 2;
   float* dK = a.dK + (size_t)bh * a.N * D;
-  T* RLw = reinterpret_cast<T*>(REDRL + w * SLOT);   // this wave's R' copy
   float* dV = a.dV + (size_t)bh * a.N * SH::DV;
 
-  StX sq, sk;
-  StV sv, sdo;
+  // the non-causal sweep reads no query-side rows: its R' is the total
+  const int half = HALVES == 2 ? w / (NW / 2) : 0;
+  constexpr int SV = HALVES == 2 ? 0 : 2, SDO = SV + 1;   // K and Q in st[0], st[1]; V and dO here
+  StX st[4 / HALVES];
   float2 gs_next = make_float2(0.f, 0.f);
-  if (c0 < c1) {
-    const int t1 = (c1 - 1) * SH::CH;
-    sq.fetch(Q, t1, a.N); sk.fetch(K, t1, a.N); sv.fetch(V, t1, a.N); sdo.fetch(dO, t1, a.N);
-    gs_next = load_gs(gst, t1, a.N, SH::CH);
-  }
-  const Frag<T>* wproj = FragBlock<T, D, FW, NS>::proj(a.wfrag_kv, h, NW, w);
+  auto fetch = [&](int t1) {
+    st[0].fetch(HALVES == 2 && half ? V : K, t1, a.N);
+    if (CAUSAL) st[1].fetch(HALVES == 2 && half ? dO : Q, t1, a.N);
+    if (HALVES == 1) st[SV].fetch(V, t1, a.N);
+    if (CAUSAL) {
+      if (HALVES == 1) st[SDO].fetch(dO, t1, a.N);
+      gs_next = load_gs(gst, t1, a.N, SH::CH, StX::tid());
+    }
+  };
+  if (c0 < c1) fetch((c1 - 1) * SH::CH);
+  const Frag<T>* wproj = FragBlock<T, D, FW, NS>::proj(a.wfrag, h, NW, w);
   const auto inv_c = inv_c_of<T>(a.tau[h]);
 
   f32x4 RT[SH::DVT1][SH::FC];
@@ -337,176 +364,169 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
       for (int fc = 0; fc < SH::FC; ++fc)
         RT[dt][fc] = *reinterpret_cast<const f32x4*>(in + state_off<SH>(w, dt, fc, l));
   }
+  // this wave's dW' partial starts from the query side's (dQ sweep) partial
+  // of this workgroup position
+  f32x4 DW[SH::PR][DT];
   {
-    // this wave's dW' partial starts from the query side's (dQ sweep) partial
-    // of this workgroup position
     const size_t nmat = NS ? 2 : 1;
     const float* qpart = a.dwpart + (((size_t)0 * a.BH + bh) * a.segments + seg) * nmat * SH::M * D;
 #pragma unroll
     for (int pr = 0; pr < SH::PR; ++pr)
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
-        *reinterpret_cast<f32x4*>(&DWL[w][((pr * DT + dt) * WAVE + l) * 4]) =
-            *reinterpret_cast<const f32x4*>(qpart + dw_tile_off<SH, D>(w, pr, dt, l));
+        DW[pr][dt] = *reinterpret_cast<const f32x4*>(qpart + dw_tile_off<SH, D>(w, pr, dt, l));
   }
   float dtau_acc = 0.f;
 
-  // dX fragments of this wave's d tile: held for the whole sweep when every
-  // wave has one d tile (DT <= NW), else loaded per chunk ahead of the barrier
-  Frag<T> wf[NW][WTS::KP][WTS::NSPLIT];
-  auto load_wf = [&](int dt) {
+  // dX fragments of this wave's d tiles w % DT (+ NW, ...)
+  Frag<T> wf[DX_LDS ? 1 : NDK][DX_LDS ? 1 : NW][WTS::KP];
+  if constexpr (DX_LDS) {
+    for (int i = threadIdx.x; i < NW * NDX; i += SH::NT)
+      DXL[i / NDX][i % NDX] = FragBlock<T, D, FW, NS>::dx(a.wfrag, h, NW, i / NDX)[i % NDX];
+  } else {
 #pragma unroll
-    for (int ww = 0; ww < NW; ++ww) {
-      const Frag<T>* wd = FragBlock<T, D, FW, NS>::dx(a.wfrag_kv, h, NW, ww);
+    for (int kd = 0; kd < NDK; ++kd)
 #pragma unroll
-      for (int ks = 0; ks < WTS::KP; ++ks)
+      for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
-        for (int sp = 0; sp < WTS::NSPLIT; ++sp) wf[ww][ks][sp] = wd[((sp * DT + dt) * WTS::KP + ks) * WAVE + l];
+        for (int ks = 0; ks < WTS::KP; ++ks)
+          wf[kd][ww][ks] = FragBlock<T, D, FW, NS>::dx(a.wfrag, h, NW, ww)[((w % DT + kd * NW) * WTS::KP + ks) * WAVE + l];
+  }
+  if (CAUSAL) {   // the zero tile of either intra-chunk matrix, and the zero row of -delta
+    if (w < 2) {
+      Frag<T> z;
+      z.zero();
+      (w == 0 ? MP : AP)[1][l] = z;
+    }
+    for (int i = threadIdx.x; i < 2 * 3 * DLD; i += SH::NT) DLT2[i / (3 * DLD)][i % (3 * DLD)] = T(0.0f);
+    __syncthreads();
+  }
+  // Store the prefetched rows into the buffers of sweep step i, which takes
+  // the chunk at token tn, and prefetch the chunk before it (itself again when
+  // it is the first: the prefetch is issued on every step, from an in-range chunk).
+  auto stage = [&](int i, int cn) {
+    const int par = i & 1, tn = cn * SH::CH;
+    if (HALVES == 1 || half == 0) {
+      st[0].store(XK2[par], SCK, [&](int t, auto ssq) {
+        SSK2[par][t] = ssq;
+        return row_scale(ssq, inv_c, a.s_const, tn + t < a.N);
+      });
+      if (CAUSAL) st[1].store(XQ, SCQ, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tn + t < a.N); });
+    }
+    if (HALVES == 1 || half == 1) {
+      st[SV].store(XV);
+      if (CAUSAL) {
+        st[SDO].store(XDO2[par]);
+        const int t = StX::tid();
+        if (t < SH::CH) {
+          INV[t] = gs_next.x;
+          DEL[t] = gs_next.y;
+          float hi, lo;
+          neg_split<T>(gs_next.y, hi, lo);
+          DLT2[par][t] = (T)hi;
+          DLT2[par][DLD + t] = (T)lo;
+        }
+      }
+    }
+    fetch((cn - 1 >= c0 ? cn - 1 : cn) * SH::CH);
+  };
+  // the bf16 copy of R' and the R' operand fragments of feature tile fc, from one conversion
+  auto r_frags = [&](int fc, Frag<T> (&rp)[KG], bool store) {
+#pragma unroll
+    for (int kd = 0; kd < KG; ++kd) {
+      rp[kd] = pair_tiles<T>(RT[2 * kd][fc], 2 * kd + 1 < SH::DVT1 ? RT[2 * kd + 1][fc] : zero4());
+      if (store) {
+        if (2 * kd + 1 < SH::DVT) {
+          store_frag_nm<T>(RL[w], RLP, fc * 16, (2 * kd) * 16, (2 * kd + 1) * 16, rp[kd]);
+        } else if (2 * kd < SH::DVT) {
+          store_tile_nm<T>(RL[w], RLP, fc * 16, (2 * kd) * 16, RT[2 * kd][fc]);
+        }
+      }
     }
   };
-  // held for the whole sweep with up to 4 waves; 8-wave workgroups (two
-  // waves per SIMD, 256 registers) load them per chunk
-  constexpr bool HOLD_WF = DT <= NW && NW <= 4;
-  if (HOLD_WF) load_wf(w % DT);
-  // Store the prefetched rows into the buffers of sweep step i and prefetch
-  // chunk cn - 1 (chunk cn itself again when cn is the last one: the prefetch
-  // is issued on every step, from an in-range chunk).
-  auto stage = [&](int i, int cn) {
-    const int par = NBUF == 2 ? i & 1 : 0, kp = i % NKB;
-    sq.store(XQ2[par], SSQ2[par]); sk.store(XK2[kp], SSK2[kp]); sv.store(XV2[par]); sdo.store(XDO2[par]);
-    if (threadIdx.x < SH::CH) {
-      GS2[par][threadIdx.x][0] = gs_next.x;
-      GS2[par][threadIdx.x][1] = gs_next.y;
+  // One tile (query tile tq, key tile tk) of an intra-chunk matrix, masked to
+  // keys at or before the query, into its half of the operand fragment.
+  auto store_intra = [&](Frag<T>* M, int tq, int tk, f32x4 v) {
+    if (tq == tk) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = 4 * g + i >= r ? v[i] : 0.f;
     }
-    const int t1 = (cn - 1 >= c0 ? cn - 1 : cn) * SH::CH;
-    sq.fetch(Q, t1, a.N); sk.fetch(K, t1, a.N); sv.fetch(V, t1, a.N); sdo.fetch(dO, t1, a.N);
-    gs_next = load_gs(gst, t1, a.N, SH::CH);
+    T* o = reinterpret_cast<T*>(&M[tk * WAVE + l]) + 4 * tq;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = (T)v[i];
   };
   // Projection fragments, reloaded per chunk (held for the whole sweep they
   // would not fit the registers).
   FreqSlice<T, D, FW, NS> fs;
-  if (EARLY) {
-    fs.load_frags(wproj);
-    if (c0 < c1) stage(0, c1 - 1);
-    __syncthreads();
+  if (!CAUSAL) {   // one R' for every chunk
+#pragma unroll
+    for (int fc = 0; fc < SH::FC; ++fc) {
+      Frag<T> rp[KG];
+      r_frags(fc, rp, true);
+    }
   }
+  if (c0 < c1) {
+    fs.load_frags(wproj);
+    stage(0, c1 - 1);
+  }
+  __syncthreads();
   for (int c = c1 - 1; c >= c0; --c) {
-    // This chunk's staging buffers.  Double-buffered, no store into them
-    // needs a barrier of its own: the chunk that last read them (two back;
-    // three back for K) is separated from the store by a dP barrier.
     const int step = c1 - 1 - c;
-    const int par = NBUF == 2 ? step & 1 : 0, kp = step % NKB;
-    IO* XQ = XQ2[par];
-    IO* XK = XK2[kp];
-    IO* XV = XV2[par];
-    IO* XDO = XDO2[par];
-    float (*GS)[2] = GS2[par];
-    typename StX::Ssq* SSQ = SSQ2[par];
-    typename StX::Ssq* SSK = SSK2[kp];
+    const int par = step & 1;
+    IO* XK = XK2[par];
+    IO* XDO = XDO2[CAUSAL ? par : 0];
+    const T* DLT = DLT2[par];
     const int tok0 = c * SH::CH;
-    // this chunk's projection fragments (with early staging, issued at the
-    // end of the previous chunk, before its dW' products)
-    if (!EARLY) fs.load_frags(wproj);
-    // With early staging this is the chunk's one barrier besides the dP
-    // barrier: after it, every wave has finished the previous chunk's reads
-    // of the other waves' LDS blocks (dP, dV partials, g shares), which this
-    // chunk writes again before its dP barrier.
-    if (EARLY) __syncthreads();
     const RowBuf dkb(dK, D, tok0, a.N, SH::CH), dvb(dV, SH::DV, tok0, a.N, SH::CH);
-    // an earlier group's dK and dV of this chunk (rows past N read zero)
-    f32x4 old_k[ACC ? NDK : 1][ACC ? NTK : 1];
-    f32x4 old_v[ACC ? SH::TT / QG : 1][ACC ? NIT : 1];
-    if (ACC) {
-#pragma unroll
-      for (int kd = 0; kd < NDK; ++kd)
-#pragma unroll
-        for (int kt = 0; kt < NTK; ++kt) {
-          const int dt = w % DT + kd * NW, tt = (DT < NW ? w / DT : 0) + kt * TT0STEP;
-          if (dt < DT && tt < SH::TT) old_k[kd][kt] = dkb.load_f4(((tt * 16 + r) * D + dt * 16 + 4 * g) * 4);
-        }
-#pragma unroll
-      for (int q = 0; q < SH::TT / QG; ++q)
-#pragma unroll
-        for (int k = 0; k < NIT; ++k) {
-          const int it = threadIdx.x + k * SH::NT;
-          if (it < QG * 16 * C4)
-            old_v[q][k] = dvb.load_f4(((q * QG * 16 + it / C4) * SH::DV + 4 * (it % C4)) * 4);
-        }
-    }
-    if (!EARLY) {
-      if (NBUF == 1) __syncthreads();   // single buffer: the previous chunk's reads are done
-      stage(step, c);
-      __syncthreads();
-    }
 
+    // ---- interval 1
     // phi(Q)/den as [token][feature] in the wave's LDS block: read back as it is
-    // for the intra-chunk kernel matrix, transposed for the token sums (the
-    // non-causal backward of K and V uses only the total R')
+    // for A, transposed for the token sums
     if (CAUSAL) {
 #pragma unroll
       for (int tt = 0; tt < SH::TT; ++tt) {
         ProjT<T> p[SH::PR];
-        typename StX::Ssq ssq;
-        project_tile_lds<T, D, FW, NS, StX::LD>(fs, XQ, SSQ, tt, p, ssq);
-        const float sc = row_scale(ssq, inv_c, a.s_const, tok0 + tt * 16 + r < a.N) * GS[tt * 16 + r][0];
+        float sc;
+        project_tile_lds<T, D, FW, NS, StX::LD>(fs, XQ, SCQ, tt, p, sc);
+        sc *= INV[tt * 16 + r];
 #pragma unroll
         for (int ft = 0; ft < SH::FT; ++ft)
-          store_frag_nm<T>(PT[w], LDP, tt * 16, (2 * ft) * 16, (2 * ft + 1) * 16,
-                           features<T, SH::FT, NS>(p, ft, sc, fv));
+          PT[tt][w * SH::FT + ft][l] = features<T, SH::FT, NS>(p, ft, sc, fv);
       }
     }
-    // phi(K) and its P2-derivative fragments
-    Frag<T> phk[SH::FT][SH::TT], psk[SH::FT][SH::TT];
+    // phi(K), with the factors of the chain rule kept in fp32: cos P1, sin P1,
+    // s e cos P2 and s e sin P2 (stationary: s e alone)
+    f32x4 kc[SH::FT][SH::TT], ks1[SH::FT][SH::TT], kw[SH::FT][SH::TT], kz[NS ? SH::FT : 1][SH::TT];
 #pragma unroll
     for (int tt = 0; tt < SH::TT; ++tt) {
       ProjT<T> p[SH::PR];
-      typename StX::Ssq ssq;
-      project_tile_lds<T, D, FW, NS, StX::LD>(fs, XK, SSK, tt, p, ssq);
-      const float sc = row_scale(ssq, inv_c, a.s_const, tok0 + tt * 16 + r < a.N);
+      float sc;
+      project_tile_lds<T, D, FW, NS, StX::LD>(fs, XK, SCK, tt, p, sc);
 #pragma unroll
-      for (int ft = 0; ft < SH::FT; ++ft) features_psi<T, SH::FT, NS>(p, ft, sc, phk[ft][tt], psk[ft][tt], fv);
-    }
-    // intra-chunk M[i][j] = dO_i . V_j - delta_i and A[i][j] = phi(Q_i)/den_i . phi(K_j), i >= j
-    Frag<T> mp[CAUSAL ? SH::KT : 1][SH::TT], ap[CAUSAL ? SH::KT : 1][SH::TT];
-    if (CAUSAL) {
+      for (int ft = 0; ft < SH::FT; ++ft) {
+        Frag<T> f;
 #pragma unroll
-      for (int tk = 0; tk < SH::TT; ++tk) {
-        f32x4 m[SH::TT], at[SH::TT];
-#pragma unroll
-        for (int tq = 0; tq < SH::TT; ++tq) {
-          m[tq] = zero4();
-          at[tq] = zero4();
-          if (tq >= tk) {
-#pragma unroll
-            for (int kd = 0; kd < SH::DV / 32; ++kd) {
-              Frag<T> ao, bv;
-              lds_row8(ao, XDO + (tq * 16 + r) * StV::LD, kd * 32 + 8 * g);
-              lds_row8(bv, XV + (tk * 16 + r) * StV::LD, kd * 32 + 8 * g);
-              mma(m[tq], ao, bv);
-            }
-#pragma unroll
-            for (int ft = 0; ft < SH::FT; ++ft)
-              mma(at[tq], load_frag_nm<T>(PT[w], LDP, tq * 16, (2 * ft) * 16, (2 * ft + 1) * 16), phk[ft][tk]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const bool keep = tq > tk || 4 * g + i >= r;
-              const float md = m[tq][i] - GS[tq * 16 + 4 * g + i][1];
-              m[tq][i] = keep ? md : 0.f;
-              at[tq][i] = keep ? at[tq][i] : 0.f;
-            }
+        for (int i = 0; i < 4; ++i) {
+          const float se = !MASK || ft * 16 + 4 * g + i < fv ? sc : 0.f;
+          float s1, c1v;
+          sincos_rev(p[ft][i], s1, c1v);
+          float wv = se;
+          if constexpr (NS) {
+            float s2, c2;
+            sincos_rev(p[SH::FT + ft][i], s2, c2);
+            wv = se * c2;
+            kz[ft][tt][i] = se * s2;
           }
+          kc[ft][tt][i] = c1v;
+          ks1[ft][tt][i] = s1;
+          kw[ft][tt][i] = wv;
+          f.set(i, c1v * wv);
+          f.set(4 + i, s1 * wv);
         }
-#pragma unroll
-        for (int ks = 0; ks < SH::KT; ++ks) {
-          mp[ks][tk] = pair_tiles<T>(m[2 * ks], m[2 * ks + 1]);
-          ap[ks][tk] = pair_tiles<T>(at[2 * ks], at[2 * ks + 1]);
-        }
+        PK[tt][w * SH::FT + ft][l] = f;
       }
     }
-    // dphi(K)^T[feature][key] = phi(Q)^T M + R'^T-rows x [V | 1].  R' is
-    // converted to operand fragments once per chunk and feature tile; the same
-    // fragments, stored as [feature][value col], are the bf16 copy of R' that
-    // the dV product reads back transposed.
+    // R' share of dphi(K)^T[feature][key] = R'^T-rows x [V | 1] + phi(Q)^T M
     f32x4 dph[SH::FC][SH::TT];
     {
       Frag<T> vf[SH::TT][KG];
@@ -526,203 +546,177 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dkv(BwdArgs a) {
 #pragma unroll
       for (int fc = 0; fc < SH::FC; ++fc) {
         Frag<T> rp[KG];
-#pragma unroll
-        for (int kd = 0; kd < KG; ++kd) {
-          rp[kd] = pair_tiles<T>(RT[2 * kd][fc], 2 * kd + 1 < SH::DVT1 ? RT[2 * kd + 1][fc] : zero4());
-          if (2 * kd + 1 < SH::DVT) {
-            store_frag_nm<T>(RLw, RLP, fc * 16, (2 * kd) * 16, (2 * kd + 1) * 16, rp[kd]);
-          } else if (2 * kd < SH::DVT) {
-            store_tile_nm<T>(RLw, RLP, fc * 16, (2 * kd) * 16, RT[2 * kd][fc]);
-          }
-        }
+        r_frags(fc, rp, CAUSAL);
 #pragma unroll
         for (int tk = 0; tk < SH::TT; ++tk) {
-          f32x4 acc = zero4();
-          if (CAUSAL) {
+          dph[fc][tk] = zero4();
 #pragma unroll
-            for (int ks = 0; ks < SH::KT; ++ks)
-              if (32 * ks + 31 >= 16 * tk)
-                mma(acc, lds_tr_frag<T>(PT[w], LDP, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, fc * 16), mp[ks][tk]);
-          }
-#pragma unroll
-          for (int kd = 0; kd < KG; ++kd) mma(acc, rp[kd], vf[tk][kd]);
-          dph[fc][tk] = acc;
+          for (int kd = 0; kd < KG; ++kd) mma(dph[fc][tk], rp[kd], vf[tk][kd]);
         }
       }
     }
-    // dV^T partial[value col][key] = dO^T A/den (intra) + R'[:dv]^T-rows x phi(K)
-    f32x4 dvp[SH::DVT][SH::TT];
+    // M tiles: the last three waves, one each
+    if (CAUSAL && w >= NW - 3) {
+      const int tq = w == NW - 1 ? 0 : 1, tk = w == NW - 3 ? 1 : 0;   // (0,0), (1,0), (1,1)
+      f32x4 m = zero4();
 #pragma unroll
-    for (int tk = 0; tk < SH::TT; ++tk)
+      for (int kd = 0; kd < SH::DV / 32; ++kd) {
+        Frag<T> ao, bv;
+        lds_row8(ao, XDO + (tq * 16 + r) * StV::LD, kd * 32 + 8 * g);
+        lds_row8(bv, XV + (tk * 16 + r) * StV::LD, kd * 32 + 8 * g);
+        mma(m, ao, bv);
+      }
+      m -= *reinterpret_cast<const f32x4*>(DEL + tq * 16 + 4 * g);
+      store_intra(&MP[0][0], tq, tk, m);
+    }
+    __syncthreads();   // phi(Q), phi(K), R' and M complete; the rows of Q and V are read
+
+    // ---- interval 2
+    // an earlier group's dK and dV of this chunk (rows past N read zero)
+    f32x4 old_k[ACC ? NOT : 1], old_v[ACC ? NOT : 1];
+    if (ACC) {
 #pragma unroll
-      for (int dt = 0; dt < SH::DVT; ++dt) {
-        f32x4 acc = zero4();
-        if (CAUSAL) {
-#pragma unroll
-          for (int ks = 0; ks < SH::KT; ++ks)
-            if (32 * ks + 31 >= 16 * tk) mma(acc, lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16), ap[ks][tk]);
+      for (int k = 0; k < NOT; ++k) {
+        const int ot = w + k * NW, off = ((ot / DT * 16 + r) * D + ot % DT * 16 + 4 * g) * 4;
+        if (ot < DT * SH::TT) {
+          old_k[k] = dkb.load_f4(off);
+          old_v[k] = dvb.load_f4(off);
         }
-#pragma unroll
-        for (int ft = 0; ft < SH::FT; ++ft)
-          mma(acc, lds_tr_frag<T>(RLw, RLP, (2 * ft) * 16 + 4 * g, (2 * ft + 1) * 16 + 4 * g, dt * 16),
-              phk[ft][tk]);
-        dvp[dt][tk] = acc;
-      }
-    // dV: reduce the per-wave partials.  With one reduction round per chunk the
-    // partials are written now and reduced after the dP barrier below, which
-    // orders these writes before every wave's reads (the slots are written
-    // again only after the next chunk's staging barrier); with several rounds
-    // each round has barriers of its own.
-    constexpr bool DEFER_DV = QG == SH::TT;
-    auto dv_write = [&](int q0) {
-#pragma unroll
-      for (int qq = 0; qq < QG; ++qq)
-#pragma unroll
-        for (int dt = 0; dt < SH::DVT; ++dt)
-          *reinterpret_cast<f32x4*>(&RED(w)[qq * 16 + r][dt * 16 + 4 * g]) = dvp[dt][q0 + qq];
-    };
-    auto dv_reduce = [&](int q0) {
-#pragma unroll
-      for (int k = 0; k < NIT; ++k) {
-        const int it = threadIdx.x + k * SH::NT;
-        if (it >= QG * 16 * C4) break;
-        const int t = it / C4, c4 = it % C4;
-        f32x4 s = zero4();
-        if (ACC) s = old_v[q0 / QG][k];   // later frequency groups add their share
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) s += *reinterpret_cast<const f32x4*>(&RED(ww)[t][4 * c4]);
-        dvb.store_f4(((q0 * 16 + t) * SH::DV + 4 * c4) * 4, s);
-      }
-    };
-    if (DEFER_DV) {
-      dv_write(0);
-    } else {
-#pragma unroll
-      for (int q0 = 0; q0 < SH::TT; q0 += QG) {
-        if (q0 > 0) __syncthreads();   // the previous round's reads of every slot are done
-        dv_write(q0);
-        __syncthreads();
-        dv_reduce(q0);
       }
     }
-    // R'^T += [dO | -delta]^T-rows x phi(Q)/den  (after every use of R'_{>c})
+    // A tiles: the first three waves, one each
+    if (CAUSAL && w < 3) {
+      const int tq = w == 0 ? 0 : 1, tk = w == 2 ? 1 : 0;
+      f32x4 at = zero4();
+#pragma unroll
+      for (int ft = 0; ft < NFT; ++ft)
+        mma(at, PT[tq][ft][l], PK[tk][ft][l]);
+      store_intra(&AP[0][0], tq, tk, at);
+    }
     if (CAUSAL) {
+      // M share of dphi(K), and R'^T += [dO | -delta]^T-rows x phi(Q)/den
+      Frag<T> gt[SH::DVT1], mp[SH::TT];
 #pragma unroll
-      for (int ks = 0; ks < SH::KT; ++ks) {
-        Frag<T> gt[SH::DVT1];
+      for (int tk = 0; tk < SH::TT; ++tk) mp[tk] = MP[tk][l];
 #pragma unroll
-        for (int dt = 0; dt < SH::DVT; ++dt) gt[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
-        gt[SH::DVT] = delta_rows<T>(GS, ks);
+      for (int dt = 0; dt < SH::DVT; ++dt) gt[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 4 * g, 16 + 4 * g, dt * 16);
+      gt[SH::DVT] = lds_tok_frag<T>(DLT + (r < 2 ? r : 2) * DLD, 0);
 #pragma unroll
-        for (int fc = 0; fc < SH::FC; ++fc) {
-          const Frag<T> pq = lds_tr_frag<T>(PT[w], LDP, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, fc * 16);
+      for (int fc = 0; fc < SH::FC; ++fc) {
+        const Frag<T> pq = tr_of_frags(PT[0][w * SH::FT + fc / 2], PT[SH::TT - 1][w * SH::FT + fc / 2], fc % 2);
 #pragma unroll
-          for (int dt = 0; dt < SH::DVT1; ++dt) mma(RT[dt][fc], gt[dt], pq);
-        }
+        for (int tk = 0; tk < SH::TT; ++tk) mma(dph[fc][tk], pq, mp[tk]);
+#pragma unroll
+        for (int dt = 0; dt < SH::DVT1; ++dt) mma(RT[dt][fc], gt[dt], pq);
       }
     }
-    // chain rule through phi(K)
-    f32x4 dp[SH::PR][SH::TT];
-    float gp[SH::TT];
+    // R' share of this wave's dV^T tiles [value col][key] over all features
+    f32x4 dv[NOT];
+#pragma unroll
+    for (int k = 0; k < NOT; ++k) dv[k] = zero4();
+#pragma unroll
+    for (int ft = 0; ft < NFT; ++ft)
+#pragma unroll
+      for (int k = 0; k < NOT; ++k) {
+        const int ot = w + k * NW;
+        if (DT * SH::TT % NW == 0 || ot < DT * SH::TT)
+          mma(dv[k], lds_tr_frag<T>(RL[ft / SH::FT], RLP, (2 * (ft % SH::FT)) * 16 + 4 * g, (2 * (ft % SH::FT) + 1) * 16 + 4 * g,
+                                    ot % DT * 16),
+              PK[ot / DT][ft][l]);
+      }
+    // chain rule through phi(K): with t = cos P1 da + sin P1 db and
+    // u = cos P1 db - sin P1 da, dP1 = s e cos P2 u, dP2 = -s e sin P2 t and
+    // <phi, dphi> = s e cos P2 t; dP as [token][projection row] in LDS
 #pragma unroll
     for (int tt = 0; tt < SH::TT; ++tt) {
       float gs = 0.f;
+      f32x4 dp[SH::PR];
 #pragma unroll
       for (int ft = 0; ft < SH::FT; ++ft) {
-        f32x4 d2 = zero4();
-        gs += feature_grad<T, SH::FT, NS>(phk[ft][tt], psk[ft][tt], dph[2 * ft][tt], dph[2 * ft + 1][tt], dp[ft][tt], d2);
-        if (NS) dp[SH::FT + ft][tt] = d2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float da = dph[2 * ft][tt][i], db = dph[2 * ft + 1][tt][i];
+          const float t = kc[ft][tt][i] * da + ks1[ft][tt][i] * db;
+          const float u = kc[ft][tt][i] * db - ks1[ft][tt][i] * da;
+          dp[ft][i] = kw[ft][tt][i] * u;
+          if constexpr (NS) dp[SH::FT + ft][i] = -kz[ft][tt][i] * t;
+          gs += kw[ft][tt][i] * t;
+        }
       }
-      gp[tt] = gs;   // this lane group's share; the four shares are summed in the dK reduction
+#pragma unroll
+      for (int ks = 0; ks < WTS::KP; ++ks)
+        DP[tt][w * WTS::KP + ks][l] = pair_tiles<T>(dp[2 * ks], 2 * ks + 1 < SH::PR ? dp[2 * ks + 1] : zero4());
+      gs = group_sum_swap(gs);
+      if (g == 0) GP[tt * 16 + r][w] = gs;
     }
-    // dK = dP W' over all projection rows + (2/c) g k, g = <phi(K), dphi(K)>;
-    // dtau -= g ||k||^2 / c.  Each wave computes whole output tiles (d tile,
-    // token tile) from every wave's dP block and that wave's dX fragments, so
-    // no cross-wave reduction is needed.  Wave w takes the d tiles
-    // dt = w mod DT (+ NW, ...) and, when there are fewer d tiles than waves,
-    // the token tiles tt = w / DT (+ NW / DT, ...).  The dX fragments of its
-    // first d tile are loaded before the barrier, so their latency overlaps it.
-    if (!HOLD_WF) load_wf(w % DT);
     // the next chunk's rows (the last step stages its own rows again, unused)
-    if (EARLY) stage(step + 1, c - 1 >= c0 ? c - 1 : c);
-    // dP of this wave as [token][projection row] in its LDS block (its own reads
-    // of phi(Q)/den there are done: one wave's LDS accesses complete in order),
-    // and this lane's share of g per token
+    stage(step + 1, c - 1 >= c0 ? c - 1 : c);
+    __syncthreads();   // dP, g shares, A and the next chunk's rows complete
+
+    // ---- interval 3
+    // the lane index again, opaque: its uses from here to the next interval 3
+    // compute their addresses once per chunk instead of holding each one in a
+    // register for the whole sweep (they spilled)
+    asm volatile("" : "+v"(l));
+    r = l % 16;
+    g = l / 16;
+    fs.load_frags(wproj);   // the next chunk's (the last step's are unused)
+    // dV: the A share; dK = dP W' over all projection rows + (2/c) g k, with
+    // g = <phi(K), dphi(K)>; dtau -= g ||k||^2 / c
+    f32x4 dk[NOT];
 #pragma unroll
-    for (int pr = 0; pr < SH::PR; ++pr)
+    for (int k = 0; k < NOT; ++k) {
+      const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
+      dk[k] = zero4();
+      if (DT * SH::TT % NW != 0 && ot >= DT * SH::TT) continue;
+      if (CAUSAL) mma(dv[k], lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 4 * g, 16 + 4 * g, dt * 16), AP[tt][l]);
 #pragma unroll
-      for (int tt = 0; tt < SH::TT; ++tt) store_tile_nm<T>(PT[w], LDP, tt * 16, pr * 16, dp[pr][tt]);
+      for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
-    for (int tt = 0; tt < SH::TT; ++tt) GP[tt * 16 + r][w][g] = gp[tt];
-    __syncthreads();   // every wave's dP block and g shares complete
-    if (DEFER_DV) dv_reduce(0);
-#pragma unroll
-    for (int kd = 0; kd < NDK; ++kd) {
-      const int dt = w % DT + kd * NW;
-      if (dt >= DT) break;
-      f32x4 acc[NTK];
-#pragma unroll
-      for (int kt = 0; kt < NTK; ++kt) {
-        const int tt = (DT < NW ? w / DT : 0) + kt * TT0STEP;
-        acc[kt] = zero4();
-        if (tt >= SH::TT) continue;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-#pragma unroll
-          for (int ks = 0; ks < WTS::KP; ++ks) {
-            Frag<T> b = load_frag_nm<T>(PT[ww], LDP, tt * 16, (2 * ks) * 16, (2 * ks + 1) * 16);
-            if (2 * ks + 1 >= SH::PR) {   // no second row tile: keep unwritten LDS out of the product
-#pragma unroll
-              for (int j = 4; j < 8; ++j) b.set(j, 0.f);
-            }
-#pragma unroll
-            for (int sp = 0; sp < WTS::NSPLIT; ++sp) mma(acc[kt], wf[ww][ks][sp], b);
-          }
+        for (int ks = 0; ks < WTS::KP; ++ks) {
+          const Frag<T> b = DP[tt][ww * WTS::KP + ks][l];
+          if constexpr (DX_LDS) mma(dk[k], DXL[ww][(dt * WTS::KP + ks) * WAVE + l], b);
+          else mma(dk[k], wf[k % NDK][ww][ks], b);
         }
-      }
-      // the next d tile's dX fragments, issued ahead of this tile's stores so
-      // that waiting for them does not wait for the stores
-      if (kd + 1 < NDK && dt + NW < DT) load_wf(dt + NW);
-#pragma unroll
-      for (int kt = 0; kt < NTK; ++kt) {
-        const int tt = (DT < NW ? w / DT : 0) + kt * TT0STEP;
-        if (tt >= SH::TT) continue;
-        const int tl = tt * 16 + r;
-        float gg = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-          const float4 v = *reinterpret_cast<const float4*>(&GP[tl][ww][0]);
-          gg += (v.x + v.y) + (v.z + v.w);
-        }
-        const float k2 = 2.0f * inv_c * gg;
-        const IO* kr = XK + tl * StX::LD + dt * 16 + 4 * g;
-        f32x4 s;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] = acc[kt][i] + k2 * io_to_float(kr[i]);
-        if (ACC) s += old_k[kd][kt];   // later frequency groups add their share
-        dkb.store_f4((tl * D + dt * 16 + 4 * g) * 4, s);
-        const float dt_term = gg * SSK[tl] * inv_c;
-        dtau_acc -= (dt == 0 && g == 0 && tok0 + tl < a.N) ? dt_term : 0.f;
-      }
     }
-    if (EARLY) fs.load_frags(wproj);   // the next chunk's (the last step's are unused)
+#pragma unroll
+    for (int k = 0; k < NOT; ++k) {
+      const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
+      if (DT * SH::TT % NW != 0 && ot >= DT * SH::TT) continue;
+      const int tl = tt * 16 + r, off = (tl * D + dt * 16 + 4 * g) * 4;
+      if (ACC) dv[k] += old_v[k];   // later frequency groups add their share
+      dvb.store_f4(off, dv[k]);
+      float gg = 0.f;
+#pragma unroll
+      for (int ww = 0; ww < NW; ww += 4) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&GP[tl][ww]);
+        gg += (v[0] + v[1]) + (v[2] + v[3]);
+      }
+      const float k2 = 2.0f * inv_c * gg;
+      const IO* kr = XK + tl * StX::LD + dt * 16 + 4 * g;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dk[k][i] += k2 * io_to_float(kr[i]);
+      if (ACC) dk[k] += old_k[k];
+      dkb.store_f4(off, dk[k]);
+      const float dt_term = gg * SSK2[par][tl] * inv_c;
+      dtau_acc -= (dt == 0 && g == 0 && tok0 + tl < a.N) ? dt_term : 0.f;
+    }
     {
-      // one 32-token k-step per chunk, added to the LDS partial one
-      // projection-row tile at a time
-      static_assert(SH::KT == 1, "one token k-step per chunk");
+      // one 32-token k-step per chunk
       Frag<T> xk[DT];
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) xk[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XK), StX::LD, 4 * g, 16 + 4 * g, dt * 16);
 #pragma unroll
       for (int pr = 0; pr < SH::PR; ++pr) {
-        const Frag<T> dpt = lds_tr_frag<T>(PT[w], LDP, 4 * g, 16 + 4 * g, pr * 16);
-        dw_mma_row<D, T>(DWL[w], pr, dpt, xk);
+        const Frag<T> dpt = tr_of_frags(DP[0][w * WTS::KP + pr / 2], DP[SH::TT - 1][w * WTS::KP + pr / 2], pr % 2);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) mma(DW[pr][dt], dpt, xk[dt]);
       }
     }
   }
   const size_t nmat = NS ? 2 : 1;
   float* out = a.dwpart + (((size_t)1 * a.BH + bh) * a.segments + seg) * nmat * SH::M * D;
-  dump_dw<SH, D, FW, NS>(out, DWL[w], w * FW);
+  dump_dw<SH, D, FW, NS>(out, DW, w * FW);
   // dtau partial of this workgroup: fixed-order tree sum
   TRED[threadIdx.x] = dtau_acc;
   __syncthreads();
@@ -814,46 +808,37 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(BwdArgs a, int md4, int d) {
 // ---------------------------------------------------------------------------
 // Host-side dispatch.
 // ---------------------------------------------------------------------------
-// Frequencies per wave (FW) and waves per workgroup (NW) of the pre-pass and
-// the dQ sweep (A) and of the dK/dV sweep (B).  The states, the partial sums
-// and the per-token scalars have split-independent layouts; each split has its
-// own prepared fragments.
-template <class T, int D, bool NS, int FWA, int NWA, int FWB, int NWB>
+// FW frequencies per wave, NW waves per workgroup, in every kernel.
+template <class T, int D, bool NS, int FW, int NW>
 static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
-  typedef Shape<T, D, FWA, NWA, NS, BWD_CHUNK> SA;
-  typedef Shape<T, D, FWB, NWB, NS, BWD_CHUNK> SB;
-  static_assert(SA::M == SB::M && SA::STATE == SB::STATE, "splits of one shape");
+  typedef Shape<T, D, FW, NW, NS, BWD_CHUNK> SH;
   const dim3 grid(a.segments * a.BH);
-  if (a.wfrag_kv != a.wfrag)   // both splits' fragments in one launch
-    k_prep_freqs2<T, D, FWA, NWA, FWB, NWB, NS><<<dim3(a.H, NWA > NWB ? NWA : NWB, 4), WAVE, 0, st>>>(
-        a.W1, a.W2, a.wfrag, a.wfrag_kv, a.w_stride);
-  else
-    k_prep_freqs<T, D, FWA, NWA, NS><<<dim3(a.H, NWA, 2), WAVE, 0, st>>>(a.W1, a.W2, a.wfrag, a.w_stride);
+  k_prep_freqs<T, D, FW, NW, NS><<<dim3(a.H, NW, 2), WAVE, 0, st>>>(a.W1, a.W2, a.wfrag, a.w_stride);
   // With the forward's key-side states passed in, the dQ sweep does the
   // pre-pass's query-side work itself and no pre-pass runs; the R' local
   // states it leaves feed the scan, or the dK/dV sweep's own suffix sum.
   const bool wr = a.fstate != nullptr;
   // a padded frequency group (only the 64-frequency shape has one, and it runs
   // first, so it never adds) takes the masking kernel variants
-  const bool masked = a.fvalid < SA::M;
-  constexpr bool CAN_MASK = SA::M == 64;
+  const bool masked = a.fvalid < SH::M;
+  constexpr bool CAN_MASK = SH::M == 64;
   if (masked && (!CAN_MASK || a.acc)) return hipErrorInvalidValue;
   auto scan_r = [&]() -> hipError_t {
     if (causal && a.rfold) return hipSuccess;
-    return launch_state_scan(a.fstate ? nullptr : a.sstate, a.rstate, a.BH, a.segments, 1, SA::STATE, causal, st,
+    return launch_state_scan(a.fstate ? nullptr : a.sstate, a.rstate, a.BH, a.segments, 1, SH::STATE, causal, st,
                              a.segments);
   };
   if (!wr) {
     timing_mark(KC_BWD_PREPASS, st, true);
     if constexpr (CAN_MASK) {
       if (masked) {
-        if (a.fstate) k_bwd_prepass<T, D, FWA, NWA, NS, false, true><<<grid, SA::NT, 0, st>>>(a);
-        else k_bwd_prepass<T, D, FWA, NWA, NS, true, true><<<grid, SA::NT, 0, st>>>(a);
+        if (a.fstate) k_bwd_prepass<T, D, FW, NW, NS, false, true><<<grid, SH::NT, 0, st>>>(a);
+        else k_bwd_prepass<T, D, FW, NW, NS, true, true><<<grid, SH::NT, 0, st>>>(a);
       }
     }
     if (!masked) {
-      if (a.fstate) k_bwd_prepass<T, D, FWA, NWA, NS, false><<<grid, SA::NT, 0, st>>>(a);
-      else k_bwd_prepass<T, D, FWA, NWA, NS, true><<<grid, SA::NT, 0, st>>>(a);
+      if (a.fstate) k_bwd_prepass<T, D, FW, NW, NS, false><<<grid, SH::NT, 0, st>>>(a);
+      else k_bwd_prepass<T, D, FW, NW, NS, true><<<grid, SH::NT, 0, st>>>(a);
     }
     timing_mark(KC_BWD_PREPASS, st, false);
     const hipError_t e = scan_r();
@@ -862,7 +847,7 @@ static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
   timing_mark(KC_BWD_DQ, st, true);
   // a later frequency group adds into the earlier groups' outputs
   {
-    const hipError_t e = launch_bwd_dq<T, D, FWA, NWA, NS>(a, causal, a.acc != 0, wr, masked, st);
+    const hipError_t e = launch_bwd_dq<T, D, FW, NW, NS>(a, causal, a.acc != 0, wr, masked, st);
     if (e != hipSuccess) return e;
   }
   timing_mark(KC_BWD_DQ, st, false);
@@ -873,25 +858,25 @@ static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
   timing_mark(KC_BWD_DKV, st, true);
   if (a.acc) {
     if (causal)
-      k_bwd_dkv<T, D, FWB, NWB, NS, true, true><<<grid, SB::NT, 0, st>>>(a);
+      k_bwd_dkv<T, D, FW, NW, NS, true, true><<<grid, SH::NT, 0, st>>>(a);
     else
-      k_bwd_dkv<T, D, FWB, NWB, NS, false, true><<<grid, SB::NT, 0, st>>>(a);
+      k_bwd_dkv<T, D, FW, NW, NS, false, true><<<grid, SH::NT, 0, st>>>(a);
   } else if (masked) {
     if constexpr (CAN_MASK) {
       if (causal)
-        k_bwd_dkv<T, D, FWB, NWB, NS, true, false, true><<<grid, SB::NT, 0, st>>>(a);
+        k_bwd_dkv<T, D, FW, NW, NS, true, false, true><<<grid, SH::NT, 0, st>>>(a);
       else
-        k_bwd_dkv<T, D, FWB, NWB, NS, false, false, true><<<grid, SB::NT, 0, st>>>(a);
+        k_bwd_dkv<T, D, FW, NW, NS, false, false, true><<<grid, SH::NT, 0, st>>>(a);
     }
   } else {
     if (causal)
-      k_bwd_dkv<T, D, FWB, NWB, NS, true, false><<<grid, SB::NT, 0, st>>>(a);
+      k_bwd_dkv<T, D, FW, NW, NS, true, false><<<grid, SH::NT, 0, st>>>(a);
     else
-      k_bwd_dkv<T, D, FWB, NWB, NS, false, false><<<grid, SB::NT, 0, st>>>(a);
+      k_bwd_dkv<T, D, FW, NW, NS, false, false><<<grid, SH::NT, 0, st>>>(a);
   }
   timing_mark(KC_BWD_DKV, st, false);
-  static_assert((SA::M * D) % 4 == 0, "the reduce moves 4 floats per thread");
-  constexpr int MD4 = SA::M * D / 4;
+  static_assert((SH::M * D) % 4 == 0, "the reduce moves 4 floats per thread");
+  constexpr int MD4 = SH::M * D / 4;
   dim3 rgrid((MD4 + 63) / 64, a.H);
   timing_mark(KC_BWD_REDUCE, st, true);
   k_bwd_reduce<NS ? 2 : 1><<<rgrid, 256, 0, st>>>(a, MD4, D);
@@ -899,27 +884,23 @@ static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <class T, int D, int FWA, int NWA, int FWB, int NWB>
+template <class T, int D, int FW, int NW>
 static hipError_t run_bwd_v(const BwdArgs& a, bool ns, bool causal, hipStream_t st) {
-  return ns ? run_bwd_t<T, D, true, FWA, NWA, FWB, NWB>(a, causal, st)
-            : run_bwd_t<T, D, false, FWA, NWA, FWB, NWB>(a, causal, st);
+  return ns ? run_bwd_t<T, D, true, FW, NW>(a, causal, st)
+            : run_bwd_t<T, D, false, FW, NW>(a, causal, st);
 }
 
 hipError_t launch_bwd(const BwdArgs& a, const KernelShape& ks, hipStream_t st) {
   if (ks.bf16) {
-    if (ks.d == 32 && ks.m == 64) return run_bwd_v<__bf16, 32, 16, 4, 16, 4>(a, ks.nonstationary, ks.causal, st);
-    if (ks.d == 64 && ks.m == 64) return run_bwd_v<__bf16, 64, 16, 4, 16, 4>(a, ks.nonstationary, ks.causal, st);
-    if (ks.d == 64 && ks.m == 128) return run_bwd_v<__bf16, 64, 16, 8, 32, 4>(a, ks.nonstationary, ks.causal, st);
-    if (ks.d == 128 && ks.m == 64) return run_bwd_v<__bf16, 128, 16, 4, 16, 4>(a, ks.nonstationary, ks.causal, st);
+    if (ks.d == 32 && ks.m == 64) return run_bwd_v<__bf16, 32, 16, 4>(a, ks.nonstationary, ks.causal, st);
+    if (ks.d == 64 && ks.m == 64) return run_bwd_v<__bf16, 64, 16, 4>(a, ks.nonstationary, ks.causal, st);
+    if (ks.d == 64 && ks.m == 128) return run_bwd_v<__bf16, 64, 16, 8>(a, ks.nonstationary, ks.causal, st);
+    if (ks.d == 128 && ks.m == 64) return run_bwd_v<__bf16, 128, 16, 4>(a, ks.nonstationary, ks.causal, st);
   } else {
-    if (ks.d == 32 && ks.m == 64) return run_bwd_v<float, 32, 16, 4, 16, 4>(a, ks.nonstationary, ks.causal, st);
+    if (ks.d == 32 && ks.m == 64) return run_bwd_v<float, 32, 16, 4>(a, ks.nonstationary, ks.causal, st);
   }
   return hipErrorNotSupported;
 }
-
-// Whether the dK/dV sweep splits the frequencies differently from the other
-// backward kernels (then it needs a second block of prepared fragments).
-bool bwd_split_differs(const KernelShape& ks) { return ks.bf16 && ks.d == 64 && ks.m == 128; }
 
 size_t bwd_state_floats(const KernelShape& ks) { return fwd_state_floats(ks); }
 // both sides (query rows and key rows) of the frequency-gradient partials

@@ -78,8 +78,8 @@ __device__ __forceinline__ Frag<T> delta_rows(const float (*GS)[2], int ks) {
 
 // Per-token (1/den, delta) of token tok0 + thread of a chunk of ch tokens: zero
 // for tokens past n and for threads past the chunk.
-__device__ __forceinline__ float2 load_gs(const float* gst, int tok0, int n, int ch) {
-  return RowBuf(gst, 2, tok0, n, ch).load_f2((int)threadIdx.x * 8);
+__device__ __forceinline__ float2 load_gs(const float* gst, int tok0, int n, int ch, int thread) {
+  return RowBuf(gst, 2, tok0, n, ch).load_f2(thread * 8);
 }
 
 // Register-dump layout of the [dv' x features] states: tile (dt, global feature
@@ -151,20 +151,18 @@ __device__ __forceinline__ void dw_mma_row(float* dwl, int pr, const Frag<T>& dp
 // Write a wave's frequency-gradient partial tiles DW[pr][dt] (rows = projection
 // rows, cols = d) into the canonical layout [matrix][m][d].
 template <class SH, int D, int FW, bool NS>
-__device__ __forceinline__ void dump_dw(float* out, const float* dwl, int f0) {
+__device__ __forceinline__ void dump_dw(float* out, const f32x4 (&dw)[SH::PR][D / 16], int f0) {
   const int l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
 #pragma unroll
   for (int pr = 0; pr < SH::PR; ++pr)
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(dwl + ((pr * (D / 16) + dt) * WAVE + l) * 4);
+    for (int dt = 0; dt < D / 16; ++dt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int mat = pr >= SH::FT ? 1 : 0;
         const int f = f0 + (pr % SH::FT) * 16 + 4 * g + i;
-        out[((size_t)mat * SH::M + f) * D + dt * 16 + r] = v[i];
+        out[((size_t)mat * SH::M + f) * D + dt * 16 + r] = dw[pr][dt][i];
       }
-    }
 }
 
 // The query side's partial is handed to the dK/dV sweep in tile-major order

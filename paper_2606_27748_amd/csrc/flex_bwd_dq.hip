@@ -82,7 +82,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
       so.fetch(Ob, c0 * SH::CH, a.N);
       den_rows(c0 * SH::CH);
     } else {
-      gs_next = load_gs(gst, c0 * SH::CH, a.N, SH::CH);
+      gs_next = load_gs(gst, c0 * SH::CH, a.N, SH::CH, (int)threadIdx.x);
     }
   }
   const Frag<T>* wproj = FragBlock<T, D, FW, NS>::proj(a.wfrag, h, NW, w);
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
         so.fetch(Ob, t1, a.N);
         den_rows(t1);
       } else {
-        gs_next = load_gs(gst, t1, a.N, SH::CH);
+        gs_next = load_gs(gst, t1, a.N, SH::CH, (int)threadIdx.x);
       }
     }
     __syncthreads();

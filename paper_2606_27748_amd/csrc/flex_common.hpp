@@ -174,6 +174,18 @@ __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
+// The same sum in registers: the gfx950 row swaps give each lane its own and
+// the other row's (half's) value.
+__device__ __forceinline__ float group_sum_swap(float x) {
+  const unsigned v = __float_as_uint(x);
+  const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // rows 0|1, 2|3
+  const unsigned p0 = p[0], p1 = p[1];
+  const unsigned u = __float_as_uint(__uint_as_float(p0) + __uint_as_float(p1));
+  const auto q = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // halves
+  const unsigned q0 = q[0], q1 = q[1];
+  return __uint_as_float(q0) + __uint_as_float(q1);
+}
+
 // ---------------------------------------------------------------------------
 // Per-wave frequency slice.  A wave owns FW consecutive frequencies starting
 // at f0; its projection rows are those FW rows of W (stationary) or of W'1
@@ -439,21 +451,6 @@ template <class T, int D, int FW, int NW, bool NS>
 __global__ __launch_bounds__(WAVE) void k_prep_freqs(const float* W1, const float* W2, void* out, int wstride) {
   prep_freqs_part<T, D, FW, NW, NS>(W1, W2, out, wstride, blockIdx.x, blockIdx.y, blockIdx.z);
 }
-// Both parts for two wave splits A and B in one launch: grid (H, max(NWA,
-// NWB), 4); blockIdx.z = 2 * split + part.
-template <class T, int D, int FWA, int NWA, int FWB, int NWB, bool NS>
-__global__ __launch_bounds__(WAVE) void k_prep_freqs2(const float* W1, const float* W2, void* outA, void* outB,
-                                                      int wstride) {
-  const int w = blockIdx.y, part = blockIdx.z % 2;
-  if (blockIdx.z < 2) {
-    if (w < NWA) prep_freqs_part<T, D, FWA, NWA, NS>(W1, W2, outA, wstride, blockIdx.x, w, part);
-  } else {
-    if (w < NWB) prep_freqs_part<T, D, FWB, NWB, NS>(W1, W2, outB, wstride, blockIdx.x, w, part);
-  }
-}
-
-
-
 
 // Trigonometric values of a projection in revolutions: cos(2 pi p), sin(2 pi p).
 // v_sin_f32 / v_cos_f32 take revolutions and reduce the argument themselves:

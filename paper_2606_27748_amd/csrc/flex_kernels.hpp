@@ -90,7 +90,6 @@ struct BwdArgs {
                       // it), the key side's holding both sides' sums in [matrix][m][d]
   float* dtaupart;    // [BH][segments] partial dtau
   void* wfrag;        // per-head frequency fragments (prepared by k_prep_freqs)
-  void* wfrag_kv;     // fragments of the dK/dV sweep (== wfrag when its split is the same)
   const float* fstate; // forward segment states ([BH][segments*fsub][state]) or NULL
   int fsub;           // forward pre-pass workgroups per segment
   int ffold;          // 1: fstate holds the local states (the forward ran no scan) and
@@ -175,7 +174,6 @@ size_t bwd_state_floats(const KernelShape& ks);
 size_t bwd_dw_floats(const KernelShape& ks);
 // bytes of the per-head frequency fragments for H heads
 size_t wfrag_bytes(const KernelShape& ks, int H);
-bool bwd_split_differs(const KernelShape& ks);
 int fwd_state_waves(const KernelShape& ks);
 // Waves per SIMD of the forward state pre-pass (its launch attribute): two,
 // except at d = 128 nonstationary, whose wave holds more than half a SIMD's
@@ -186,6 +184,10 @@ int fwd_state_wgs_per_cu(const KernelShape& ks);
 constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
   return bf16 && (m > 64 || d < 128 || ch < 64 || !causal) ? 2 : 1;
 }
+
+// Waves per SIMD the dK/dV sweep is compiled for: two, except at d = 128 (one
+// wave's states and dW' partial alone take 136 registers) and on the fp32 path.
+constexpr int dkv_waves_per_eu(bool bf16, int d) { return bf16 && d <= 64 ? 2 : 1; }
 
 // state (or NULL): [BH][P*sub][E]; writes the exclusive prefix (causal) into
 // slot p*sub of every segment p, or the total (non-causal) into slot 0.

@@ -71,6 +71,9 @@ struct RowStage {
   static constexpr int LDS_ELEMS = ROWS * LD;
   uint4 r[PER];
 
+  // the stage's thread index (a workgroup of 2 NT threads has two stages)
+  static __device__ __forceinline__ int tid() { return (int)(threadIdx.x % NT); }
+
   // rows: this (b,h) slice's [N, COLS] rows; rows at or beyond n (and the
   // vectors of threads past the chunk) read as zero.  n > tok0.  The chunk's
   // rows are consecutive in memory, so vector v sits 16 v bytes into it: one
@@ -79,7 +82,7 @@ struct RowStage {
   __device__ __forceinline__ void fetch(const IO* __restrict__ rows, int tok0, int n) {
     const RowBuf b(rows, COLS, tok0, n, ROWS);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) r[i] = b.load16(((int)threadIdx.x + i * NT) * 16);
+    for (int i = 0; i < PER; ++i) r[i] = b.load16((tid() + i * NT) * 16);
   }
   __device__ __forceinline__ uint4 vec(int i) const { return r[i]; }
   // keeps the fetched rows' loads without storing them anywhere (loads whose
@@ -88,12 +91,12 @@ struct RowStage {
 #pragma unroll
     for (int i = 0; i < PER; ++i) asm volatile("" ::"v"(r[i].x), "v"(r[i].y), "v"(r[i].z), "v"(r[i].w));
   }
-  // whether vector index v (of thread threadIdx.x) is part of the chunk
+  // whether vector index v (of thread tid()) is part of the chunk
   static __device__ __forceinline__ bool mine(int v) { return NV % NT == 0 || v < NV; }
   __device__ __forceinline__ void store(IO* lds) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int v = threadIdx.x + i * NT;
+      const int v = tid() + i * NT;
       if (mine(v)) {
         const int t = v / VPR, c = v % VPR;
         *reinterpret_cast<uint4*>(lds + t * LD + c * VEC) = vec(i);
@@ -119,7 +122,7 @@ struct RowStage {
     static_assert(NT % VPR == 0 && VPR <= WAVE, "a row's vectors must share a wave");
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int v = threadIdx.x + i * NT;
+      const int v = tid() + i * NT;
       Ssq s = 0;
       if (mine(v)) {
         const int t = v / VPR, c = v % VPR;
@@ -143,7 +146,7 @@ struct RowStage {
   __device__ __forceinline__ void store_t(T* ldsT) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int v = threadIdx.x + i * NT;
+      const int v = tid() + i * NT;
       if (mine(v)) {
         const int t = v / VPR, c = v % VPR;
         const uint4 x = vec(i);
@@ -449,6 +452,31 @@ __device__ __forceinline__ Frag<T> lds_tr_frag(const T* L, int ld, int kb0, int 
     for (int j = 0; j < 4; ++j) {
       f.set(j, L[(kb0 + j) * ld + m0 + i]);
       f.set(4 + j, L[(kb1 + j) * ld + m0 + i]);
+    }
+  }
+  return f;
+}
+
+// The transpose load from operand fragments as they are stored, [lane][8
+// slots]: f0 holds columns (lane % 16) 0..15, f1 16..31, its slots 4 half +
+// (0..3) the rows 4g + (0..3) of one tile.  The result has lane m = row and
+// k slots 0..3 = columns 4g .. 4g+3 (f0), 4..7 = columns 16 + 4g .. (f1).
+template <class T>
+__device__ __forceinline__ Frag<T> tr_of_frags(const Frag<T> (&f0)[WAVE], const Frag<T> (&f1)[WAVE], int half) {
+  const int l = threadIdx.x % WAVE, i = l % 16, g = l / 16;
+  Frag<T> f;
+  if constexpr (IsBf16<T>::value) {
+    // lane i of a group addresses column 4g + i/4, rows 4 (i % 4) .. + 3
+    const int at = (16 * (i % 4) + 4 * g + i / 4) * 8 + 4 * half;
+    const tr_v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(reinterpret_cast<const T*>(&f0[0]) + at));
+    const tr_v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(reinterpret_cast<const T*>(&f1[0]) + at));
+    f.v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+  } else {
+    // lane i is row i: slot i % 4 of the fragments of lanes 16 (i / 4) + column
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f.set(j, f0[16 * (i / 4) + 4 * g + j].v[4 * half + i % 4]);
+      f.set(4 + j, f1[16 * (i / 4) + 4 * g + j].v[4 * half + i % 4]);
     }
   }
   return f;
