@@ -263,7 +263,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
 // old values are loaded ahead of the next chunk's prefetch, so waiting for
 // them never waits for that prefetch.
 template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ACC, bool MASK = false>
-__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(dkv_waves_per_eu(IsBf16<T>::value, D))))
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(bwd_waves_per_eu(IsBf16<T>::value, D))))
 void k_bwd_dkv(BwdArgs a) {
   typedef Shape<T, D, FW, NW, NS, BWD_CHUNK> SH;
   typedef typename Io<T>::type IO;
@@ -288,8 +288,8 @@ void k_bwd_dkv(BwdArgs a) {
   __shared__ __attribute__((aligned(16))) IO XK2[2][StX::LDS_ELEMS];
   __shared__ __attribute__((aligned(16))) IO XV[StV::LDS_ELEMS];
   __shared__ __attribute__((aligned(16))) IO XDO2[CAUSAL ? 2 : 1][CAUSAL ? StV::LDS_ELEMS : 8];
-  __shared__ Frag<T> PT[CAUSAL ? SH::TT : 1][CAUSAL ? NFT : 1][WAVE];   // phi(Q)/den, operand fragments
-  __shared__ Frag<T> DP[SH::TT][NW * WTS::KP][WAVE];   // dP, operand fragments (k = pairs of projection row tiles)
+  __shared__ FragLds<T> PT[CAUSAL ? SH::TT : 1][CAUSAL ? NFT : 1];   // phi(Q)/den, operand fragments
+  __shared__ FragLds<T> DP[SH::TT][NW * WTS::KP];   // dP, operand fragments (k = pairs of projection row tiles)
   __shared__ __attribute__((aligned(16))) T RL[NW][SH::FC * 16 * RLP];   // R' copy
   __shared__ Frag<T> PK[SH::TT][NFT][WAVE];      // phi(K), operand fragments
   __shared__ Frag<T> MP[SH::TT][WAVE], AP[SH::TT][WAVE];   // M and A: [key tile], k = query tokens
@@ -491,7 +491,7 @@ void k_bwd_dkv(BwdArgs a) {
         sc *= INV[tt * 16 + r];
 #pragma unroll
         for (int ft = 0; ft < SH::FT; ++ft)
-          PT[tt][w * SH::FT + ft][l] = features<T, SH::FT, NS>(p, ft, sc, fv);
+          PT[tt][w * SH::FT + ft].put(l, features<T, SH::FT, NS>(p, ft, sc, fv));
       }
     }
     // phi(K), with the factors of the chain rule kept in fp32: cos P1, sin P1,
@@ -590,7 +590,7 @@ void k_bwd_dkv(BwdArgs a) {
       f32x4 at = zero4();
 #pragma unroll
       for (int ft = 0; ft < NFT; ++ft)
-        mma(at, PT[tq][ft][l], PK[tk][ft][l]);
+        mma(at, PT[tq][ft].get(l), PK[tk][ft][l]);
       store_intra(&AP[0][0], tq, tk, at);
     }
     if (CAUSAL) {
@@ -645,7 +645,7 @@ void k_bwd_dkv(BwdArgs a) {
       }
 #pragma unroll
       for (int ks = 0; ks < WTS::KP; ++ks)
-        DP[tt][w * WTS::KP + ks][l] = pair_tiles<T>(dp[2 * ks], 2 * ks + 1 < SH::PR ? dp[2 * ks + 1] : zero4());
+        DP[tt][w * WTS::KP + ks].put(l, pair_tiles<T>(dp[2 * ks], 2 * ks + 1 < SH::PR ? dp[2 * ks + 1] : zero4()));
       gs = group_sum_swap(gs);
       if (g == 0) GP[tt * 16 + r][w] = gs;
     }
@@ -674,7 +674,7 @@ void k_bwd_dkv(BwdArgs a) {
       for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
         for (int ks = 0; ks < WTS::KP; ++ks) {
-          const Frag<T> b = DP[tt][ww * WTS::KP + ks][l];
+          const Frag<T> b = DP[tt][ww * WTS::KP + ks].get(l);
           if constexpr (DX_LDS) mma(dk[k], DXL[ww][(dt * WTS::KP + ks) * WAVE + l], b);
           else mma(dk[k], wf[k % NDK][ww][ks], b);
         }

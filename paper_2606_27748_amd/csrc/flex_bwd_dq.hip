@@ -8,45 +8,69 @@ namespace flex {
 
 // ---------------------------------------------------------------------------
 // dQ: ascending sweep with the key-side prefix state S'.
+//
+// A chunk has three intervals between two barriers, as in the dK/dV sweep:
+//   1  (waves split the frequencies) phi(K) and phi(Q)/den; the S' share of
+//      dphi(Q); three waves form the tiles of M^T, M = dO V^T - delta
+//   2  (frequencies) the M share of dphi(Q), the S' (and R') update, the chain
+//      rule, dP to LDS, the next chunk's rows to LDS
+//   3  (output tiles) dQ = dP W'; (frequencies) dW' += dP^T Q
+// us per pass before (every wave forming all of M^T, a barrier of its own for
+// the rows, K and V staged without need in the non-causal sweep) and after:
+// training step d = 64, m = 128 (B*H = 32, N = 8192) 424 and 411, d = 128,
+// m = 256 2439 and 2427, encoder training (non-causal m = 64) 232 and 227.
 // ---------------------------------------------------------------------------
-// ACC: add dQ to the values an earlier frequency group stored (loaded at the
-// start of each chunk, ahead of the next chunk's prefetch).
+// ACC: add dQ to the values an earlier frequency group stored (loaded ahead of
+// the next chunk's prefetch).
 // WR: this sweep also does the pre-pass's query-side work (used when the
 // forward's key-side states are passed in, so no pre-pass runs): the per-token
 // 1/den and delta = dO . O, from the staging registers, written for the dK/dV
 // sweep, and the segment-local R'^T = sum [dO | -delta]^T-rows x phi(Q)/den.
 template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ACC, bool WR, bool MASK = false>
-__global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(bwd_waves_per_eu(IsBf16<T>::value, D))))
+void k_bwd_dq(BwdArgs a) {
   typedef Shape<T, D, FW, NW, NS, BWD_CHUNK> SH;
   typedef typename Io<T>::type IO;
-  typedef RowStage<IO, D, SH::NT, SH::CH> StX;
-  typedef RowStage<IO, SH::DV, SH::NT, SH::CH> StV;
+  // With at least two threads per 16-byte vector of a chunk's rows, half of the
+  // waves stage Q, K and V and the other half dO and O.
+  constexpr int HALVES = 2 * SH::CH * D * (int)sizeof(IO) / 16 <= SH::NT ? 2 : 1;
+  constexpr int NTH = SH::NT / HALVES;
+  typedef RowStage<IO, D, NTH, SH::CH> StX;
+  static_assert(D == SH::DV && StX::NV % NTH == 0, "one stage type, the same row vectors per thread");
   typedef WTSlice<T, D, FW, NS> WTS;
   constexpr int DT = D / 16;
   constexpr int KG = (SH::DVT1 + 1) / 2;        // k-steps over [dO | -delta]
   constexpr int NOT = (DT * SH::TT + NW - 1) / NW;   // dQ tiles per wave (at most)
-  // staging is double-buffered by chunk parity where LDS allows (d <= 64)
-  constexpr int NBUF = D <= 64 ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) IO XQ2[NBUF][StX::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) IO XK2[NBUF][StX::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) IO XV2[NBUF][StV::LDS_ELEMS];
-  __shared__ __attribute__((aligned(16))) IO XDO2[NBUF][StV::LDS_ELEMS];
-  constexpr int LDP = SH::FC * 16 + 4;          // row stride of the per-wave [token][row] blocks
-  __shared__ __attribute__((aligned(16))) T PT[NW][SH::CH * LDP];   // dP, [token][projection row]
-  __shared__ __attribute__((aligned(16))) float DWL[NW][SH::PR * DT * WAVE * 4];
-  __shared__ float GS2[NBUF][SH::CH][2];
-  __shared__ typename StX::Ssq SSQ2[NBUF][SH::CH];
-  __shared__ __attribute__((aligned(16))) float SCK2[NBUF][SH::CH];   // per-token key scale s e(k)
-  // dX fragments of every wave's projection rows, copied to LDS once per
-  // workgroup: the dQ tiles read them there instead of from the L2 cache
-  // every chunk
-  constexpr int NDX = FragBlock<T, D, FW, NS>::NT_ * WAVE;   // fragments per wave
-  constexpr bool DX_LDS = true;
+  constexpr int NDX = FragBlock<T, D, FW, NS>::NT_ * WAVE;   // dX fragments per wave
+  static_assert(SH::TT == 2 && SH::KT == 1 && SH::FT == 1 && NW >= 4, "32-token chunks, three waves for the intra-chunk tiles");
+  // rows read in interval 1 only (K) need one staging buffer (stored in
+  // interval 2), the others two, by chunk parity
+  __shared__ __attribute__((aligned(16))) IO XQ2[2][StX::LDS_ELEMS];
+  __shared__ __attribute__((aligned(16))) IO XK[CAUSAL ? StX::LDS_ELEMS : 8];
+  __shared__ __attribute__((aligned(16))) IO XV2[CAUSAL ? 2 : 1][CAUSAL ? StX::LDS_ELEMS : 8];
+  __shared__ __attribute__((aligned(16))) IO XDO2[2][StX::LDS_ELEMS];
+  // phi(Q)/den, then dP, operand fragments (dP: k = pairs of projection row tiles)
+  __shared__ FragLds<T> DP[SH::TT][NW];
+  __shared__ Frag<T> MT[CAUSAL ? SH::TT : 1][WAVE];   // M^T: [query tile], k = key tokens
+  // dW' partial: in registers, except at d = 64 causal, where the two states
+  // take them
+  constexpr bool DW_REG = D != 64 || !CAUSAL;
+  __shared__ __attribute__((aligned(16))) float DWL[DW_REG ? 1 : NW][DW_REG ? 4 : SH::PR * DT * WAVE * 4];
+  // dX fragments of every wave's projection rows: held in registers with four
+  // waves (each then has DT / 4 d tiles), in LDS with eight
+  constexpr bool DX_LDS = NW > 4;
+  constexpr int NDK = DT > NW ? DT / NW : 1;     // d tiles of one wave
+  static_assert(DT <= NW ? NW % DT == 0 : DT % NW == 0, "a wave keeps its d tiles");
   __shared__ Frag<T> DXL[DX_LDS ? NW : 1][DX_LDS ? NDX : 1];
+  __shared__ __attribute__((aligned(16))) float SCQ[SH::CH], SCK[SH::CH], INV[SH::CH], DEL[SH::CH];
+  __shared__ __attribute__((aligned(16))) T DHL[SH::CH][2];   // -delta as a (hi, lo) pair
+  constexpr int DLD = SH::CH + 8;
+  __shared__ __attribute__((aligned(16))) T DLT2[2][3 * DLD];   // the same as operand rows, and a row of zeros
 
   const WgCoord wc = wg_coord(a.segments, a.H, a.BH);
   const int seg = wc.seg, bh = wc.bh, h = bh % a.H;
-  const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  int l = threadIdx.x % WAVE, r = l % 16, g = l / 16;
   const int fv = slice_valid<MASK, FW>(a.fvalid, w);
   const int c0 = seg * a.chunks_per_seg;
   const int c1 = min(c0 + a.chunks_per_seg, a.nchunks);
@@ -54,39 +78,40 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
   const IO* K = static_cast<const IO*>(a.K) + (size_t)bh * a.N * D;
   const IO* V = static_cast<const IO*>(a.V) + (size_t)bh * a.N * SH::DV;
   const IO* dO = static_cast<const IO*>(a.dO) + (size_t)bh * a.N * SH::DV;
-  float* gst = a.gstats + (size_t)bh * a.N * 2;
-  float* dQ = a.dQ + (size_t)bh * a.N * D;
-  // WR: thread v stages vectors v + i NT (i < PER) of Q, dO and O alike, so
-  // the row sums dO . O come out of its staging registers
-  static_assert(!WR || (StX::VPR == StV::VPR && StX::NV == StV::NV && (StV::NV <= SH::NT || StV::NV % SH::NT == 0)),
-                "the same row vectors per thread for Q, dO and O");
-  constexpr int WPER = WR ? StV::PER : 1;
   const IO* Ob = static_cast<const IO*>(a.O) + (size_t)bh * a.N * SH::DV;
   const float* den = a.den + (size_t)bh * a.N;
+  float* gst = a.gstats + (size_t)bh * a.N * 2;
+  float* dQ = a.dQ + (size_t)bh * a.N * D;
+
+  // stages: Q, K, V of the first half in st[0..2]; dO and O here (K and V only
+  // for the intra-chunk terms of the causal sweep)
+  const int half = HALVES == 2 ? w / (NW / 2) : 0;
+  constexpr int SDO = HALVES == 2 ? 0 : 3, SO = SDO + 1;
+  StX st[HALVES == 2 ? 3 : 5];
+  constexpr int WPER = WR ? StX::PER : 1;
   float dn_next[WPER];
+  float2 gs_next = make_float2(0.f, 0.f);
 #pragma unroll
   for (int i = 0; i < WPER; ++i) dn_next[i] = 0.f;
-  auto den_rows = [&](int t0) {   // rows past N (and threads past the rows) read zero, unused
-    const RowBuf b(den, 1, t0, a.N, SH::CH);
-#pragma unroll
-    for (int i = 0; i < WPER; ++i) dn_next[i] = b.load_f1((int)(threadIdx.x + i * SH::NT) / StV::VPR * 4);
-  };
-
-  StX sq, sk;
-  StV sv, sdo, so;
-  float2 gs_next = make_float2(0.f, 0.f);
-  if (c0 < c1) {
-    sq.fetch(Q, c0 * SH::CH, a.N); sk.fetch(K, c0 * SH::CH, a.N);
-    sv.fetch(V, c0 * SH::CH, a.N); sdo.fetch(dO, c0 * SH::CH, a.N);
-    if (WR) {
-      so.fetch(Ob, c0 * SH::CH, a.N);
-      den_rows(c0 * SH::CH);
-    } else {
-      gs_next = load_gs(gst, c0 * SH::CH, a.N, SH::CH, (int)threadIdx.x);
+  auto fetch = [&](int t0) {
+    st[0].fetch(HALVES == 2 && half ? dO : Q, t0, a.N);
+    // (non-causal, two halves: the first half's load is unused, its own rows again)
+    if (CAUSAL || (WR && HALVES == 2)) st[1].fetch(HALVES == 2 && half ? Ob : CAUSAL ? K : Q, t0, a.N);
+    if (CAUSAL) st[2].fetch(V, t0, a.N);
+    if (HALVES == 1) {
+      st[SDO].fetch(dO, t0, a.N);
+      if (WR) st[SO].fetch(Ob, t0, a.N);
     }
-  }
+    if (WR) {   // den of this thread's rows (rows past N read zero, unused)
+      const RowBuf b(den, 1, t0, a.N, SH::CH);
+#pragma unroll
+      for (int i = 0; i < WPER; ++i) dn_next[i] = b.load_f1((StX::tid() + i * NTH) / StX::VPR * 4);
+    } else {
+      gs_next = load_gs(gst, t0, a.N, SH::CH, StX::tid());
+    }
+  };
+  if (c0 < c1) fetch(c0 * SH::CH);
   const Frag<T>* wproj = FragBlock<T, D, FW, NS>::proj(a.wfrag, h, NW, w);
-  const Frag<T>* wdx = FragBlock<T, D, FW, NS>::dx(a.wfrag, h, NW, w);
   const auto inv_c = inv_c_of<T>(a.tau[h]);
 
   f32x4 ST[SH::DVT1][SH::FC];
@@ -119,12 +144,37 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
       for (int fc = 0; fc < SH::FC; ++fc)
         ST[dt][fc] = *reinterpret_cast<const f32x4*>(in + state_off<SH>(w, dt, fc, l));
   }
-  for (int i = l; i < SH::PR * DT * WAVE; i += WAVE)
-    *reinterpret_cast<f32x4*>(&DWL[w][i * 4]) = zero4();
-  if constexpr (DX_LDS) {   // ordered before the first dQ tile by the first staging barrier
+  f32x4 DW[DW_REG ? SH::PR : 1][DW_REG ? DT : 1];
+  if constexpr (DW_REG) {
+#pragma unroll
+    for (int pr = 0; pr < SH::PR; ++pr)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) DW[pr][dt] = zero4();
+  } else {
+    for (int i = l; i < SH::PR * DT * WAVE; i += WAVE) *reinterpret_cast<f32x4*>(&DWL[w][i * 4]) = zero4();
+  }
+  // dX fragments of this wave's d tiles w % DT (+ NW, ...)
+  Frag<T> wf[DX_LDS ? 1 : NDK][DX_LDS ? 1 : NW][WTS::KP];
+  if constexpr (DX_LDS) {
     for (int i = threadIdx.x; i < NW * NDX; i += SH::NT)
       DXL[i / NDX][i % NDX] = FragBlock<T, D, FW, NS>::dx(a.wfrag, h, NW, i / NDX)[i % NDX];
+  } else {
+#pragma unroll
+    for (int kd = 0; kd < NDK; ++kd)
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww)
+#pragma unroll
+        for (int ks = 0; ks < WTS::KP; ++ks)
+          wf[kd][ww][ks] = FragBlock<T, D, FW, NS>::dx(a.wfrag, h, NW, ww)[((w % DT + kd * NW) * WTS::KP + ks) * WAVE + l];
   }
+  // the zero tile of M^T, and the zero row of -delta
+  if (CAUSAL && w == 0) {
+    Frag<T> z;
+    z.zero();
+    MT[0][l] = z;
+  }
+  if (WR) for (int i = threadIdx.x; i < 2 * 3 * DLD; i += SH::NT) DLT2[i / (3 * DLD)][i % (3 * DLD)] = T(0.0f);
+  __syncthreads();
   const Frag<T> ones = ones_col01<T>();
   f32x4 RT[WR ? SH::DVT1 : 1][WR ? SH::FC : 1];
 #pragma unroll
@@ -132,263 +182,268 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
 #pragma unroll
     for (int fc = 0; fc < (WR ? SH::FC : 1); ++fc) RT[dt][fc] = zero4();
 
-  // projection fragments: held for the whole sweep at d <= 64 (without the
-  // query-side states, which take those registers), else reloaded per chunk
-  // ahead of the staging barriers
-  constexpr bool KEEP_FS = D <= 64 && !WR;
+  // Store the prefetched rows of chunk cn into the buffers of sweep step i
+  // and prefetch the next chunk (itself again when it is the last: the
+  // prefetch is issued on every step, from an in-range chunk).
+  auto put_delta = [&](int par, int t, float inv, float dl) {
+    INV[t] = inv;
+    DEL[t] = dl;
+    float hi, lo;
+    neg_split<T>(dl, hi, lo);
+    DHL[t][0] = (T)hi;
+    DHL[t][1] = (T)lo;
+    if (WR) {
+      DLT2[par][t] = (T)hi;
+      DLT2[par][DLD + t] = (T)lo;
+    }
+  };
+  auto stage = [&](int i, int cn) {
+    const int par = i & 1, tn = cn * SH::CH;
+    auto scale = [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tn + t < a.N); };
+    if (HALVES == 1 || half == 0) {
+      st[0].store(XQ2[par], SCQ, scale);
+      if (CAUSAL) {
+        st[1].store(XK, SCK, scale);
+        st[2].store(XV2[par]);
+      }
+    }
+    if (HALVES == 1 || half == 1) {
+      st[SDO].store(XDO2[par]);
+      if constexpr (WR) {
+        // 1/den and delta of this thread's rows (rows past N: zero vectors, delta 0,
+        // and their stores to memory are dropped)
+        const RowBuf gb(gst, 2, tn, a.N, SH::CH);
+#pragma unroll
+        for (int k = 0; k < WPER; ++k) {
+          const int v = StX::tid() + k * NTH, t = v / StX::VPR;
+          float dsum = 0.f;
+          const uint4 x = st[SDO].vec(k), y = st[SO].vec(k);
+          const IO* ex = reinterpret_cast<const IO*>(&x);
+          const IO* ey = reinterpret_cast<const IO*>(&y);
+#pragma unroll
+          for (int j = 0; j < StX::VEC; ++j) dsum += io_to_float(ex[j]) * io_to_float(ey[j]);
+          dsum = lane_sum<StX::VPR>(dsum);
+          const float rcp = 1.0f / dn_next[k];
+          const float inv = tn + t < a.N ? rcp : 0.f;
+          if (v % StX::VPR == 0) {
+            put_delta(par, t, inv, dsum);
+            gb.store_f2(t * 8, make_float2(inv, dsum));
+          }
+        }
+      } else {
+        if (StX::tid() < SH::CH) put_delta(par, StX::tid(), gs_next.x, gs_next.y);
+      }
+    }
+    fetch((cn + 1 < c1 ? cn + 1 : cn) * SH::CH);
+  };
+  // projection fragments, reloaded per chunk (held for the whole sweep they
+  // would not fit the registers)
   FreqSlice<T, D, FW, NS> fs;
-  if (KEEP_FS) fs.load_frags(wproj);
+  if (c0 < c1) {
+    fs.load_frags(wproj);
+    stage(0, c0);
+  }
+  __syncthreads();
   for (int c = c0; c < c1; ++c) {
-    // This chunk's staging buffers.  Double-buffered, they need no barrier
-    // before they are written: the chunk that last read them (two back) is
-    // separated from this point by the previous chunk's barriers.
-    const int par = NBUF == 2 ? (c - c0) & 1 : 0;
+    const int step = c - c0;
+    const int par = step & 1;
     IO* XQ = XQ2[par];
-    IO* XK = XK2[par];
-    IO* XV = XV2[par];
+    IO* XV = XV2[CAUSAL ? par : 0];
     IO* XDO = XDO2[par];
-    float (*GS)[2] = GS2[par];
-    typename StX::Ssq* SSQ = SSQ2[par];
-    float* SCK = SCK2[par];
+    const T* DLT = DLT2[par];
     const int tok0 = c * SH::CH;
-    if (!KEEP_FS) fs.load_frags(wproj);
     const RowBuf dqb(dQ, D, tok0, a.N, SH::CH);
+
+    // ---- interval 1
+    // phi(K) of this wave's features enters only contractions over the key
+    // tokens: token-row fragments (k = tokens), no transpose
+    Frag<T> pk[SH::FC];
+    if (CAUSAL) feature_frags_rows<T, D, FW, NS, StX::LD>(fs, XK, SCK, 0, pk, fv);
+    // phi(Q)/den, and the factors of the chain rule in fp32: cos P1, sin P1,
+    // s e cos P2 / den and s e sin P2 / den (stationary: s e / den alone; the
+    // 1/den of dphi(Q) is carried by these: the products are the same)
+    f32x4 qc[SH::TT], qs[SH::TT], qw[SH::TT], qz[NS ? SH::TT : 1];
+    Frag<T> phq[SH::TT];
+#pragma unroll
+    for (int tt = 0; tt < SH::TT; ++tt) {
+      ProjT<T> p[SH::PR];
+      float sc;
+      project_tile_lds<T, D, FW, NS, StX::LD>(fs, XQ, SCQ, tt, p, sc);
+      sc *= INV[tt * 16 + r];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float se = !MASK || 4 * g + i < fv ? sc : 0.f;
+        float s1, c1v;
+        sincos_rev(p[0][i], s1, c1v);
+        float wv = se;
+        if constexpr (NS) {
+          float s2, c2;
+          sincos_rev(p[1][i], s2, c2);
+          wv = se * c2;
+          qz[tt][i] = se * s2;
+        }
+        qc[tt][i] = c1v;
+        qs[tt][i] = s1;
+        qw[tt][i] = wv;
+        if (WR) {
+          phq[tt].set(i, c1v * wv);
+          phq[tt].set(4 + i, s1 * wv);
+        }
+      }
+    }
+    // S' share of den * dphi(Q)^T[feature][query] = S'^T-rows x [dO | -delta] + phi(K)^T M^T
+    f32x4 dph[SH::FC][SH::TT];
+    {
+      Frag<T> gf[SH::TT][KG];
+#pragma unroll
+      for (int tq = 0; tq < SH::TT; ++tq)
+#pragma unroll
+        for (int kd = 0; kd < KG; ++kd) {
+          if (32 * kd < SH::DV) {
+            gf[tq][kd] = lds_tok_frag<T>(reinterpret_cast<const T*>(XDO) + (tq * 16 + r) * StX::LD, kd);
+          } else {
+            Frag<T> f;
+            f.zero();
+            const T hi = DHL[tq * 16 + r][0], lo = DHL[tq * 16 + r][1];
+            if (g == 0) { f.v[0] = hi; f.v[1] = lo; }
+            gf[tq][kd] = f;
+          }
+        }
+#pragma unroll
+      for (int fc = 0; fc < SH::FC; ++fc)
+#pragma unroll
+        for (int kd = 0; kd < KG; ++kd) {
+          const Frag<T> sp = pair_tiles<T>(ST[2 * kd][fc], 2 * kd + 1 < SH::DVT1 ? ST[2 * kd + 1][fc] : zero4());
+#pragma unroll
+          for (int tq = 0; tq < SH::TT; ++tq) {
+            if (kd == 0) dph[fc][tq] = zero4();
+            mma(dph[fc][tq], sp, gf[tq][kd]);
+          }
+        }
+    }
+    // M^T tiles, rows = key tokens, cols = query tokens, keys at or before the
+    // query: the last three waves, one each
+    if (CAUSAL && w >= NW - 3) {
+      const int tk = w == NW - 3 ? 1 : 0, tq = w == NW - 1 ? 0 : 1;   // (0,0), (0,1), (1,1)
+      f32x4 m = zero4();
+#pragma unroll
+      for (int kd = 0; kd < SH::DV / 32; ++kd) {
+        Frag<T> av, bo;
+        lds_row8(av, XV + (tk * 16 + r) * StX::LD, kd * 32 + 8 * g);
+        lds_row8(bo, XDO + (tq * 16 + r) * StX::LD, kd * 32 + 8 * g);
+        mma(m, av, bo);
+      }
+      const float dl = DEL[tq * 16 + r];
+      T* o = reinterpret_cast<T*>(&MT[CAUSAL ? tq : 0][l]) + 4 * tk;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float md = m[i] - dl;
+        o[i] = (T)(tk < tq || 4 * g + i <= r ? md : 0.f);
+      }
+    }
+    __syncthreads();   // M^T complete; K's rows are read, and the previous chunk's dP
+
+    // ---- interval 2
     // an earlier group's dQ of this chunk (rows past N read zero)
     f32x4 old_q[ACC ? NOT : 1];
     if (ACC) {
 #pragma unroll
       for (int k = 0; k < NOT; ++k) {
-        const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
-        if (ot < DT * SH::TT) old_q[k] = dqb.load_f4(((tt * 16 + r) * D + dt * 16 + 4 * g) * 4);
+        const int ot = w + k * NW;
+        if (ot < DT * SH::TT) old_q[k] = dqb.load_f4(((ot / DT * 16 + r) * D + ot % DT * 16 + 4 * g) * 4);
       }
-    }
-    if (NBUF == 1) __syncthreads();   // single buffer: the previous chunk's reads are done
-    sq.store(XQ, SSQ);
-    sk.store(XK, SCK, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tok0 + t < a.N); });
-    sv.store(XV); sdo.store(XDO);
-    if constexpr (WR) {
-      // 1/den and delta of this thread's rows (rows past N: zero vectors, delta 0,
-      // and their stores to memory are dropped)
-      const RowBuf gb(gst, 2, tok0, a.N, SH::CH);
-#pragma unroll
-      for (int i = 0; i < WPER; ++i) {
-        const int v = threadIdx.x + i * SH::NT, t = v / StV::VPR;
-        const bool mine = v < StV::NV;
-        const bool ok = mine && tok0 + t < a.N;
-        float dsum = 0.f;
-        const uint4 x = sdo.vec(i), y = so.vec(i);
-        const IO* ex = reinterpret_cast<const IO*>(&x);
-        const IO* ey = reinterpret_cast<const IO*>(&y);
-#pragma unroll
-        for (int j = 0; j < StV::VEC; ++j) dsum += io_to_float(ex[j]) * io_to_float(ey[j]);
-        dsum = lane_sum<StV::VPR>(dsum);
-        const float rcp = 1.0f / dn_next[i];
-        const float inv = ok ? rcp : 0.f;
-        if (mine && v % StV::VPR == 0) {
-          GS[t][0] = inv;
-          GS[t][1] = dsum;
-          gb.store_f2(t * 8, make_float2(inv, dsum));
-        }
-      }
-    } else {
-      if (threadIdx.x < SH::CH) { GS[threadIdx.x][0] = gs_next.x; GS[threadIdx.x][1] = gs_next.y; }
-    }
-    {
-      const int t1 = c + 1 < c1 ? tok0 + SH::CH : tok0;   // the last chunk refetches itself (unused)
-      sq.fetch(Q, t1, a.N); sk.fetch(K, t1, a.N); sv.fetch(V, t1, a.N); sdo.fetch(dO, t1, a.N);
-      if (WR) {
-        so.fetch(Ob, t1, a.N);
-        den_rows(t1);
-      } else {
-        gs_next = load_gs(gst, t1, a.N, SH::CH, (int)threadIdx.x);
-      }
-    }
-    __syncthreads();
-
-    // phi(K) of this wave's features enters only contractions over the key
-    // tokens: token-row fragments (k = tokens), no transpose
-    Frag<T> pk[SH::KT][SH::FC];
-#pragma unroll
-    for (int ks = 0; ks < SH::KT; ++ks) feature_frags_rows<T, D, FW, NS, StX::LD>(fs, XK, SCK, ks, pk[ks], fv);
-    // phi(Q)/den and its P2-derivative fragments (the 1/den of dphi(Q) is
-    // carried by these: their products with dphi(Q) in the chain rule are the
-    // same)
-    Frag<T> phq[SH::FT][SH::TT], psq[SH::FT][SH::TT];
-#pragma unroll
-    for (int tt = 0; tt < SH::TT; ++tt) {
-      ProjT<T> p[SH::PR];
-      typename StX::Ssq ssq;
-      project_tile_lds<T, D, FW, NS, StX::LD>(fs, XQ, SSQ, tt, p, ssq);
-      const float sc = row_scale(ssq, inv_c, a.s_const, tok0 + tt * 16 + r < a.N) * GS[tt * 16 + r][0];
-#pragma unroll
-      for (int ft = 0; ft < SH::FT; ++ft) features_psi<T, SH::FT, NS>(p, ft, sc, phq[ft][tt], psq[ft][tt], fv);
     }
     if constexpr (WR) {
-      // R'^T += [dO | -delta]^T-rows x phi(Q)/den, with phi(Q)/den as [token]
-      // [feature] in this wave's LDS block (read transposed; the block takes
-      // this wave's dP later, after these reads)
+      // R'^T += [dO | -delta]^T-rows x phi(Q)/den, with phi(Q)/den read back
+      // transposed from this wave's fragments (which take its dP after that)
 #pragma unroll
-      for (int tt = 0; tt < SH::TT; ++tt)
+      for (int tt = 0; tt < SH::TT; ++tt) DP[tt][w].put(l, phq[tt]);
+      Frag<T> gt[SH::DVT1];
 #pragma unroll
-        for (int ft = 0; ft < SH::FT; ++ft)
-          store_frag_nm<T>(PT[w], LDP, tt * 16, (2 * ft) * 16, (2 * ft + 1) * 16, phq[ft][tt]);
-#pragma unroll
-      for (int ks = 0; ks < SH::KT; ++ks) {
-        Frag<T> gt[SH::DVT1];
-#pragma unroll
-        for (int dt = 0; dt < SH::DVT; ++dt) gt[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
-        gt[SH::DVT] = delta_rows<T>(GS, ks);
-#pragma unroll
-        for (int fc = 0; fc < SH::FC; ++fc) {
-          const Frag<T> pq = lds_tr_frag<T>(PT[w], LDP, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, fc * 16);
-#pragma unroll
-          for (int dt = 0; dt < SH::DVT1; ++dt) mma(RT[dt][fc], gt[dt], pq);
-        }
-      }
-    }
-    // intra-chunk M^T[j][i] = dO_i . V_j - delta_i for j <= i (1/den_i applied later)
-    Frag<T> mt[CAUSAL ? SH::KT : 1][SH::TT];
-    if (CAUSAL) {
-#pragma unroll
-      for (int tq = 0; tq < SH::TT; ++tq) {
-        const float dl = GS[tq * 16 + r][1];
-        f32x4 m[SH::TT];
-#pragma unroll
-        for (int tk = 0; tk < SH::TT; ++tk) {
-          m[tk] = zero4();
-          if (tk <= tq) {
-#pragma unroll
-            for (int kd = 0; kd < SH::DV / 32; ++kd) {
-              Frag<T> av, bo;
-              lds_row8(av, XV + (tk * 16 + r) * StV::LD, kd * 32 + 8 * g);
-              lds_row8(bo, XDO + (tq * 16 + r) * StV::LD, kd * 32 + 8 * g);
-              mma(m[tk], av, bo);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const bool keep = tk < tq || 4 * g + i <= r;
-              const float md = m[tk][i] - dl;
-              m[tk][i] = keep ? md : 0.f;
-            }
-          }
-        }
-#pragma unroll
-        for (int ks = 0; ks < SH::KT; ++ks) mt[ks][tq] = pair_tiles<T>(m[2 * ks], m[2 * ks + 1]);
-      }
-    }
-    // den * dphi(Q)^T[feature][query] = phi(K)^T M^T + S'^T-rows x [dO | -delta]
-    f32x4 dph[SH::FC][SH::TT];
-#pragma unroll
-    for (int tq = 0; tq < SH::TT; ++tq) {
-      Frag<T> gf[KG];
-#pragma unroll
-      for (int kd = 0; kd < KG; ++kd) {
-        if (32 * kd < SH::DV) {
-          gf[kd] = lds_tok_frag<T>(reinterpret_cast<const T*>(XDO) + (tq * 16 + r) * StV::LD, kd);
-        } else {
-          Frag<T> f;
-          f.zero();
-          float hi, lo;
-          neg_split<T>(GS[tq * 16 + r][1], hi, lo);
-          if (g == 0) { f.set(0, hi); f.set(1, lo); }
-          gf[kd] = f;
-        }
-      }
+      for (int dt = 0; dt < SH::DVT; ++dt) gt[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StX::LD, 4 * g, 16 + 4 * g, dt * 16);
+      gt[SH::DVT] = lds_tok_frag<T>(DLT + (r < 2 ? r : 2) * DLD, 0);
 #pragma unroll
       for (int fc = 0; fc < SH::FC; ++fc) {
-        f32x4 acc = zero4();
-        if (CAUSAL) {
+        const Frag<T> pq = tr_of_frags(DP[0][w], DP[1][w], fc);
 #pragma unroll
-          for (int ks = 0; ks < SH::KT; ++ks)
-            if (32 * ks <= 16 * tq + 15) mma(acc, pk[ks][fc], mt[ks][tq]);
-        }
-#pragma unroll
-        for (int kd = 0; kd < KG; ++kd) {
-          const f32x4 z = zero4();
-          const Frag<T> sp = pair_tiles<T>(ST[2 * kd][fc], 2 * kd + 1 < SH::DVT1 ? ST[2 * kd + 1][fc] : z);
-          mma(acc, sp, gf[kd]);
-        }
-        dph[fc][tq] = acc;
+        for (int dt = 0; dt < SH::DVT1; ++dt) mma(RT[dt][fc], gt[dt], pq);
       }
     }
     if (CAUSAL) {
-      // S'^T += [V | 1]^T-rows x phi(K)
+      // M share of dphi(Q); S'^T += [V | 1]^T-rows x phi(K)
 #pragma unroll
-      for (int ks = 0; ks < SH::KT; ++ks) {
-        Frag<T> vt[SH::DVT];
+      for (int tq = 0; tq < SH::TT; ++tq) {
+        const Frag<T> mt = MT[CAUSAL ? tq : 0][l];
 #pragma unroll
-        for (int dt = 0; dt < SH::DVT; ++dt) vt[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XV), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
+        for (int fc = 0; fc < SH::FC; ++fc) mma(dph[fc][tq], pk[fc], mt);
+      }
 #pragma unroll
-        for (int fc = 0; fc < SH::FC; ++fc) {
+      for (int dt = 0; dt < SH::DVT1; ++dt) {
+        const Frag<T> vt = dt < SH::DVT ? lds_tr_frag<T>(reinterpret_cast<const T*>(XV), StX::LD, 4 * g, 16 + 4 * g, dt * 16) : ones;
 #pragma unroll
-          for (int dt = 0; dt < SH::DVT; ++dt) mma(ST[dt][fc], vt[dt], pk[ks][fc]);
-          mma(ST[SH::DVT][fc], ones, pk[ks][fc]);
-        }
+        for (int fc = 0; fc < SH::FC; ++fc) mma(ST[dt][fc], vt, pk[fc]);
       }
     }
-    // chain rule through phi(Q): dP per radian, tiles [projection row tile][token tile]
-    f32x4 dp[SH::PR][SH::TT];
+    // chain rule through phi(Q) (as for K in the dK/dV sweep): dP per radian
 #pragma unroll
-    for (int tt = 0; tt < SH::TT; ++tt)
+    for (int tt = 0; tt < SH::TT; ++tt) {
+      f32x4 d1, d2 = zero4();
 #pragma unroll
-      for (int ft = 0; ft < SH::FT; ++ft) {
-        f32x4 d2 = zero4();
-        feature_grad<T, SH::FT, NS>(phq[ft][tt], psq[ft][tt], dph[2 * ft][tt], dph[2 * ft + 1][tt], dp[ft][tt], d2);
-        if (NS) dp[SH::FT + ft][tt] = d2;
+      for (int i = 0; i < 4; ++i) {
+        const float da = dph[0][tt][i], db = dph[1][tt][i];
+        d1[i] = qw[tt][i] * (qc[tt][i] * db - qs[tt][i] * da);
+        if constexpr (NS) d2[i] = -qz[tt][i] * (qc[tt][i] * da + qs[tt][i] * db);
       }
-    // dP of this wave as [token][projection row] in its LDS block
-#pragma unroll
-    for (int pr = 0; pr < SH::PR; ++pr)
-#pragma unroll
-      for (int tt = 0; tt < SH::TT; ++tt) store_tile_nm<T>(PT[w], LDP, tt * 16, pr * 16, dp[pr][tt]);
-    __syncthreads();   // every wave's dP block complete
-    // dQ = dP W' over all projection rows: each wave computes whole output
-    // tiles dQ^T (d tile, token tile) from every wave's dP block and that
-    // wave's dX fragments, so no cross-wave reduction is needed
-    // (every tile's products first, then the stores: the dX fragment loads of
-    // a later tile never wait behind an earlier tile's stores)
+      DP[tt][w].put(l, pair_tiles<T>(d1, d2));
+    }
+    // the next chunk's rows (the last step stages its own rows again, unused)
+    stage(step + 1, c + 1 < c1 ? c + 1 : c);
+    __syncthreads();   // dP and the next chunk's rows complete
+
+    // ---- interval 3
+    // the lane index again, opaque: its uses from here to the next interval 3
+    // compute their addresses once per chunk instead of holding each one in a
+    // register for the whole sweep
+    asm volatile("" : "+v"(l));
+    r = l % 16;
+    g = l / 16;
+    fs.load_frags(wproj);   // the next chunk's (the last step's are unused)
+    // dQ = dP W' over all projection rows, whole output tiles
     f32x4 acc[NOT];
 #pragma unroll
     for (int k = 0; k < NOT; ++k) {
-      const int ot = w + k * NW;
+      const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
       acc[k] = zero4();
-      if (ot >= DT * SH::TT) continue;
-      const int dt = ot % DT, tt = ot / DT;
+      if (DT * SH::TT % NW != 0 && ot >= DT * SH::TT) continue;
 #pragma unroll
-      for (int ww = 0; ww < NW; ++ww) {
-        const Frag<T>* wd = DX_LDS ? DXL[ww] : FragBlock<T, D, FW, NS>::dx(a.wfrag, h, NW, ww);
+      for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
         for (int ks = 0; ks < WTS::KP; ++ks) {
-          Frag<T> b = load_frag_nm<T>(PT[ww], LDP, tt * 16, (2 * ks) * 16, (2 * ks + 1) * 16);
-          if (2 * ks + 1 >= SH::PR) {   // no second row tile: keep unwritten LDS out of the product
-#pragma unroll
-            for (int j = 4; j < 8; ++j) b.set(j, 0.f);
-          }
-#pragma unroll
-          for (int sp = 0; sp < WTS::NSPLIT; ++sp) mma(acc[k], wd[((sp * DT + dt) * WTS::KP + ks) * WAVE + l], b);
+          if constexpr (DX_LDS) mma(acc[k], DXL[ww][(dt * WTS::KP + ks) * WAVE + l], DP[tt][ww].get(l));
+          else mma(acc[k], wf[k % NDK][ww][ks], DP[tt][ww].get(l));
         }
-      }
     }
 #pragma unroll
     for (int k = 0; k < NOT; ++k) {
-      const int ot = w + k * NW;
-      if (ot >= DT * SH::TT) continue;
-      const int dt = ot % DT, tt = ot / DT;
+      const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
+      if (DT * SH::TT % NW != 0 && ot >= DT * SH::TT) continue;
       if (ACC) acc[k] += old_q[k];   // later frequency groups add their share
       dqb.store_f4(((tt * 16 + r) * D + dt * 16 + 4 * g) * 4, acc[k]);
     }
-    // frequency gradient partial: dW'[rows][d] += dP^T Q
+    // frequency gradient partial: dW'[rows][d] += dP^T Q, one 32-token k-step
     {
-      // one 32-token k-step per chunk, added to the LDS partial one
-      // projection-row tile at a time
-      static_assert(SH::KT == 1, "one token k-step per chunk");
       Frag<T> xq[DT];
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) xq[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XQ), StX::LD, 4 * g, 16 + 4 * g, dt * 16);
 #pragma unroll
       for (int pr = 0; pr < SH::PR; ++pr) {
-        const Frag<T> dpt = lds_tr_frag<T>(PT[w], LDP, 4 * g, 16 + 4 * g, pr * 16);
-        dw_mma_row<D, T>(DWL[w], pr, dpt, xq);
+        const Frag<T> dpt = tr_of_frags(DP[0][w], DP[1][w], pr);
+        if constexpr (DW_REG) {
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) mma(DW[pr][dt], dpt, xq[dt]);
+        } else {
+          dw_mma_row<D, T>(DWL[w], pr, dpt, xq);
+        }
       }
     }
   }
@@ -397,9 +452,12 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_dq(BwdArgs a) {
 #pragma unroll
   for (int pr = 0; pr < SH::PR; ++pr)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      *reinterpret_cast<f32x4*>(out + dw_tile_off<SH, D>(w, pr, dt, l)) =
-          *reinterpret_cast<const f32x4*>(&DWL[w][((pr * DT + dt) * WAVE + l) * 4]);
+    for (int dt = 0; dt < DT; ++dt) {
+      f32x4 v;
+      if constexpr (DW_REG) v = DW[pr][dt];
+      else v = *reinterpret_cast<const f32x4*>(&DWL[w][((pr * DT + dt) * WAVE + l) * 4]);
+      *reinterpret_cast<f32x4*>(out + dw_tile_off<SH, D>(w, pr, dt, l)) = v;
+    }
   if constexpr (WR) {
     float* ro = a.rstate + ((size_t)bh * a.segments + seg) * SH::STATE;
 #pragma unroll

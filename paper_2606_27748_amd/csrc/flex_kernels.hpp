@@ -185,9 +185,9 @@ constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
   return bf16 && (m > 64 || d < 128 || ch < 64 || !causal) ? 2 : 1;
 }
 
-// Waves per SIMD the dK/dV sweep is compiled for: two, except at d = 128 (one
+// Waves per SIMD the backward sweeps are compiled for: two, except at d = 128 (one
 // wave's states and dW' partial alone take 136 registers) and on the fp32 path.
-constexpr int dkv_waves_per_eu(bool bf16, int d) { return bf16 && d <= 64 ? 2 : 1; }
+constexpr int bwd_waves_per_eu(bool bf16, int d) { return bf16 && d <= 64 ? 2 : 1; }
 
 // state (or NULL): [BH][P*sub][E]; writes the exclusive prefix (causal) into
 // slot p*sub of every segment p, or the total (non-causal) into slot 0.

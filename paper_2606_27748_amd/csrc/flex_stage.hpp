@@ -457,26 +457,55 @@ __device__ __forceinline__ Frag<T> lds_tr_frag(const T* L, int ld, int kb0, int 
   return f;
 }
 
-// The transpose load from operand fragments as they are stored, [lane][8
-// slots]: f0 holds columns (lane % 16) 0..15, f1 16..31, its slots 4 half +
-// (0..3) the rows 4g + (0..3) of one tile.  The result has lane m = row and
-// k slots 0..3 = columns 4g .. 4g+3 (f0), 4..7 = columns 16 + 4g .. (f1).
+// One wave's operand fragment in LDS as it is held, 8 slots per lane (fp32:
+// the lane groups 32 bytes further apart, so that the transposed reads of tr()
+// fall into different banks).
 template <class T>
-__device__ __forceinline__ Frag<T> tr_of_frags(const Frag<T> (&f0)[WAVE], const Frag<T> (&f1)[WAVE], int half) {
+struct FragLds {
+  static constexpr int PAD = IsBf16<T>::value ? 0 : 8;   // elements per lane group
+  __attribute__((aligned(16))) T v[WAVE * 8 + 4 * PAD];
+  static __device__ __forceinline__ int at(int l) { return l * 8 + l / 16 * PAD; }
+  __device__ __forceinline__ void put(int l, const Frag<T>& f) { *reinterpret_cast<decltype(f.v)*>(v + at(l)) = f.v; }
+  __device__ __forceinline__ Frag<T> get(int l) const {
+    Frag<T> f;
+    f.v = *reinterpret_cast<const decltype(f.v)*>(v + at(l));
+    return f;
+  }
+};
+template <>
+__device__ __forceinline__ void FragLds<float>::put(int l, const Frag<float>& f) {
+  float4* o = reinterpret_cast<float4*>(v + at(l));
+  o[0] = make_float4(f.v[0], f.v[1], f.v[2], f.v[3]);
+  o[1] = make_float4(f.v[4], f.v[5], f.v[6], f.v[7]);
+}
+template <>
+__device__ __forceinline__ Frag<float> FragLds<float>::get(int l) const {
+  Frag<float> f;
+  lds_row8(f, v + at(l), 0);
+  return f;
+}
+
+// The transpose load from two fragments in LDS: f0 holds columns (lane % 16)
+// 0..15, f1 16..31, its slots 4 half + (0..3) the rows 4g + (0..3) of one
+// tile.  The result has lane m = row and k slots 0..3 = columns 4g .. 4g+3
+// (f0), 4..7 = columns 16 + 4g .. (f1).
+template <class T>
+__device__ __forceinline__ Frag<T> tr_of_frags(const FragLds<T>& f0, const FragLds<T>& f1, int half) {
   const int l = threadIdx.x % WAVE, i = l % 16, g = l / 16;
   Frag<T> f;
   if constexpr (IsBf16<T>::value) {
     // lane i of a group addresses column 4g + i/4, rows 4 (i % 4) .. + 3
-    const int at = (16 * (i % 4) + 4 * g + i / 4) * 8 + 4 * half;
-    const tr_v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(reinterpret_cast<const T*>(&f0[0]) + at));
-    const tr_v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(reinterpret_cast<const T*>(&f1[0]) + at));
+    const int at = FragLds<T>::at(16 * (i % 4) + 4 * g + i / 4) + 4 * half;
+    const tr_v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(f0.v + at));
+    const tr_v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(f1.v + at));
     f.v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
   } else {
     // lane i is row i: slot i % 4 of the fragments of lanes 16 (i / 4) + column
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      f.set(j, f0[16 * (i / 4) + 4 * g + j].v[4 * half + i % 4]);
-      f.set(4 + j, f1[16 * (i / 4) + 4 * g + j].v[4 * half + i % 4]);
+      const int at = FragLds<T>::at(16 * (i / 4) + 4 * g + j) + 4 * half + i % 4;
+      f.set(j, f0.v[at]);
+      f.set(4 + j, f1.v[at]);
     }
   }
   return f;
