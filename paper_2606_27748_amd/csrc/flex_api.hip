@@ -238,6 +238,14 @@ int fwd_fold_of(const flex_desc* d, int P) {
   return d->causal && (long long)pre_segs_of(d, P) * fwd_sub_of(d, P) <= kFoldMax ? 1 : 0;
 }
 
+// Workgroups of the attention sweeps that run on one CU at a time: the bf16
+// shapes of 64 frequencies at d <= 64 (4 waves, within 256 registers and 80 KB
+// of LDS) run two, the others one.
+int resident_wgs(const flex_desc* d) {
+  const KernelShape ks = attn_shape(d);
+  return ks.bf16 && ks.d <= 64 && ks.m == 64 ? 2 : 1;
+}
+
 // Segments per (b,h): enough workgroups to cover the 256 CUs in whole rounds
 // while keeping the per-segment state traffic small.  Costs are in units of
 // one sweep chunk: the sweep's rounds of chunks (a pre-pass adds about a third
@@ -245,9 +253,13 @@ int fwd_fold_of(const flex_desc* d, int P) {
 // the pre-pass, read and written by the scan, read by the sweep).  A chunk's
 // time is estimated from its MFMA work relative to the d = 64, m = 128
 // nonstationary shape, measured at about 6.7 us per 64-token chunk.
-int pick_segments(const flex_desc* d) {
+// Two workgroups that share a CU take about 1.45 times as long as one.  us per
+// training step of m = 64 shapes with one and with two per CU: d = 64, B*H = 64,
+// N = 4000 non-causal 220 and 205, causal 303 and 254; stationary B*H = 32,
+// N = 8192 272 and 228; B*H = 8, N = 16000 180 and 168; but B*H = 32, N = 2048
+// (segments of 4 and 2 chunks) 108 and 114, which the state traffic keeps at one.
+int plan_segments(const flex_desc* d, int resident) {
   const int nc = nchunks_of(d);
-  if (d->segments > 0) return d->segments < nc ? d->segments : nc;
   const long long bh = (long long)d->B * d->H;
   const KernelShape ks = attn_shape(d);
   const double m_eff = ks.nonstationary ? 2.0 * ks.m : ks.m;
@@ -260,13 +272,28 @@ int pick_segments(const flex_desc* d) {
     const int cps = (nc + p - 1) / p;
     const int used = (nc + cps - 1) / cps;  // segments that hold chunks
     if (used != p) continue;
-    const long long wgs = bh * p;
-    const long long rounds = (wgs + kCUs - 1) / kCUs;
+    const long long per_cu = (bh * p + kCUs - 1) / kCUs;
+    const double rounds = resident == 2 ? 1.45 * (double)(per_cu / 2) + (double)(per_cu % 2) : (double)per_cu;
     const double traffic = 4.0 * p * bh * state_bytes / 5.0e12 / t_chunk;
     const double cost = rounds * (double)cps * (p > 1 || !d->causal ? 1.35 : 1.0) + 0.5 * p * bh / kCUs + traffic;
     if (cost < best_cost - 1e-9) { best_cost = cost; best = p; }
   }
   return best;
+}
+
+size_t fwd_ws_bytes(const flex_desc* d, int P);
+
+// extra: bytes of the forward workspace besides the plan's own.  A plan for
+// two workgroups per CU holds more segment states; where these alone would
+// take the forward past the static scratch of the no-allocation entry point,
+// the plan for one is used, in every entry point alike.
+int pick_segments(const flex_desc* d, size_t extra = 0) {
+  const int nc = nchunks_of(d);
+  if (d->segments > 0) return d->segments < nc ? d->segments : nc;
+  const int p = plan_segments(d, resident_wgs(d));
+  if (resident_wgs(d) == 1 || fwd_ws_bytes(d, p) + extra <= (size_t)FLEX_NOALLOC_SCRATCH_BYTES) return p;
+  const int p1 = plan_segments(d, 1);
+  return fwd_ws_bytes(d, p1) + extra <= (size_t)FLEX_NOALLOC_SCRATCH_BYTES ? p1 : p;
 }
 
 float s_const_of(const flex_desc* d) {
@@ -279,15 +306,19 @@ float s_const_of(const flex_desc* d) {
 // Forward workspace: the segment states of every frequency group, one block of
 // prepared fragments (reused group after group) and, with several groups, the
 // fp32 numerator / denominator sums.
-size_t fwd_group_state_bytes(const flex_desc* d) {
-  const size_t P = (size_t)pick_segments(d);
-  return align256((size_t)d->B * d->H * P * fwd_sub_of(d, (int)P) * fwd_state_floats(attn_shape(d)) *
-                  sizeof(float));
+size_t fwd_group_state_bytes(const flex_desc* d, int P) {
+  return align256((size_t)d->B * d->H * P * fwd_sub_of(d, P) * fwd_state_floats(attn_shape(d)) * sizeof(float));
 }
+size_t fwd_group_state_bytes(const flex_desc* d) { return fwd_group_state_bytes(d, pick_segments(d)); }
 size_t fwd_acc_bytes(const flex_desc* d) {
   if (groups_of(d).n == 1) return 0;
   const size_t rows = (size_t)d->B * d->H * d->N;
   return align256(rows * d->dv * sizeof(float)) + align256(rows * sizeof(float));
+}
+
+size_t fwd_ws_bytes(const flex_desc* d, int P) {
+  return groups_of(d).n * fwd_group_state_bytes(d, P) + align256(wfrag_bytes(attn_shape(d), d->H)) + fwd_acc_bytes(d) +
+         pad_bytes(d);
 }
 
 // dv != d: the attention runs at width w = max(d, dv) on zero-padded
@@ -297,11 +328,6 @@ size_t fwd_acc_bytes(const flex_desc* d) {
 // and dO get d - dv zero columns: den, delta and every gradient but the
 // padded columns of dV are unchanged.  The padded copies sit after the
 // padded shape's own workspace.
-flex_desc padded_desc(const flex_desc* d) {
-  flex_desc p = *d;
-  p.d = p.dv = d->d > d->dv ? d->d : d->dv;
-  return p;
-}
 struct ValuePad {
   size_t q, k, w1, w2, dq, dk, dw1, dw2, v, o, dO, dv, total;
 };
@@ -338,6 +364,15 @@ ValuePad value_pad_of(const flex_desc* d, int pass) {
   return L;
 }
 
+// The padded shape, with the segments chosen for it (they depend on the whole
+// forward workspace).
+flex_desc padded_desc(const flex_desc* d) {
+  flex_desc p = *d;
+  p.d = p.dv = d->d > d->dv ? d->d : d->dv;
+  p.segments = pick_segments(&p, value_pad_of(d, FLEX_PASS_FWD).total);
+  return p;
+}
+
 size_t ws_bytes_of(const flex_desc* d, int pass) {
   if (d->dv != d->d && pass != FLEX_PASS_FEATURE_MAP) {
     const flex_desc pd = padded_desc(d);
@@ -348,7 +383,7 @@ size_t ws_bytes_of(const flex_desc* d, int pass) {
   const size_t P = (size_t)pick_segments(d);
   if (pass == FLEX_PASS_FEATURE_MAP) return 0;
   const size_t wf = align256(wfrag_bytes(ks, d->H));
-  if (pass == FLEX_PASS_FWD) return groups_of(d).n * fwd_group_state_bytes(d) + wf + fwd_acc_bytes(d) + pad_bytes(d);
+  if (pass == FLEX_PASS_FWD) return fwd_ws_bytes(d, (int)P);
   // backward: key-side and query-side states, per-token scalars, frequency-gradient
   // and dtau partials
   return 2 * align256(bh * P * bwd_state_floats(ks) * sizeof(float)) +
@@ -509,8 +544,8 @@ int32_t run_fwd(const flex_desc* desc, const void* Q, const void* K, const void*
   } else {
     // chunks per non-causal sweep workgroup: up to kSweepChunks (or
     // kReadoutChunks), fewer when that leaves the CUs short of workgroups
-    // (one, or for the token-split readout two, resident per CU)
-    const int per_wg = readout_split(desc) ? 2 : 1;
+    // (with resident_wgs of them running on a CU at a time)
+    const int per_wg = resident_wgs(desc);
     const int cap = readout_split(desc) ? kReadoutChunks : kSweepChunks;
     const long long per_cu = ((long long)a.nchunks * a.BH + per_wg * kCUs - 1) / (per_wg * kCUs);
     a.sweep_chunk = kChunk;
