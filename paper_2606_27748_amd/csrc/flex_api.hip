@@ -189,12 +189,12 @@ int nchunks_of(const flex_desc* d) { return (d->N + kChunk - 1) / kChunk; }
 
 // Chunks per workgroup of the non-causal sweep (its chunks are independent).
 constexpr int kSweepChunks = 8;
-// The bf16 stationary shapes with m = 64 read out with the tokens split
+// The bf16 stationary shapes with m <= 64 (one group) read out with the tokens split
 // across waves (k_fwd_readout): a workgroup holds the whole total state, so it
 // takes up to 64 chunks, about one round of two workgroups per CU.
 constexpr int kReadoutChunks = 64;
 bool readout_split(const flex_desc* d) {
-  return !d->causal && d->io_dtype == FLEX_BF16 && d->variant == FLEX_STATIONARY && d->m == 64 && d->d <= 64;
+  return !d->causal && d->io_dtype == FLEX_BF16 && d->variant == FLEX_STATIONARY && d->m <= 64 && d->d <= 64;
 }
 
 // Segments whose local state the forward pre-pass forms: a causal forward
@@ -228,14 +228,23 @@ int fwd_sub_of(const flex_desc* d, int P) {
   return best;
 }
 
-// Whether the causal sweeps (the forward's and the backward's dQ sweep) sum
-// their carry-in from the segments' local states themselves, with no scan
-// launch: when a workgroup reads at most kFoldMax local states.  The sum runs
-// in the scan's order, so both ways give the same bits.
+// Whether the sweeps (the forward's and the backward's dQ sweep) sum their
+// carry-in (causal) or the total state (non-causal) from the segments' local
+// states themselves, with no scan launch: when a workgroup reads at most
+// kFoldMax local states.  The sum runs in the scan's order, so both ways give
+// the same bits.  Non-causal, every workgroup reads every state (in the
+// token-split readout every wave does), so it pays only where the launch is
+// what counts: a single state (the scan would change nothing), or at most
+// kFoldChunks chunks in all.  us per call before and after: one fp32 head of 256
+// tokens 18.7 and 15.7; but B*H = 128, N = 16384 with four states 270 and 288.
 constexpr int kFoldMax = 4;
 constexpr int kRFoldMax = 8;   // R' suffixes: native-layout reads, cheaper to sum
+constexpr int kFoldChunks = 128;
+bool fold_noncausal(const flex_desc* d) { return (long long)nchunks_of(d) * d->B * d->H <= kFoldChunks; }
 int fwd_fold_of(const flex_desc* d, int P) {
-  return d->causal && (long long)pre_segs_of(d, P) * fwd_sub_of(d, P) <= kFoldMax ? 1 : 0;
+  const long long n = (long long)pre_segs_of(d, P) * fwd_sub_of(d, P);
+  if (d->causal) return n <= kFoldMax ? 1 : 0;
+  return n == 1 || (n <= kFoldMax && !readout_split(d) && fold_noncausal(d)) ? 1 : 0;
 }
 
 // Workgroups of the attention sweeps that run on one CU at a time: the bf16
@@ -643,7 +652,10 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
     a.ffold = fwd_fold_of(desc, a.segments);
     // with the forward's key-side states the scan would handle R' alone: the
     // dK/dV sweep sums its suffix itself when it reads at most kRFoldMax states
-    a.rfold = desc->causal && a.segments - 1 <= kRFoldMax ? 1 : 0;
+    // (non-causal: the total, under the forward's rule)
+    a.rfold = (desc->causal ? a.segments - 1 <= kRFoldMax
+                            : a.segments == 1 || (a.segments <= kFoldMax && fold_noncausal(desc)))
+                  ? 1 : 0;
   }
   a.s_const = s_const_of(desc);
   const size_t bh = (size_t)a.BH, P = (size_t)a.segments;

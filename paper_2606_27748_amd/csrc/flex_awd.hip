@@ -32,6 +32,8 @@
 #include "flex_stage.hpp"
 #include "flex_kernels.hpp"
 
+#include <type_traits>
+
 namespace flex {
 
 namespace {
@@ -42,6 +44,8 @@ constexpr float LN2 = 0.69314718055994531f;
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float log2_fast(float x) { return __builtin_amdgcn_logf(x); }
 __device__ __forceinline__ float rcp_fast(float x) { return __builtin_amdgcn_rcpf(x); }
+// The larger of two numbers as one instruction (fmaxf first quiets NaNs)
+__device__ __forceinline__ float max_fast(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, INFINITY); }
 
 // Waves per SIMD the quadratic passes are compiled for: the bf16 shapes with
 // up to 128 features fit 3 (4 for the d = 64 loss pass) without spilling; the
@@ -170,7 +174,12 @@ void k_awd_fwd(AwdArgs a) {
   StP sp;
   sx.fetch(K, 0, a.N);
   sp.fetch(PK, 0, a.N);
-  for (int kt = 0; kt < a.ntile; ++kt) {
+  // MASKED: a last tile that the keys do not fill; whole tiles take no masks (a
+  // third of the vector instructions; us per step of B*H = 256, N = 512, d = m =
+  // 64 with both passes' masks gone and the chain-rule pass counting its units:
+  // 233 before, 206 after)
+  auto key_tile = [&](int kt, auto masked) {
+    constexpr bool MASKED = decltype(masked)::value;
     __syncthreads();   // the previous tile's LDS reads are done
     sx.store(XL);
     sp.store(PL);
@@ -183,8 +192,6 @@ void k_awd_fwd(AwdArgs a) {
     f32x4 s[4], av[4];
     tile_products<T, D, F, StX::LD, StP::LD>(XL, PL, xf, pf, s, av);
     const int kb = kt * AWD_TILE + 4 * g;
-    // whole tiles (every tile but a ragged last one) skip the key masks
-    const bool full = (kt + 1) * AWD_TILE <= a.N;
     // the query's maximum over this tile's valid keys, shared by its four
     // lane groups (c1 > 0 scales raw logits into base 2)
     float tmax = -INFINITY;
@@ -192,7 +199,7 @@ void k_awd_fwd(AwdArgs a) {
     for (int sub = 0; sub < 4; ++sub)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (full || kb + sub * 16 + i < a.N) tmax = fmaxf(tmax, s[sub][i]);
+        if (!MASKED || kb + sub * 16 + i < a.N) tmax = max_fast(tmax, s[sub][i]);
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     tmax *= a.c1;
@@ -216,7 +223,7 @@ void k_awd_fwd(AwdArgs a) {
     for (int sub = 0; sub < 4; ++sub)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const bool ok = full || kb + sub * 16 + i < a.N;
+        const bool ok = !MASKED || kb + sub * 16 + i < a.N;
         const float e = ok ? exp2_fast(fmaf(s[sub][i], a.c1, nm)) : 0.f;
         Z += e;
         if (ok) LS = fmaf(e, log2_fast(av[sub][i] * rden), LS);
@@ -236,7 +243,10 @@ void k_awd_fwd(AwdArgs a) {
         }
       }
     }
-  }
+  };
+  const int nfull = a.N / AWD_TILE;
+  for (int kt = 0; kt < nfull; ++kt) key_tile(kt, std::false_type{});
+  if (nfull < a.ntile) key_tile(nfull, std::true_type{});
   // the four lane groups of a query share its maximum: plain sums
   Z += __shfl_xor(Z, 16);
   Z += __shfl_xor(Z, 32);
@@ -308,7 +318,10 @@ void k_awd_bwd_k(AwdArgs a) {
   // per-row statistics: loaded unconditionally from a clamped row, zeroed past N when stored
   bool sr_ok = (int)threadIdx.x < a.N;
   float2 sr = stats[min((int)threadIdx.x % AWD_TILE, a.N - 1)];
-  for (int ot = 0; ot < a.ntile; ++ot) {
+  // MASKED: as in the loss pass.  (Own rows past N compute unused values: no
+  // other row reads them, and they are not stored.)
+  auto query_tile = [&](int ot, auto masked) {
+    constexpr bool MASKED = decltype(masked)::value;
     __syncthreads();
     sx.store(XL);
     sp.store(PL);
@@ -333,7 +346,7 @@ void k_awd_bwd_k(AwdArgs a) {
         const float2 st = SL[sub * 16 + 4 * g + i];
         const float p = exp2_fast(s[sub][i] * a.c1 - st.x);
         const float gv = st.y - p * rcp_fast(av[sub][i]);
-        G[sub][i] = (ook && ob + sub * 16 + i < a.N) ? gv : 0.f;
+        G[sub][i] = !MASKED || ob + sub * 16 + i < a.N ? gv : 0.f;
       }
 #pragma unroll
     for (int kp = 0; kp < 2; ++kp) {
@@ -344,7 +357,10 @@ void k_awd_bwd_k(AwdArgs a) {
             lds_tr_frag<T>(reinterpret_cast<const T*>(PL), StP::LD, 32 * kp + 4 * g, 32 * kp + 16 + 4 * g,
                            ft * 16));
     }
-  }
+  };
+  const int nfull = a.N / AWD_TILE;
+  for (int ot = 0; ot < nfull; ++ot) query_tile(ot, std::false_type{});
+  if (nfull < a.ntile) query_tile(nfull, std::true_type{});
   // dphi is stored in the io dtype: its rounding (2^-9 relative on the bf16
   // path) is below that of the bf16 features the passes already use
   IO* dst = static_cast<IO*>(a.dphk) + po;
@@ -393,43 +409,40 @@ __global__ __launch_bounds__(M / 16 * WAVE) void k_awd_wgrad(AwdArgs a) {
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt) dw[pr][dt] = zero4();
   float gt = 0.f;
-  // chunk u -> rows n0.. of side (0: Q, 1: K) of slice (b, h)
-  auto rows_of = [&](int u, const IO*& X, const IO*& dph, int& n0, int& side) {
-    side = u / per_side;
-    const int rem = u % per_side, b = rem / nch;
-    const size_t bh = (size_t)b * a.H + h;
-    X = static_cast<const IO*>(side ? a.K : a.Q) + bh * a.N * D;
-    dph = static_cast<const IO*>(side ? a.dphk : a.dphq) + bh * a.N * F;
-    n0 = (rem % nch) * ROWS;
+  // Unit u is 32 rows from n0 of side (0: Q, 1: K) of slice (b, h); counted up,
+  // with no division per unit.
+  struct Unit {
+    int side, b, n0;
+  };
+  auto next = [&](Unit u) {
+    u.n0 += ROWS;
+    if (u.n0 >= a.N) {
+      u.n0 = 0;
+      if (++u.b == a.B) {
+        u.b = 0;
+        ++u.side;
+      }
+    }
+    return u;
   };
   StX sx;
   StD sd;
-  if (u0 < u1) {
-    const IO* X;
-    const IO* dph;
-    int n0, side;
-    rows_of(u0, X, dph, n0, side);
-    sx.fetch(X, n0, a.N);
-    sd.fetch(dph, n0, a.N);
-  }
+  auto fetch = [&](const Unit& u) {
+    const size_t bh = (size_t)u.b * a.H + h;
+    sx.fetch(static_cast<const IO*>(u.side ? a.K : a.Q) + bh * a.N * D, u.n0, a.N);
+    sd.fetch(static_cast<const IO*>(u.side ? a.dphk : a.dphq) + bh * a.N * F, u.n0, a.N);
+  };
+  Unit cur = {u0 / per_side, u0 % per_side / nch, u0 % nch * ROWS};
+  if (u0 < u1) fetch(cur);
   for (int u = u0; u < u1; ++u) {
-    const IO* X;
-    const IO* dph;
-    int n0, side;
-    rows_of(u, X, dph, n0, side);
-    const float gw = side ? 1.f : 0.f;   // dtau takes the K rows only
+    const int n0 = cur.n0;
+    const float gw = cur.side ? 1.f : 0.f;   // dtau takes the K rows only
     __syncthreads();
     sx.store(XL, SSQ);
     sd.store(DL);
     __syncthreads();
-    {
-      const IO* Xn;
-      const IO* dn;
-      int nn, sn;
-      rows_of(u + 1 < u1 ? u + 1 : u, Xn, dn, nn, sn);   // the last unit refetches itself (unused)
-      sx.fetch(Xn, nn, a.N);
-      sd.fetch(dn, nn, a.N);
-    }
+    if (u + 1 < u1) cur = next(cur);
+    fetch(cur);   // the last unit refetches itself (unused)
     f32x4 dp[2][FS::PR];
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {

@@ -341,14 +341,14 @@ void k_bwd_dkv(BwdArgs a) {
   const auto inv_c = inv_c_of<T>(a.tau[h]);
 
   f32x4 RT[SH::DVT1][SH::FC];
-  if (CAUSAL && a.rfold) {
-    // the suffix of the later segments' local states, summed in the scan's
-    // order (last segment first)
+  if (a.rfold) {
+    // the suffix of the later segments' local states (non-causal: the total),
+    // summed in the scan's order (last segment first)
 #pragma unroll
     for (int dt = 0; dt < SH::DVT1; ++dt)
 #pragma unroll
       for (int fc = 0; fc < SH::FC; ++fc) RT[dt][fc] = zero4();
-    for (int q = a.segments - 1; q > seg; --q) {
+    for (int q = a.segments - 1; q > (CAUSAL ? seg : -1); --q) {
       const float* in = a.rstate + ((size_t)bh * a.segments + q) * SH::STATE;
 #pragma unroll
       for (int dt = 0; dt < SH::DVT1; ++dt)
@@ -824,7 +824,7 @@ static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
   constexpr bool CAN_MASK = SH::M == 64;
   if (masked && (!CAN_MASK || a.acc)) return hipErrorInvalidValue;
   auto scan_r = [&]() -> hipError_t {
-    if (causal && a.rfold) return hipSuccess;
+    if (a.rfold) return hipSuccess;
     return launch_state_scan(a.fstate ? nullptr : a.sstate, a.rstate, a.BH, a.segments, 1, SH::STATE, causal, st,
                              a.segments);
   };

@@ -115,15 +115,15 @@ void k_bwd_dq(BwdArgs a) {
   const auto inv_c = inv_c_of<T>(a.tau[h]);
 
   f32x4 ST[SH::DVT1][SH::FC];
-  if (a.fstate && CAUSAL && a.ffold) {
-    // the forward ran no scan: the exclusive prefix of its local states, summed
-    // in the scan's order (the same sum the forward sweep formed)
+  if (a.fstate && a.ffold) {
+    // the forward ran no scan: the exclusive prefix (total) of its local states,
+    // summed in the scan's order (the same sum the forward sweep formed)
     const float* blk = a.fstate + (size_t)bh * a.segments * a.fsub * SH::STATE;
 #pragma unroll
     for (int dt = 0; dt < SH::DVT1; ++dt)
 #pragma unroll
       for (int fc = 0; fc < SH::FC; ++fc) ST[dt][fc] = zero4();
-    for (int k = 0; k < seg * a.fsub; ++k) {
+    for (int k = 0; k < (CAUSAL ? seg : a.segments) * a.fsub; ++k) {
       const float* in = blk + (size_t)k * SH::STATE;
 #pragma unroll
       for (int dt = 0; dt < SH::DVT1; ++dt)

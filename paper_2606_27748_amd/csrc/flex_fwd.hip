@@ -254,13 +254,13 @@ void k_fwd_sweep(FwdArgs a) {
   f32x4 S[SH::FC][SH::DVT1];
   {
     const float* blk = a.state + (size_t)bh * a.segments * a.sub * SH::STATE + (size_t)w * SH::WAVE_STATE;
-    if (CAUSAL && a.fold) {
-      // the exclusive prefix of the local states, summed in the scan's order
+    if (a.fold) {
+      // the exclusive prefix (total) of the local states, summed in the scan's order
 #pragma unroll
       for (int fc = 0; fc < SH::FC; ++fc)
 #pragma unroll
         for (int dt = 0; dt < SH::DVT1; ++dt) S[fc][dt] = zero4();
-      for (int k = 0; k < seg * a.sub; ++k) {
+      for (int k = 0; k < (CAUSAL ? seg : a.pre_segs) * a.sub; ++k) {
         const float* in = blk + (size_t)k * SH::STATE;
 #pragma unroll
         for (int fc = 0; fc < SH::FC; ++fc)
@@ -524,7 +524,7 @@ void k_fwd_readout(FwdArgs a) {
   StX sq;
   if (c0 < c1) sq.fetch(Q, c0 * CHUNK, a.N);
   const auto inv_c = inv_c_of<T>(a.tau[h]);
-  // total state (slot 0 of this slice after the scan): pre-pass wave ft holds
+  // total state (slot 0 of this slice): pre-pass wave ft holds
   // frequency tile ft, its tile fc = 0 the cos features and fc = 1 the sin ones
   Frag<T> sf[DVT1][FT];
   {
@@ -587,7 +587,11 @@ void k_fwd_readout(FwdArgs a) {
 // The chunk's X rows are staged through LDS (prefetched a chunk ahead), every
 // wave projects them for its frequency slice, and the features are gathered
 // as [token][feature] rows in LDS, then written out as whole 16-byte vectors.
-template <class T, int D, int FW, int NW, bool NS>
+// FULL: the launch fills all M frequencies (every m but a last slice's), so a
+// vector's place is known at compile time: the divisions by a row's vectors
+// were half of the kernel's instructions (us per call of B*H = 96, N = 1000, d =
+// 64, m = 128: 26 before, 20.6 after).
+template <class T, int D, int FW, int NW, bool NS, bool FULL>
 __global__ __launch_bounds__(NW * WAVE) void k_feature_map(FwdArgs a) {
   typedef Shape<T, D, FW, NW, NS> SH;
   typedef typename Io<T>::type IO;
@@ -603,9 +607,10 @@ __global__ __launch_bounds__(NW * WAVE) void k_feature_map(FwdArgs a) {
   // this launch covers frequencies [state_f0, state_f0 + fvalid) of state_m
   // (fvalid <= M, a multiple of 16): their cos and sin columns of rows of
   // 2 state_m features
-  const int fv = a.fvalid, mo = a.state_m, f0o = a.state_f0;
+  const int fv = FULL ? SH::M : a.fvalid, mo = a.state_m, f0o = a.state_f0;
   const int vrow = 2 * fv / VEC;               // output vectors per row
   const int nvo = CHUNK * vrow;
+  constexpr int NVO = (CHUNK * F / VEC + SH::NT - 1) / SH::NT;   // vectors per thread (at most)
   const IO* X = static_cast<const IO*>(blockIdx.z ? a.K : a.Q) + (size_t)bh * a.N * D;
   IO* Phi = static_cast<IO*>(blockIdx.z ? a.O2 : a.O) + (size_t)bh * a.N * 2 * mo;
   const int c0 = blockIdx.x * a.chunks_per_seg;
@@ -617,10 +622,10 @@ __global__ __launch_bounds__(NW * WAVE) void k_feature_map(FwdArgs a) {
   const auto inv_c = inv_c_of<T>(a.tau[h]);
   for (int c = c0; c < c1; ++c) {
     const int tok0 = c * CHUNK;
-    __syncthreads();   // the previous chunk's reads of XL and PH are done
+    // no barrier: the previous chunk's reads of XL ended before its last barrier
     sx.store(XL, SSQ);
     sx.fetch(X, c + 1 < c1 ? tok0 + CHUNK : tok0, a.N);   // the last chunk refetches itself (unused)
-    __syncthreads();
+    __syncthreads();   // rows staged; the previous chunk's features are read
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       ProjT<T> p[SH::PR];
@@ -640,12 +645,15 @@ __global__ __launch_bounds__(NW * WAVE) void k_feature_map(FwdArgs a) {
       }
     }
     __syncthreads();
-    for (int v = threadIdx.x; v < nvo; v += SH::NT) {
+    const RowBuf ob(Phi, 2 * mo, tok0, a.N, CHUNK);   // drops the rows past N
+#pragma unroll
+    for (int k = 0; k < NVO; ++k) {
+      const int v = threadIdx.x + k * SH::NT;
+      if ((!FULL || CHUNK * F / VEC % SH::NT != 0) && v >= nvo) break;
       const int t = v / vrow, j = v % vrow;
       const int part = j / (fv / VEC), cv = j % (fv / VEC);   // cos block, then sin block
-      if (tok0 + t < a.N)
-        *reinterpret_cast<uint4*>(Phi + (size_t)(tok0 + t) * 2 * mo + part * mo + f0o + cv * VEC) =
-            *reinterpret_cast<const uint4*>(PH + t * LDF + part * SH::M + cv * VEC);
+      ob.store16((t * 2 * mo + part * mo + f0o + cv * VEC) * (int)sizeof(IO),
+                 *reinterpret_cast<const uint4*>(PH + t * LDF + part * SH::M + cv * VEC));
     }
   }
 }
@@ -777,7 +785,8 @@ static hipError_t run_fmap_t(const FwdArgs& a, hipStream_t st) {
   typedef Shape<T, D, FW, NW, NS> SH;
   dim3 grid((a.nchunks + a.chunks_per_seg - 1) / a.chunks_per_seg, a.BH, a.K ? 2 : 1);
   timing_mark(KC_FEATURE_MAP, st, true);
-  k_feature_map<T, D, FW, NW, NS><<<grid, SH::NT, 0, st>>>(a);
+  if (a.fvalid == SH::M) k_feature_map<T, D, FW, NW, NS, true><<<grid, SH::NT, 0, st>>>(a);
+  else k_feature_map<T, D, FW, NW, NS, false><<<grid, SH::NT, 0, st>>>(a);
   timing_mark(KC_FEATURE_MAP, st, false);
   return hipGetLastError();
 }

@@ -33,10 +33,11 @@ struct FwdArgs {
   int sub;            // state pre-pass workgroups per segment (chunks_per_seg % sub == 0)
   int pre_segs;       // segments whose local state the pre-pass forms: all (non-causal),
                       // all but the last (causal: only exclusive prefixes are read)
-  int fold;           // causal: 1 = no scan launch, each sweep workgroup sums its carry-in
-                      // from the local states of the segments before its own (in the
-                      // scan's order); 0 = the scan writes the carry-ins over each
-                      // segment's first slot
+  int fold;           // 1 = no scan launch, each sweep workgroup sums its carry-in
+                      // (non-causal: the total) from the local states of the segments
+                      // before its own (of all segments), in the scan's order; 0 = the
+                      // scan writes the carry-ins over each segment's first slot (the
+                      // total into slot 0)
   int sweep_groups;   // sweep workgroups per (b,h): the segments (causal) or chunk groups (non-causal)
   int sweep_cps;      // chunks per sweep workgroup
   int sweep_chunk;    // tokens per chunk of the causal sweep: 16, 32 or 64 (the
@@ -95,9 +96,10 @@ struct BwdArgs {
   int ffold;          // 1: fstate holds the local states (the forward ran no scan) and
                       // the dQ sweep sums its carry-in from them; 0: the carry-in of
                       // segment p is in slot p*fsub
-  int rfold;          // causal with fstate: 1 = no scan launch, the dK/dV sweep sums its
-                      // R' carry-in from the local states of the later segments (in the
-                      // scan's order); 0 = the scan writes the suffixes over them
+  int rfold;          // with fstate: 1 = no scan launch, the dK/dV sweep sums its R'
+                      // carry-in from the local states of the later segments
+                      // (non-causal: of all segments), in the scan's order; 0 = the scan
+                      // writes the suffixes over them (the total into slot 0)
   int BH, B, H, N;
   int nchunks, segments, chunks_per_seg;
   float s_const;

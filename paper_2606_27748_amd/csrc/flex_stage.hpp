@@ -43,6 +43,9 @@ struct RowBuf {
   __device__ __forceinline__ float2 load_f2(int off) const {
     return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
   }
+  __device__ __forceinline__ void store16(int off, uint4 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off, 0, 0);
+  }
   __device__ __forceinline__ void store_f4(int off, f32x4 v) const {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off, 0, 0);
   }
