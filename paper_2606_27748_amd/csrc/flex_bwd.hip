@@ -292,7 +292,10 @@ void k_bwd_dkv(BwdArgs a) {
   __shared__ FragLds<T> DP[SH::TT][NW * WTS::KP];   // dP, operand fragments (k = pairs of projection row tiles)
   __shared__ __attribute__((aligned(16))) T RL[NW][SH::FC * 16 * RLP];   // R' copy
   __shared__ Frag<T> PK[SH::TT][NFT][WAVE];      // phi(K), operand fragments
-  __shared__ Frag<T> MP[SH::TT][WAVE], AP[SH::TT][WAVE];   // M and A: [key tile], k = query tokens
+  // M and A: [key tile], k = query tokens; A as a high and a low operand
+  // (rounded once over all features it would carry more error than the features)
+  constexpr int NSA = IsBf16<T>::value ? 2 : 1;
+  __shared__ Frag<T> MP[SH::TT][WAVE], AP[NSA][SH::TT][WAVE];
   // dX fragments of every wave's projection rows: held in registers with four
   // waves (each then has DT / 4 d tiles), in LDS with eight
   constexpr bool DX_LDS = NW > 4;
@@ -396,7 +399,8 @@ void k_bwd_dkv(BwdArgs a) {
     if (w < 2) {
       Frag<T> z;
       z.zero();
-      (w == 0 ? MP : AP)[1][l] = z;
+      if (w == 0) MP[1][l] = z;
+      else AP[0][1][l] = AP[NSA - 1][1][l] = z;
     }
     for (int i = threadIdx.x; i < 2 * 3 * DLD; i += SH::NT) DLT2[i / (3 * DLD)][i % (3 * DLD)] = T(0.0f);
     __syncthreads();
@@ -446,14 +450,21 @@ void k_bwd_dkv(BwdArgs a) {
   };
   // One tile (query tile tq, key tile tk) of an intra-chunk matrix, masked to
   // keys at or before the query, into its half of the operand fragment.
-  auto store_intra = [&](Frag<T>* M, int tq, int tk, f32x4 v) {
+  // (lo: its remainder's, or nullptr)
+  auto store_intra = [&](Frag<T>* M, Frag<T>* lo, int tq, int tk, f32x4 v) {
     if (tq == tk) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = 4 * g + i >= r ? v[i] : 0.f;
     }
     T* o = reinterpret_cast<T*>(&M[tk * WAVE + l]) + 4 * tq;
+    T hi[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (T)v[i];
+    for (int i = 0; i < 4; ++i) { hi[i] = (T)v[i]; o[i] = hi[i]; }
+    if (lo) {
+      T* ol = reinterpret_cast<T*>(&lo[tk * WAVE + l]) + 4 * tq;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ol[i] = (T)(v[i] - (float)hi[i]);
+    }
   };
   // Projection fragments, reloaded per chunk (held for the whole sweep they
   // would not fit the registers).
@@ -567,7 +578,7 @@ void k_bwd_dkv(BwdArgs a) {
         mma(m, ao, bv);
       }
       m -= *reinterpret_cast<const f32x4*>(DEL + tq * 16 + 4 * g);
-      store_intra(&MP[0][0], tq, tk, m);
+      store_intra(&MP[0][0], nullptr, tq, tk, m);
     }
     __syncthreads();   // phi(Q), phi(K), R' and M complete; the rows of Q and V are read
 
@@ -591,7 +602,7 @@ void k_bwd_dkv(BwdArgs a) {
 #pragma unroll
       for (int ft = 0; ft < NFT; ++ft)
         mma(at, PT[tq][ft].get(l), PK[tk][ft][l]);
-      store_intra(&AP[0][0], tq, tk, at);
+      store_intra(&AP[0][0][0], NSA == 2 ? &AP[1][0][0] : nullptr, tq, tk, at);
     }
     if (CAUSAL) {
       // M share of dphi(K), and R'^T += [dO | -delta]^T-rows x phi(Q)/den
@@ -669,7 +680,11 @@ void k_bwd_dkv(BwdArgs a) {
       const int ot = w + k * NW, dt = ot % DT, tt = ot / DT;
       dk[k] = zero4();
       if (DT * SH::TT % NW != 0 && ot >= DT * SH::TT) continue;
-      if (CAUSAL) mma(dv[k], lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 4 * g, 16 + 4 * g, dt * 16), AP[tt][l]);
+      if (CAUSAL) {
+        const Frag<T> gt = lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 4 * g, 16 + 4 * g, dt * 16);
+#pragma unroll
+        for (int p = 0; p < NSA; ++p) mma(dv[k], gt, AP[p][tt][l]);
+      }
 #pragma unroll
       for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
