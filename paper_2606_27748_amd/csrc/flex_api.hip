@@ -424,7 +424,7 @@ AwdLayout awd_layout(const flex_desc* d) {
   const size_t bh = (size_t)d->B * d->H, N = (size_t)d->N, F = 2 * (size_t)d->m;
   const size_t io = d->io_dtype == FLEX_BF16 ? 2 : 4;
   const size_t nmat = d->variant == FLEX_NONSTATIONARY ? 2 : 1;
-  const size_t parts = (size_t)flex::awd_parts(d->B, d->H, d->N);
+  const size_t parts = (size_t)flex::awd_parts(d->B, d->H, d->N, d->m);
   AwdLayout L;
   size_t off = 0;
   L.phq = off;    off += align256(bh * N * F * io);
@@ -790,7 +790,7 @@ int32_t flex_awd_loss(const flex_desc* desc, const void* Q, const void* K, const
   a.dtau = grads ? dtau : nullptr;
   a.BH = desc->B * desc->H; a.B = desc->B; a.H = desc->H; a.N = desc->N;
   a.ntile = awd_ntile(desc);
-  a.parts = awd_parts(desc->B, desc->H, desc->N);
+  a.parts = awd_parts(desc->B, desc->H, desc->N, desc->m);
   a.c1 = (float)(1.4426950408889634 / sqrt((double)desc->d));
   a.log2n = (float)log2((double)desc->N);
   a.inv_n = (float)(1.0 / (double)desc->N);

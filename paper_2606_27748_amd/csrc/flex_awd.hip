@@ -55,6 +55,11 @@ struct AwdOcc {
   static constexpr int value = (IsBf16<T>::value && F <= 128) ? ((GRAD || D < 64) ? 3 : 4) : 1;
 };
 
+// Waves per SIMD the chain-rule pass is compiled for: with 4-wave workgroups
+// (m = 64, bf16) the most that fit without spilling, three workgroups per CU
+// nonstationary and four stationary; the others keep the compiler's choice.
+constexpr int awd_wgrad_waves(bool bf16, int m, bool ns) { return !bf16 || m > 64 ? 1 : ns ? 3 : 4; }
+
 // Operand fragments of one row (COLS columns, k = columns) of a row-major
 // [N][COLS] io block; rows past the end read as zero.
 template <class T, int COLS>
@@ -386,7 +391,8 @@ void k_awd_bwd_k(AwdArgs a) {
 // rescaling of phi(Q_i) changes, so <phi(Q_i), dphi(Q_i)> = 0 exactly (formed
 // from rounded products it would be pure rounding noise).
 template <class T, int D, int M, bool NS>
-__global__ __launch_bounds__(M / 16 * WAVE) void k_awd_wgrad(AwdArgs a) {
+__global__ __launch_bounds__(M / 16 * WAVE) __attribute__((amdgpu_waves_per_eu(awd_wgrad_waves(IsBf16<T>::value, M, NS))))
+void k_awd_wgrad(AwdArgs a) {
   typedef typename Io<T>::type IO;
   constexpr int NW = M / 16, NT = NW * WAVE, F = 2 * M, ROWS = 32;
   typedef RowStage<IO, D, NT, ROWS> StX;
@@ -541,10 +547,11 @@ __global__ __launch_bounds__(256) void k_awd_reduce(AwdArgs a, int M, int D) {
     }
   }
   if (blockIdx.x != 0) return;
-  if (a.dW1 && a.dtau && threadIdx.x == 0) {
+  if (a.dW1 && a.dtau && w == 1) {   // every lane its share in order, then a fixed tree
     float t = 0.f;
-    for (int p = 0; p < a.parts; ++p) t += a.dtpart[(size_t)h * a.parts + p];
-    a.dtau[h] = t;
+    for (int p = l; p < a.parts; p += WAVE) t += a.dtpart[(size_t)h * a.parts + p];
+    t = group_sum(lane_sum<16>(t));
+    if (l == 0) a.dtau[h] = t;
   }
   for (int b = threadIdx.x; b < a.B; b += 256) {
     const size_t bh = (size_t)b * a.H + h;
@@ -593,11 +600,13 @@ bool awd_shape_supported(bool bf16, int d, int m) {
   return d == 32 && m == 64;
 }
 
-// Workgroups of the chain-rule pass per head: about 512 in all, at most one
-// per 32-row chunk of the head.
-int awd_parts(int B, int H, int N) {
+// Workgroups of the chain-rule pass per head: about 768 in all (three
+// per CU) at m = 64, 512 at m = 128 (8 waves each), at most one per 32-row
+// chunk of the head.
+int awd_parts(int B, int H, int N, int m) {
   const long long chunks = 2LL * B * ((N + 31) / 32);
-  long long p = (512 + H - 1) / H;
+  const int wgs = m == 64 ? 768 : 512;
+  long long p = (wgs + H - 1) / H;
   if (p > chunks) p = chunks;
   return (int)(p < 1 ? 1 : p);
 }

@@ -812,11 +812,13 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(BwdArgs a, int md4, int d) {
       *o1 = x[0];
     }
   }
-  if (a.dtau && blockIdx.x == 0 && threadIdx.x == 0) {
+  if (a.dtau && blockIdx.x == 0 && q == 1) {
+    // one wave, every lane its share of the partials in order, then a fixed tree
     float s = 0.f;
-    for (int b = 0; b < a.B; ++b)
-      for (int p = 0; p < a.segments; ++p) s += a.dtaupart[((size_t)b * a.H + h) * a.segments + p];
-    a.dtau[h] = a.acc ? a.dtau[h] + s : s;
+    for (int j = threadIdx.x % 64; j < count; j += 64)
+      s += a.dtaupart[((size_t)(j / a.segments) * a.H + h) * a.segments + j % a.segments];
+    s = group_sum(lane_sum<16>(s));
+    if (threadIdx.x % 64 == 0) a.dtau[h] = a.acc ? a.dtau[h] + s : s;
   }
 }
 

@@ -164,7 +164,7 @@ struct AwdArgs {
   float inv_n;        // 1 / N
   float s_const;
 };
-int awd_parts(int B, int H, int N);
+int awd_parts(int B, int H, int N, int m);
 // Supported (d, m) of the distillation loss; the launch returns
 // hipErrorInvalidValue for any other shape.
 bool awd_shape_supported(bool bf16, int d, int m);
