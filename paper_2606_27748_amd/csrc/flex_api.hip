@@ -185,6 +185,24 @@ KernelShape attn_shape(const flex_desc* d) {
   return k;
 }
 
+// Frequency groups of the forward: as groups_of, but of 128 at bf16 d = 128 when
+// m is a multiple of 128 (eight waves of 16 frequencies hold a group's states in
+// the forward; the backward's states and frequency-gradient partials of 128
+// would not fit).  Half as many groups read Q, K and V and pass on the sums of
+// numerator and denominator, and a sweep runs two waves per SIMD.  us per pass
+// with groups of 64 and of 128: training step B*H = 32, N = 8192, m = 256 2434
+// and 2050 (sweeps 561 and 300, pre-passes 183 and 112).
+Groups fwd_groups_of(const flex_desc* d) {
+  if (d->d == 128 && d->m % 128 == 0 && d->io_dtype == FLEX_BF16) return Groups{d->m / 128, 128, 128};
+  return groups_of(d);
+}
+// Kernel shape of the forward (one of its groups).
+KernelShape fwd_shape(const flex_desc* d) {
+  KernelShape k = kshape(d);
+  k.m = fwd_groups_of(d).m;
+  return k;
+}
+
 int nchunks_of(const flex_desc* d) { return (d->N + kChunk - 1) / kChunk; }
 
 // Chunks per workgroup of the non-causal sweep (its chunks are independent).
@@ -212,7 +230,7 @@ int fwd_sub_of(const flex_desc* d, int P) {
   const int cps = (nc + P - 1) / P;
   const long long used = pre_segs_of(d, P);
   if (used <= 0) return 1;
-  const KernelShape ks = attn_shape(d);
+  const KernelShape ks = fwd_shape(d);
   const long long cap = (long long)kCUs * fwd_state_wgs_per_cu(ks);
   const double m_eff = ks.nonstationary ? 2.0 * ks.m : ks.m;
   const double t_pre = 2.2e-6 * (2.0 * ks.d * m_eff + 4.0 * ks.m * (d->dv + 1)) / 66048.0;
@@ -316,17 +334,17 @@ float s_const_of(const flex_desc* d) {
 // prepared fragments (reused group after group) and, with several groups, the
 // fp32 numerator / denominator sums.
 size_t fwd_group_state_bytes(const flex_desc* d, int P) {
-  return align256((size_t)d->B * d->H * P * fwd_sub_of(d, P) * fwd_state_floats(attn_shape(d)) * sizeof(float));
+  return align256((size_t)d->B * d->H * P * fwd_sub_of(d, P) * fwd_state_floats(fwd_shape(d)) * sizeof(float));
 }
 size_t fwd_group_state_bytes(const flex_desc* d) { return fwd_group_state_bytes(d, pick_segments(d)); }
 size_t fwd_acc_bytes(const flex_desc* d) {
-  if (groups_of(d).n == 1) return 0;
+  if (fwd_groups_of(d).n == 1) return 0;
   const size_t rows = (size_t)d->B * d->H * d->N;
   return align256(rows * d->dv * sizeof(float)) + align256(rows * sizeof(float));
 }
 
 size_t fwd_ws_bytes(const flex_desc* d, int P) {
-  return groups_of(d).n * fwd_group_state_bytes(d, P) + align256(wfrag_bytes(attn_shape(d), d->H)) + fwd_acc_bytes(d) +
+  return fwd_groups_of(d).n * fwd_group_state_bytes(d, P) + align256(wfrag_bytes(attn_shape(d), d->H)) + fwd_acc_bytes(d) +
          pad_bytes(d);
 }
 
@@ -527,12 +545,12 @@ int32_t run_fwd(const flex_desc* desc, const void* Q, const void* K, const void*
   a.state_out = state_out;
   a.state_m = desc->m;
   a.state_dv = state_dv > 0 ? state_dv : desc->dv;
-  const Groups G = groups_of(desc);
-  const KernelShape ks = attn_shape(desc);
+  const Groups G = fwd_groups_of(desc);
+  const KernelShape ks = fwd_shape(desc);
   const size_t sb = fwd_group_state_bytes(desc);
   a.wfrag = base + G.n * sb;
   if (G.n > 1) {
-    char* acc = base + G.n * sb + align256(wfrag_bytes(ks, desc->H));
+    char* acc = base + G.n * sb + align256(wfrag_bytes(attn_shape(desc), desc->H));
     a.acc_num = reinterpret_cast<float*>(acc);
     a.acc_den = reinterpret_cast<float*>(acc + align256((size_t)desc->B * desc->H * desc->N * desc->dv * sizeof(float)));
   }
@@ -548,6 +566,7 @@ int32_t run_fwd(const flex_desc* desc, const void* Q, const void* K, const void*
     // the sweep's chunks of chunk_of(desc) tokens: a segment spans the same
     // tokens as its 64-token pre-pass chunks
     a.sweep_chunk = chunk_of(desc);
+    if (a.sweep_chunk > 32 && sweep_short_chunks(ks.d, ks.m)) a.sweep_chunk = 32;
     a.sweep_groups = a.segments;
     a.sweep_cps = a.chunks_per_seg * (kChunk / a.sweep_chunk);
   } else {
@@ -649,6 +668,7 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
   }
   if (fwd_ws) {
     a.fsub = fwd_sub_of(desc, a.segments);
+    a.fstride = (int)fwd_state_floats(fwd_shape(desc));
     a.ffold = fwd_fold_of(desc, a.segments);
     // with the forward's key-side states the scan would handle R' alone: the
     // dK/dV sweep sums its suffix itself when it reads at most kRFoldMax states
@@ -669,6 +689,7 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
   a.wfrag = base + 2 * sb + gb + align256(bh * P * bwd_dw_floats(ks) * sizeof(float)) + align256(bh * P * sizeof(float));
   a.dw_stride = desc->m * desc->d;
   const PadRows pr = pad_rows_of(desc, base + ws_bytes_of(desc, FLEX_PASS_BWD));
+  const int per = fwd_groups_of(desc).m / G.m;
   for (int g = 0; g < G.n; ++g) {
     if (!group_rows(desc, G, pr, g, W1, W2, stream, &a.W1, &a.W2, &a.w_stride, &a.fvalid))
       return FLEX_ERR_HIP;
@@ -677,7 +698,9 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
     a.dW2 = dW2 ? dW2 + woff : nullptr;
     a.acc = g > 0;
     if (fwd_ws)
-      a.fstate = reinterpret_cast<const float*>(static_cast<const char*>(fwd_ws) + g * fwd_group_state_bytes(desc));
+      // (a forward group of 128 frequencies holds two backward groups' states in a row)
+      a.fstate = reinterpret_cast<const float*>(static_cast<const char*>(fwd_ws) + g / per * fwd_group_state_bytes(desc)) +
+                 (g % per) * bwd_state_floats(ks);
     const hipError_t e = launch_bwd(a, ks, stream);
     if (e != hipSuccess) return FLEX_ERR_HIP;
   }

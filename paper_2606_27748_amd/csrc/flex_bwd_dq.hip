@@ -118,20 +118,20 @@ void k_bwd_dq(BwdArgs a) {
   if (a.fstate && a.ffold) {
     // the forward ran no scan: the exclusive prefix (total) of its local states,
     // summed in the scan's order (the same sum the forward sweep formed)
-    const float* blk = a.fstate + (size_t)bh * a.segments * a.fsub * SH::STATE;
+    const float* blk = a.fstate + (size_t)bh * a.segments * a.fsub * a.fstride;
 #pragma unroll
     for (int dt = 0; dt < SH::DVT1; ++dt)
 #pragma unroll
       for (int fc = 0; fc < SH::FC; ++fc) ST[dt][fc] = zero4();
     for (int k = 0; k < (CAUSAL ? seg : a.segments) * a.fsub; ++k) {
-      const float* in = blk + (size_t)k * SH::STATE;
+      const float* in = blk + (size_t)k * a.fstride;
 #pragma unroll
       for (int dt = 0; dt < SH::DVT1; ++dt)
 #pragma unroll
         for (int fc = 0; fc < SH::FC; ++fc) ST[dt][fc] += fwd_state_tile_t<SH>(in, w, dt, fc);
     }
   } else if (a.fstate) {
-    const float* in = a.fstate + ((size_t)bh * a.segments * a.fsub + (CAUSAL ? seg * a.fsub : 0)) * SH::STATE;
+    const float* in = a.fstate + ((size_t)bh * a.segments * a.fsub + (CAUSAL ? seg * a.fsub : 0)) * a.fstride;
 #pragma unroll
     for (int dt = 0; dt < SH::DVT1; ++dt)
 #pragma unroll

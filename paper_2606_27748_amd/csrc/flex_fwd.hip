@@ -27,7 +27,7 @@ namespace flex {
 // MASK: the variant for a padded frequency group (features of its padding
 // rows masked to zero), as in the sweeps.
 template <class T, int D, int FW, int NW, bool NS, bool MASK = false>
-__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(state_waves_per_eu(D, NS), state_waves_per_eu(D, NS))))
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(state_waves_per_eu(D, NS, NW), state_waves_per_eu(D, NS, NW))))
 void k_fwd_state(FwdArgs a) {
   typedef Shape<T, D, FW, NW, NS> SH;
   typedef typename Io<T>::type IO;
@@ -64,9 +64,9 @@ void k_fwd_state(FwdArgs a) {
   const Frag<T> ones = ones_all<T>();
   const int g = (threadIdx.x % WAVE) / 16;
 
-  // projection fragments: held for the whole sweep where registers allow
-  // (d <= 64), else reloaded per chunk ahead of the staging barriers
-  constexpr bool KEEP_FS = D <= 64;
+  // projection fragments: held for the whole sweep where registers allow, else
+  // reloaded per chunk ahead of the staging barriers
+  constexpr bool KEEP_FS = state_keeps_frags(D, NW);
   FreqSlice<T, D, FW, NS> fs;
   // held for the whole sweep: built from W by each wave (no prepared copy is needed)
   if (KEEP_FS) fs.load(a.W1 + (size_t)h * a.w_stride, NS ? a.W2 + (size_t)h * a.w_stride : nullptr, w * FW);
@@ -734,7 +734,7 @@ static void launch_sweep(const FwdArgs& a, bool causal, dim3 grid, hipStream_t s
     k_fwd_sweep<T, D, FW, NW, NS, true, ADD, 16, MASK><<<grid, SH::NT, 0, st>>>(a);
   } else if (a.sweep_chunk == 32) {
     k_fwd_sweep<T, D, FW, NW, NS, true, ADD, 32, MASK><<<grid, SH::NT, 0, st>>>(a);
-  } else {
+  } else if constexpr (!sweep_short_chunks(D, FW * NW)) {
     k_fwd_sweep<T, D, FW, NW, NS, true, ADD, 64, MASK><<<grid, SH::NT, 0, st>>>(a);
   }
 }
@@ -744,15 +744,16 @@ static hipError_t run_fwd_t(const FwdArgs& a, bool causal, hipStream_t st) {
   typedef Shape<T, D, FW, NW, NS> SH;
   const dim3 grid(a.sweep_groups * a.BH);
   const dim3 pgrid(a.pre_segs * a.sub * a.BH);
-  // prepared fragments serve the state pre-pass at d > 64, which reloads them
-  // per chunk; the other forward kernels build theirs from W once
-  if (D > 64) k_prep_freqs<T, D, FW, NW, NS><<<dim3(a.H, NW, 1), WAVE, 0, st>>>(a.W1, a.W2, a.wfrag, a.w_stride);
+  // prepared fragments serve the state pre-pass where it reloads them per
+  // chunk; the other forward kernels build theirs from W once
+  if (!state_keeps_frags(D, NW)) k_prep_freqs<T, D, FW, NW, NS><<<dim3(a.H, NW, 1), WAVE, 0, st>>>(a.W1, a.W2, a.wfrag, a.w_stride);
   timing_mark(KC_FWD_STATE, st, true);
   // a padded frequency group (only the 64-frequency shape has one, and it
   // runs first, so it never adds) takes the masking kernel variants
   const bool masked = a.fvalid < FW * NW;
   constexpr bool CAN_MASK = FW * NW == 64;
   if (masked && (!CAN_MASK || a.acc >= 2)) return hipErrorInvalidValue;
+  if (causal && sweep_short_chunks(D, FW * NW) && a.sweep_chunk > 32) return hipErrorInvalidValue;
   if (pgrid.x > 0) {
     if constexpr (CAN_MASK) {
       if (masked) k_fwd_state<T, D, FW, NW, NS, true><<<pgrid, SH::NT, 0, st>>>(a);
@@ -819,6 +820,7 @@ hipError_t launch_fwd(const FwdArgs& a, const KernelShape& ks, bool fmap, hipStr
     if (ks.d == 64 && ks.m == 64) return run_attn_v<__bf16, 64, 16, 4>(a, ns, causal, st);
     if (ks.d == 64 && ks.m == 128) return run_attn_v<__bf16, 64, 16, 8>(a, ns, causal, st);
     if (ks.d == 128 && ks.m == 64) return run_attn_v<__bf16, 128, 16, 4>(a, ns, causal, st);
+    if (ks.d == 128 && ks.m == 128) return run_attn_v<__bf16, 128, 16, 8>(a, ns, causal, st);
   } else {
     if (ks.d == 32 && ks.m == 64) return run_attn_v<float, 32, 16, 4>(a, ns, causal, st);
   }
@@ -857,12 +859,12 @@ size_t wfrag_bytes(const KernelShape& ks, int H) {
 }
 
 // Waves per workgroup of the forward attention kernels of a shape.
-int fwd_state_waves(const KernelShape& ks) { return (ks.bf16 && ks.d == 64 && ks.m == 128) ? 8 : 4; }
+int fwd_state_waves(const KernelShape& ks) { return ks.bf16 && ks.m == 128 ? 8 : 4; }
 
 // Workgroups of the forward state pre-pass that run on one CU at a time, from
 // the waves per SIMD its launch attributes fix.
 int fwd_state_wgs_per_cu(const KernelShape& ks) {
-  const int per_simd = state_waves_per_eu(ks.d, ks.nonstationary);
+  const int per_simd = state_waves_per_eu(ks.d, ks.nonstationary, fwd_state_waves(ks));
   const int wg_per_simd = fwd_state_waves(ks) / 4;
   return per_simd >= wg_per_simd ? per_simd / wg_per_simd : 1;
 }

@@ -91,8 +91,10 @@ struct BwdArgs {
                       // it), the key side's holding both sides' sums in [matrix][m][d]
   float* dtaupart;    // [BH][segments] partial dtau
   void* wfrag;        // per-head frequency fragments (prepared by k_prep_freqs)
-  const float* fstate; // forward segment states ([BH][segments*fsub][state]) or NULL
+  const float* fstate; // forward segment states ([BH][segments*fsub][fstride]) or NULL
   int fsub;           // forward pre-pass workgroups per segment
+  int fstride;        // floats from one of its blocks to the next (more than the state
+                      // of this group where the forward's groups are wider)
   int ffold;          // 1: fstate holds the local states (the forward ran no scan) and
                       // the dQ sweep sums its carry-in from them; 0: the carry-in of
                       // segment p is in slot p*fsub
@@ -178,9 +180,12 @@ size_t bwd_dw_floats(const KernelShape& ks);
 size_t wfrag_bytes(const KernelShape& ks, int H);
 int fwd_state_waves(const KernelShape& ks);
 // Waves per SIMD of the forward state pre-pass (its launch attribute): two,
-// except at d = 128 nonstationary, whose wave holds more than half a SIMD's
-// registers.
-constexpr int state_waves_per_eu(int d, bool ns) { return (d <= 64 || !ns) ? 2 : 1; }
+// except at d = 128 nonstationary with 4 waves, whose wave holds more than half
+// a SIMD's registers.
+constexpr int state_waves_per_eu(int d, bool ns, int waves) { return (d <= 64 || !ns || waves >= 8) ? 2 : 1; }
+// Whether its waves hold their projection fragments for the whole pass, built
+// from W (else they reload prepared ones per chunk).
+constexpr bool state_keeps_frags(int d, int waves) { return d <= 64 || waves >= 8; }
 int fwd_state_wgs_per_cu(const KernelShape& ks);
 // Waves per SIMD the forward sweep is compiled for.
 constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
@@ -190,6 +195,10 @@ constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
 // Waves per SIMD the backward sweeps are compiled for: two, except at d = 128 (one
 // wave's states and dW' partial alone take 136 registers) and on the fp32 path.
 constexpr int bwd_waves_per_eu(bool bf16, int d) { return bf16 && d <= 64 ? 2 : 1; }
+
+// Whether the causal forward sweep of a shape takes chunks of at most 32 tokens:
+// at d = m = 128 the operands of 64 tokens next to the state's do not fit LDS.
+constexpr bool sweep_short_chunks(int d, int m) { return d >= 128 && m > 64; }
 
 // state (or NULL): [BH][P*sub][E]; writes the exclusive prefix (causal) into
 // slot p*sub of every segment p, or the total (non-causal) into slot 0.

@@ -91,6 +91,23 @@ def test_backward_small(F, io, d, m, variant, causal, reuse):
     check_rows(wl, x, got, ref, kap)
 
 
+@pytest.mark.parametrize("N", [33, 65, 97])
+@pytest.mark.parametrize("io,d,m", [("bf16", 32, 64), ("bf16", 64, 64), ("bf16", 64, 128), ("bf16", 128, 128),
+                                    ("f32", 32, 64)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_backward_chunk_edges(F, io, d, m, causal, N):
+    """Sequences that end one token into a 32- or 64-token chunk: the sweeps'
+    intra-chunk tiles and the rows staged a chunk ahead at their edges, with the
+    forward's states (at d = m = 128 those of one wider forward group)."""
+    wl = W.Workload("edges", 2, 2, N, d, m, "nonstationary", causal, io, True, 29)
+    x = W.generate(wl)
+    kap = masked_inputs(wl, x)
+    got = gpu_fwd_bwd(F, wl, x, reuse=True)
+    ref, sc = oracle_bwd(wl, x)
+    check_grads(io, got, ref, names_of(wl), sc)
+    check_rows(wl, x, got, ref, kap)
+
+
 @pytest.mark.parametrize("d,dv", [(64, 32), (128, 64), (128, 32), (32, 64), (64, 128), (32, 128)])
 @pytest.mark.parametrize("variant", ["stationary", "nonstationary"])
 @pytest.mark.parametrize("causal", [False, True])

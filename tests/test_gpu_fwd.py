@@ -91,6 +91,20 @@ def test_forward_small(F, io, d, m, variant, causal):
     check_forward(io, to_f64(O), to_f64(den), O_ref, den_ref, kap, sc)
 
 
+@pytest.mark.parametrize("N", [31, 33, 65])
+@pytest.mark.parametrize("m,chunk", [(128, 0), (128, 16), (256, 0), (256, 64)])
+def test_forward_wide_groups(F, m, chunk, N):
+    """bf16 d = 128 with m a multiple of 128: groups of 128 frequencies, whose
+    causal sweep takes at most 32 tokens per chunk (one group writes O itself,
+    of two the second divides), at the edges of its chunks."""
+    wl, x = small("bf16", 128, m, "nonstationary", True, N=N, seed=41)
+    t = to_device(x)
+    d = desc_of(wl, chunk=chunk)
+    O, den = F.flex_linattn_fwd(d, t["Q"], t["K"], t["V"], t["W1"], t["W2"], t["tau"])
+    O_ref, den_ref, kap, sc = oracle_fwd(x, wl)
+    check_forward("bf16", to_f64(O), to_f64(den), O_ref, den_ref, kap, sc)
+
+
 # (d, d_v) with d_v != d: run at width max(d, d_v) on zero-padded copies
 VALUE_WIDTHS = [(64, 32), (128, 64), (128, 32), (32, 64), (64, 128), (32, 128)]
 
