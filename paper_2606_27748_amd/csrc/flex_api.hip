@@ -110,9 +110,11 @@ KernelShape kshape(const flex_desc* d) {
 }
 
 // Frequency groups of the attention kernels.  The kernels cover (d, m) =
-// (32, 64), (64, 64), (64, 128) (bf16) and (128, 64) in one launch per pass;
-// every other shape runs as groups of 128 frequencies (bf16 d = 64, m a
-// multiple of 128) or of 64 (at d = 128, m = 256 the per-workgroup state and
+// (32, 64), (32, 128), (64, 64), (64, 128) (bf16) and (128, 64) in one launch per
+// pass; every other shape runs as groups of 128 frequencies (bf16 d <= 64, m a
+// multiple of 128; us per training step at d = 32, m = 128 with two groups of 64
+// and with one of 128: B*H = 64, N = 2000 causal 248 and 167, non-causal 155 and
+// 104, B*H = 8, N = 1000 81 and 56) or of 64 (at d = 128, m = 256 the per-workgroup state and
 // frequency-gradient partials of one group fit registers and LDS, all 256
 // frequencies would not).  When 64 does not divide m, the first group holds
 // the first `last` frequencies and zero rows after them, whose features the
@@ -124,7 +126,7 @@ struct Groups {
   int n, m, last;
 };
 Groups groups_of(const flex_desc* d) {
-  if (d->d == 64 && d->m % 128 == 0 && d->io_dtype == FLEX_BF16) return Groups{d->m / 128, 128, 128};
+  if (d->d <= 64 && d->m % 128 == 0 && d->io_dtype == FLEX_BF16) return Groups{d->m / 128, 128, 128};
   const int n = (d->m + 63) / 64;
   return Groups{n, 64, d->m - 64 * (n - 1)};
 }
@@ -343,9 +345,10 @@ size_t fwd_acc_bytes(const flex_desc* d) {
   return align256(rows * d->dv * sizeof(float)) + align256(rows * sizeof(float));
 }
 
+// Prepared fragments: for the d = 128 pre-pass only (the others build theirs from W).
+size_t fwd_wfrag_bytes(const flex_desc* d) { return d->d <= 64 ? 0 : align256(wfrag_bytes(attn_shape(d), d->H)); }
 size_t fwd_ws_bytes(const flex_desc* d, int P) {
-  return fwd_groups_of(d).n * fwd_group_state_bytes(d, P) + align256(wfrag_bytes(attn_shape(d), d->H)) + fwd_acc_bytes(d) +
-         pad_bytes(d);
+  return fwd_groups_of(d).n * fwd_group_state_bytes(d, P) + fwd_wfrag_bytes(d) + fwd_acc_bytes(d) + pad_bytes(d);
 }
 
 // dv != d: the attention runs at width w = max(d, dv) on zero-padded
@@ -550,7 +553,7 @@ int32_t run_fwd(const flex_desc* desc, const void* Q, const void* K, const void*
   const size_t sb = fwd_group_state_bytes(desc);
   a.wfrag = base + G.n * sb;
   if (G.n > 1) {
-    char* acc = base + G.n * sb + align256(wfrag_bytes(attn_shape(desc), desc->H));
+    char* acc = base + G.n * sb + fwd_wfrag_bytes(desc);
     a.acc_num = reinterpret_cast<float*>(acc);
     a.acc_den = reinterpret_cast<float*>(acc + align256((size_t)desc->B * desc->H * desc->N * desc->dv * sizeof(float)));
   }

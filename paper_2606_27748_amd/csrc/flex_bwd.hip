@@ -910,6 +910,7 @@ static hipError_t run_bwd_v(const BwdArgs& a, bool ns, bool causal, hipStream_t 
 hipError_t launch_bwd(const BwdArgs& a, const KernelShape& ks, hipStream_t st) {
   if (ks.bf16) {
     if (ks.d == 32 && ks.m == 64) return run_bwd_v<__bf16, 32, 16, 4>(a, ks.nonstationary, ks.causal, st);
+    if (ks.d == 32 && ks.m == 128) return run_bwd_v<__bf16, 32, 16, 8>(a, ks.nonstationary, ks.causal, st);
     if (ks.d == 64 && ks.m == 64) return run_bwd_v<__bf16, 64, 16, 4>(a, ks.nonstationary, ks.causal, st);
     if (ks.d == 64 && ks.m == 128) return run_bwd_v<__bf16, 64, 16, 8>(a, ks.nonstationary, ks.causal, st);
     if (ks.d == 128 && ks.m == 64) return run_bwd_v<__bf16, 128, 16, 4>(a, ks.nonstationary, ks.causal, st);

@@ -36,7 +36,7 @@ void k_bwd_dq(BwdArgs a) {
   constexpr int HALVES = 2 * SH::CH * D * (int)sizeof(IO) / 16 <= SH::NT ? 2 : 1;
   constexpr int NTH = SH::NT / HALVES;
   typedef RowStage<IO, D, NTH, SH::CH> StX;
-  static_assert(D == SH::DV && StX::NV % NTH == 0, "one stage type, the same row vectors per thread");
+  static_assert(D == SH::DV && (StX::NV % NTH == 0 || StX::NV < NTH), "one stage type, the same row vectors per thread");
   typedef WTSlice<T, D, FW, NS> WTS;
   constexpr int DT = D / 16;
   constexpr int KG = (SH::DVT1 + 1) / 2;        // k-steps over [dO | -delta]
@@ -225,7 +225,7 @@ void k_bwd_dq(BwdArgs a) {
           dsum = lane_sum<StX::VPR>(dsum);
           const float rcp = 1.0f / dn_next[k];
           const float inv = tn + t < a.N ? rcp : 0.f;
-          if (v % StX::VPR == 0) {
+          if (v < StX::NV && v % StX::VPR == 0) {
             put_delta(par, t, inv, dsum);
             gb.store_f2(t * 8, make_float2(inv, dsum));
           }
@@ -505,6 +505,7 @@ hipError_t launch_bwd_dq(const BwdArgs& a, bool causal, bool grouped_acc, bool w
   template hipError_t launch_bwd_dq<T, D, FW, NW, true>(const BwdArgs&, bool, bool, bool, bool, hipStream_t); \
   template hipError_t launch_bwd_dq<T, D, FW, NW, false>(const BwdArgs&, bool, bool, bool, bool, hipStream_t);
 FLEX_DQ_SHAPE(__bf16, 32, 16, 4)
+FLEX_DQ_SHAPE(__bf16, 32, 16, 8)
 FLEX_DQ_SHAPE(__bf16, 64, 16, 4)
 FLEX_DQ_SHAPE(__bf16, 64, 16, 8)
 FLEX_DQ_SHAPE(__bf16, 128, 16, 4)

@@ -817,6 +817,7 @@ hipError_t launch_fwd(const FwdArgs& a, const KernelShape& ks, bool fmap, hipStr
   }
   if (ks.bf16) {
     if (ks.d == 32 && ks.m == 64) return run_attn_v<__bf16, 32, 16, 4>(a, ns, causal, st);
+    if (ks.d == 32 && ks.m == 128) return run_attn_v<__bf16, 32, 16, 8>(a, ns, causal, st);
     if (ks.d == 64 && ks.m == 64) return run_attn_v<__bf16, 64, 16, 4>(a, ns, causal, st);
     if (ks.d == 64 && ks.m == 128) return run_attn_v<__bf16, 64, 16, 8>(a, ns, causal, st);
     if (ks.d == 128 && ks.m == 64) return run_attn_v<__bf16, 128, 16, 4>(a, ns, causal, st);
@@ -849,6 +850,7 @@ size_t wfrag_bytes(const KernelShape& ks, int H) {
   const bool ns = ks.nonstationary;
   if (ks.bf16) {
     if (ks.d == 32 && ks.m == 64) return ns ? wfrag_bytes_t<__bf16, 32, 16, true>(H, 4) : wfrag_bytes_t<__bf16, 32, 16, false>(H, 4);
+    if (ks.d == 32 && ks.m == 128) return ns ? wfrag_bytes_t<__bf16, 32, 16, true>(H, 8) : wfrag_bytes_t<__bf16, 32, 16, false>(H, 8);
     if (ks.d == 64 && ks.m == 64) return ns ? wfrag_bytes_t<__bf16, 64, 16, true>(H, 4) : wfrag_bytes_t<__bf16, 64, 16, false>(H, 4);
     if (ks.d == 64 && ks.m == 128) return ns ? wfrag_bytes_t<__bf16, 64, 16, true>(H, 8) : wfrag_bytes_t<__bf16, 64, 16, false>(H, 8);
     if (ks.d == 128 && ks.m == 64) return ns ? wfrag_bytes_t<__bf16, 128, 16, true>(H, 4) : wfrag_bytes_t<__bf16, 128, 16, false>(H, 4);
