@@ -111,14 +111,17 @@ KernelShape kshape(const flex_desc* d) {
 
 // Frequency groups of the attention kernels.  The kernels cover (d, m) =
 // (32, 64), (32, 128), (64, 64), (64, 128) (bf16) and (128, 64) in one launch per
-// pass; every other shape runs as groups of 128 frequencies (bf16 d <= 64, m a
-// multiple of 128; us per training step at d = 32, m = 128 with two groups of 64
-// and with one of 128: B*H = 64, N = 2000 causal 248 and 167, non-causal 155 and
-// 104, B*H = 8, N = 1000 81 and 56) or of 64 (at d = 128, m = 256 the per-workgroup state and
-// frequency-gradient partials of one group fit registers and LDS, all 256
-// frequencies would not).  When 64 does not divide m, the first group holds
-// the first `last` frequencies and zero rows after them, whose features the
-// kernels mask to zero (it runs first, so only write variants need masking).
+// pass; every other shape runs as groups of 128 frequencies or of 64.
+// Of 128: bf16 d <= 64 with m a multiple of 128, or more than 64 above one.  us
+// per training step at d = 32, m = 128 with two groups of 64 and with one of 128:
+// B*H = 64, N = 2000 causal 248 and 167, non-causal 155 and 104, B*H = 8, N = 1000
+// 81 and 56; m = 80 (one group of 128 with 48 padding rows, against two of 64 with
+// as many): B*H = 64, N = 2000 causal d = 64 386 and 230, d = 32 260 and 182.
+// Of 64: the others (at d = 128 the backward's states and frequency-gradient
+// partials of 64 fit registers and LDS, those of 128 would not).
+// When the width does not divide m, the first group holds the first `last`
+// frequencies and zero rows after them, whose features the kernels mask to
+// zero (it runs first, so only write variants need masking).
 // The groups' contributions to the numerator, denominator and the Q/K/V/tau
 // gradients are summed in launch order; the frequency gradients of a group
 // are its own rows.
@@ -126,7 +129,10 @@ struct Groups {
   int n, m, last;
 };
 Groups groups_of(const flex_desc* d) {
-  if (d->d <= 64 && d->m % 128 == 0 && d->io_dtype == FLEX_BF16) return Groups{d->m / 128, 128, 128};
+  if (d->d <= 64 && d->io_dtype == FLEX_BF16 && (d->m % 128 == 0 || d->m % 128 > 64)) {
+    const int n128 = (d->m + 127) / 128;
+    return Groups{n128, 128, d->m - 128 * (n128 - 1)};
+  }
   const int n = (d->m + 63) / 64;
   return Groups{n, 64, d->m - 64 * (n - 1)};
 }

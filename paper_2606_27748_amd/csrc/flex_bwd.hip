@@ -835,10 +835,10 @@ static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
   // pre-pass's query-side work itself and no pre-pass runs; the R' local
   // states it leaves feed the scan, or the dK/dV sweep's own suffix sum.
   const bool wr = a.fstate != nullptr;
-  // a padded frequency group (only the 64-frequency shape has one, and it runs
-  // first, so it never adds) takes the masking kernel variants
+  // a padded frequency group (it runs first, so it never adds) takes the
+  // masking kernel variants
   const bool masked = a.fvalid < SH::M;
-  constexpr bool CAN_MASK = SH::M == 64;
+  constexpr bool CAN_MASK = group_can_pad(D, SH::M);
   if (masked && (!CAN_MASK || a.acc)) return hipErrorInvalidValue;
   auto scan_r = [&]() -> hipError_t {
     if (a.rfold) return hipSuccess;

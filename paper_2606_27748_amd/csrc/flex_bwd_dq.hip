@@ -485,8 +485,8 @@ template <class T, int D, int FW, int NW, bool NS>
 hipError_t launch_bwd_dq(const BwdArgs& a, bool causal, bool grouped_acc, bool wr, bool masked, hipStream_t st) {
   typedef Shape<T, D, FW, NW, NS, BWD_CHUNK> SA;
   const dim3 grid(a.segments * a.BH);
-  if (masked) {   // a padded group: the 64-frequency shape, never adding
-    if constexpr (FW * NW == 64) {
+  if (masked) {   // a padded group: never adding
+    if constexpr (group_can_pad(D, FW * NW)) {
       if (!grouped_acc) {
         launch_dq_acc<T, D, FW, NW, NS, false, true>(a, causal, wr, grid, SA::NT, st);
         return hipGetLastError();

@@ -748,10 +748,10 @@ static hipError_t run_fwd_t(const FwdArgs& a, bool causal, hipStream_t st) {
   // chunk; the other forward kernels build theirs from W once
   if (!state_keeps_frags(D, NW)) k_prep_freqs<T, D, FW, NW, NS><<<dim3(a.H, NW, 1), WAVE, 0, st>>>(a.W1, a.W2, a.wfrag, a.w_stride);
   timing_mark(KC_FWD_STATE, st, true);
-  // a padded frequency group (only the 64-frequency shape has one, and it
-  // runs first, so it never adds) takes the masking kernel variants
+  // a padded frequency group (it runs first, so it never adds) takes the
+  // masking kernel variants
   const bool masked = a.fvalid < FW * NW;
-  constexpr bool CAN_MASK = FW * NW == 64;
+  constexpr bool CAN_MASK = group_can_pad(D, FW * NW);
   if (masked && (!CAN_MASK || a.acc >= 2)) return hipErrorInvalidValue;
   if (causal && sweep_short_chunks(D, FW * NW) && a.sweep_chunk > 32) return hipErrorInvalidValue;
   if (pgrid.x > 0) {

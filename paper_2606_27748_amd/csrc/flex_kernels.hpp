@@ -196,6 +196,10 @@ constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
 // wave's states and dW' partial alone take 136 registers) and on the fp32 path.
 constexpr int bwd_waves_per_eu(bool bf16, int d) { return bf16 && d <= 64 ? 2 : 1; }
 
+// Whether a shape's frequency group may be padded (the masking kernel variants
+// are compiled for it).
+constexpr bool group_can_pad(int d, int m) { return m == 64 || (m == 128 && d <= 64); }
+
 // Whether the causal forward sweep of a shape takes chunks of at most 32 tokens:
 // at d = m = 128 the operands of 64 tokens next to the state's do not fit LDS.
 constexpr bool sweep_short_chunks(int d, int m) { return d >= 128 && m > 64; }

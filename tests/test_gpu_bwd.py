@@ -93,7 +93,9 @@ def test_backward_small(F, io, d, m, variant, causal, reuse):
 
 @pytest.mark.parametrize("N", [33, 65, 97])
 @pytest.mark.parametrize("io,d,m", [("bf16", 32, 64), ("bf16", 32, 128), ("bf16", 64, 64), ("bf16", 64, 128),
-                                    ("bf16", 128, 128), ("f32", 32, 64)])
+                                    ("bf16", 128, 128), ("f32", 32, 64),
+                                    # one padded group of 128; a padded and a whole one
+                                    ("bf16", 32, 112), ("bf16", 64, 80), ("bf16", 64, 208)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_backward_chunk_edges(F, io, d, m, causal, N):
     """Sequences that end one token into a 32- or 64-token chunk: the sweeps'

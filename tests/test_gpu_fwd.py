@@ -91,6 +91,19 @@ def test_forward_small(F, io, d, m, variant, causal):
     check_forward(io, to_f64(O), to_f64(den), O_ref, den_ref, kap, sc)
 
 
+@pytest.mark.parametrize("d,m", [(32, 80), (32, 112), (64, 80), (64, 112), (64, 208)])
+@pytest.mark.parametrize("variant", ["stationary", "nonstationary"])
+@pytest.mark.parametrize("causal", [False, True])
+def test_forward_padded_wide_group(F, d, m, variant, causal):
+    """bf16 d <= 64 with m more than 64 above a multiple of 128: the first group
+    of 128 frequencies is padded."""
+    wl, x = small("bf16", d, m, variant, causal, N=97, seed=43)
+    t = to_device(x)
+    O, den = F.flex_linattn_fwd(desc_of(wl), t["Q"], t["K"], t["V"], t["W1"], t["W2"], t["tau"])
+    O_ref, den_ref, kap, sc = oracle_fwd(x, wl)
+    check_forward("bf16", to_f64(O), to_f64(den), O_ref, den_ref, kap, sc)
+
+
 @pytest.mark.parametrize("N", [31, 33, 65])
 @pytest.mark.parametrize("m,chunk", [(128, 0), (128, 16), (256, 0), (256, 64)])
 def test_forward_wide_groups(F, m, chunk, N):
