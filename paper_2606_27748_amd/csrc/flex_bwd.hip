@@ -18,8 +18,9 @@
 //   k_bwd_dkv     : descending chunk sweep carrying R'; dK, dV, the key-side
 //                   frequency-gradient partials and dtau partials,
 //   k_bwd_reduce  : fixed-order sums of the partials into dW1, dW2, dtau.
-// Waves split the frequencies as in the forward.  Both states are held as
-// accumulator tiles with value columns as rows ([dv' x features]).
+// Waves split the frequencies in the work on features and states, and the output
+// tiles in the products over all features.  Both states are held as accumulator
+// tiles with value columns as rows ([dv' x features]).
 #include "flex_bwd_common.hpp"
 
 namespace flex {
@@ -257,7 +258,8 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
 // pass before (dV partials of every wave summed through LDS, dW' there too, 4
 // waves of 32 frequencies at m = 128) and after: training step d = 64, m = 128
 // (B*H = 32, N = 8192) 469 and 424, d = 128, m = 256 2561 and 2439, encoder
-// training (non-causal m = 64, B*H = 64, N = 4000) 253 and 232.
+// training (non-causal m = 64, B*H = 64, N = 4000) 253 and 232, then 209 with two
+// workgroups per CU.  (A as hi + lo costs 3 of these us at m = 128.)
 // ---------------------------------------------------------------------------
 // ACC: add dK and dV to the values an earlier frequency group stored.  The
 // old values are loaded ahead of the next chunk's prefetch, so waiting for

@@ -1,42 +1,12 @@
 // Device helpers shared by the backward kernels (flex_bwd.hip, flex_bwd_dq.hip):
-// feature fragments with their P2-derivative, the normaliser rows of the
-// backward states, per-token scalars, state tile layouts, the feature-map
-// chain rule and the frequency-gradient partials.
+// the normaliser rows of the backward states, per-token scalars, state tile
+// layouts and the frequency-gradient partials.
 #pragma once
 #include "flex_common.hpp"
 #include "flex_kernels.hpp"
 #include "flex_stage.hpp"
 
 namespace flex {
-
-// Feature fragment (as in the forward) plus, for the nonstationary variant,
-// the fragment of d phi / d P2 up to sign: slots [s e sin P2 cos P1 | s e sin P2 sin P1].
-// fv: as in features (slice frequencies >= fv give zero fragments).
-template <class T, int FT, bool NS, class P>
-__device__ __forceinline__ void features_psi(const P (&p)[NS ? 2 * FT : FT], int ft, float scale,
-                                             Frag<T>& phi, Frag<T>& psi, int fv = FT * 16) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float s1, c1;
-    sincos_rev(p[ft][i], s1, c1);
-    if (NS) {
-      float s2, c2;
-      sincos_rev(p[FT + ft][i], s2, c2);
-      const float sc = scale * c2, ss = scale * s2;
-      phi.set(i, c1 * sc);
-      phi.set(4 + i, s1 * sc);
-      psi.set(i, c1 * ss);
-      psi.set(4 + i, s1 * ss);
-    } else {
-      phi.set(i, c1 * scale);
-      phi.set(4 + i, s1 * scale);
-    }
-  }
-  if (fv < FT * 16) {
-    mask_features(phi, ft, fv);
-    if (NS) mask_features(psi, ft, fv);
-  }
-}
 
 // -x as a two-term operand split (hi, lo): exact to about 16 bits on the bf16
 // path.  The backward states carry the normaliser products in two rows of the
@@ -114,24 +84,8 @@ __device__ __forceinline__ f32x4 fwd_state_tile_t(const float* blk, int w, int d
   return v;
 }
 
-// Chain rule through one wave's features for frequency tile ft, token tile tt:
-// dP (per radian) for the projection rows, and <phi, dphi> summed over this
-// lane's slots.
-template <class T, int FT, bool NS>
-__device__ __forceinline__ float feature_grad(const Frag<T>& phi, const Frag<T>& psi,
-                                              const f32x4& da, const f32x4& db, f32x4& dp1, f32x4& dp2) {
-  float gsum = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float a = phi.get(i), b = phi.get(4 + i);
-    dp1[i] = a * db[i] - b * da[i];
-    if (NS) dp2[i] = -(psi.get(i) * da[i] + psi.get(4 + i) * db[i]);
-    gsum += a * da[i] + b * db[i];
-  }
-  return gsum;
-}
-
-// The per-wave frequency-gradient partial dW'[rows][d] lives in LDS in
+// The dQ sweep's per-wave frequency-gradient partial dW'[rows][d], where registers
+// do not hold it, lives in LDS in
 // register-dump order (tile, lane, 4 floats).  Each chunk's product for
 // projection-row tile pr is formed with the LDS tiles as the MFMA's
 // accumulator input (one 16-byte read and write per lane and tile), so the

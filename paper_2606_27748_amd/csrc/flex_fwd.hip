@@ -170,7 +170,8 @@ __global__ __launch_bounds__(256) void k_state_scan(float* state0, float* state1
 // before (4 waves of 32 frequencies, partials reduced through LDS) and after:
 // d = 64, m = 128 nonstationary, B*H = 32, N = 8192: 97 and 81; stationary,
 // B*H = 96, N = 1024: 44 and 39; d = 128, m = 256 (four groups, and the last
-// one divides, where a pass of its own took 35): 620 and 559.
+// one divides, where a pass of its own took 35): 620 and 559, and 300 as two
+// groups of 128 frequencies with 8 waves.
 // ---------------------------------------------------------------------------
 // ADD: add this frequency group's numerator and denominator to the sums the
 // earlier groups stored; the old sums are loaded at the start of each chunk,

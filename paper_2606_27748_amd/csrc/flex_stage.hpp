@@ -144,21 +144,6 @@ struct RowStage {
       if (mine(v) && v % VPR == 0) out[v / VPR] = f(i, v / VPR, s);
     }
   }
-  // transposed store: ldsT[col][token] with row stride LDT (operand type T)
-  template <class T, int LDT>
-  __device__ __forceinline__ void store_t(T* ldsT) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int v = tid() + i * NT;
-      if (mine(v)) {
-        const int t = v / VPR, c = v % VPR;
-        const uint4 x = vec(i);
-        const IO* e = reinterpret_cast<const IO*>(&x);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) ldsT[(c * VEC + j) * LDT + t] = io_to_op<T>(e[j]);
-      }
-    }
-  }
 };
 
 // Operand fragment of 8 consecutive columns [c0, c0+8) of LDS row `row`.
