@@ -397,7 +397,7 @@ void k_fwd_sweep(FwdArgs a) {
           }
         }
 #pragma unroll
-        for (int ks = 0; ks < KT; ++ks) split_pair<T>(at[2 * ks], at[2 * ks + 1], ap[ks], al[ks]);
+        for (int ks = 0; ks < KT; ++ks) split_pair_low<T>(at[2 * ks], at[2 * ks + 1], ap[ks], al[ks]);
       }
       f32x4 acc[NDT], zn = zero4();
 #pragma unroll

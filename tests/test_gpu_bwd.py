@@ -265,6 +265,29 @@ def test_backward_single_token(F, causal):
             assert np.linalg.norm(gh) <= TOL["bf16"] * scale[h], (n, h, np.linalg.norm(gh), scale[h])
 
 
+@pytest.mark.parametrize("io,d,m", [("bf16", 32, 64), ("bf16", 64, 128), ("bf16", 128, 64), ("f32", 32, 64)])
+@pytest.mark.parametrize("reuse", [False, True])
+def test_backward_overflowing_kernel_values(F, io, d, m, reuse):
+    """Features finite, phi(Q_i)/den_i . phi(K_j) beyond fp32 (den = 1 given):
+    with all rows alike and dO > 0 every dV is a positive infinity (the
+    intra-chunk matrix enters as a high and a low part, and an infinity has no
+    remainder to add)."""
+    import torch
+    wl = W.Workload("overflow", 1, 2, 70, d, m, "stationary", True, io, True, 23)
+    t = to_device(W.generate(wl))
+    desc = desc_of(wl)
+    row = t["Q"][:, :, :1].float()
+    row = (row * (60.0 / row.square().sum(-1, keepdim=True)).sqrt()).to(t["Q"].dtype)   # |row|^2 = 60, exp(tau) = 1
+    Q = row.expand_as(t["Q"]).contiguous()
+    tau = t["tau"].new_zeros(wl.H)
+    V, dO = t["V"].abs() + 1, t["dO"].abs() + 1
+    ws = torch.empty(F.workspace_size(desc, F.FLEX_PASS_FWD) + 256, dtype=torch.uint8, device=Q.device)
+    O, den = F.flex_linattn_fwd(desc, Q, Q, V, t["W1"], None, tau, ws=ws)
+    g = F.flex_linattn_bwd(desc, Q, Q, V, t["W1"], None, tau, torch.ones_like(O), torch.ones_like(den), dO,
+                           fwd_ws=ws if reuse else None)
+    assert np.all(np.isposinf(to_f64(g["dV"])))
+
+
 def test_backward_deterministic(F):
     import torch
     wl = W.Workload("det", 2, 2, 300, 64, 128, "nonstationary", True, "bf16", True, 27)

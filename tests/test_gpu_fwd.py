@@ -223,6 +223,23 @@ def test_forward_deterministic_and_den_optional(F):
     assert torch.equal(O1.view(torch.int16), O3.view(torch.int16))
 
 
+@pytest.mark.parametrize("io,d,m", [("bf16", 32, 64), ("bf16", 64, 128), ("bf16", 128, 128), ("f32", 32, 64)])
+def test_forward_overflowing_kernel_values(F, io, d, m):
+    """Rows long enough that phi is finite but every phi(Q_i).phi(K_j) overflows
+    fp32: with all rows alike each product is a positive infinity, and so is
+    den (the intra-chunk matrix enters the bf16 readout as a high and a low
+    part, and an infinity has no remainder to add)."""
+    wl, x = small(io, d, m, "stationary", True, B=1, H=2, N=70, seed=23)
+    t = to_device(x)
+    row = t["Q"][:, :, :1].float()
+    row = (row * (60.0 / row.square().sum(-1, keepdim=True)).sqrt()).to(t["Q"].dtype)   # |row|^2 = 60, exp(tau) = 1
+    Q = row.expand_as(t["Q"]).contiguous()
+    tau = t["tau"].new_zeros(wl.H)
+    V = t["V"].abs() + 1
+    _, den = F.flex_linattn_fwd(desc_of(wl), Q, Q, V, t["W1"], None, tau)
+    assert np.all(np.isposinf(to_f64(den)))
+
+
 def test_forward_sigma_invariance(F):
     """O does not depend on sigma (it scales phi); den scales by sigma^2."""
     wl, x = small("f32", 32, 64, "stationary", True, N=150)
