@@ -632,10 +632,12 @@ void k_bwd_dkv(BwdArgs a) {
 #pragma unroll
       for (int k = 0; k < NOT; ++k) {
         const int ot = w + k * NW;
-        if (DT * SH::TT % NW == 0 || ot < DT * SH::TT)
-          mma(dv[k], lds_tr_frag<T>(RL[ft / SH::FT], RLP, (2 * (ft % SH::FT)) * 16 + 4 * g, (2 * (ft % SH::FT) + 1) * 16 + 4 * g,
-                                    ot % DT * 16),
-              PK[ot / DT][ft][l]);
+        if (DT * SH::TT % NW == 0 || ot < DT * SH::TT) {
+          const Frag<T> rt = lds_tr_frag<T>(RL[ft / SH::FT], RLP, (2 * (ft % SH::FT)) * 16 + 4 * g,
+                                            (2 * (ft % SH::FT) + 1) * 16 + 4 * g, ot % DT * 16);
+          if constexpr (CAUSAL) mma_tree(dv[k], rt, PK[ot / DT][ft][l]);
+          else mma(dv[k], rt, PK[ot / DT][ft][l]);
+        }
       }
     // chain rule through phi(K): with t = cos P1 da + sin P1 db and
     // u = cos P1 db - sin P1 da, dP1 = s e cos P2 u, dP2 = -s e sin P2 t and
@@ -685,7 +687,7 @@ void k_bwd_dkv(BwdArgs a) {
       if (CAUSAL) {
         const Frag<T> gt = lds_tr_frag<T>(reinterpret_cast<const T*>(XDO), StV::LD, 4 * g, 16 + 4 * g, dt * 16);
 #pragma unroll
-        for (int p = 0; p < NSA; ++p) mma(dv[k], gt, AP[p][tt][l]);
+        for (int p = 0; p < NSA; ++p) mma_tree(dv[k], gt, AP[p][tt][l]);
       }
 #pragma unroll
       for (int ww = 0; ww < NW; ++ww)

@@ -288,6 +288,33 @@ def test_backward_overflowing_kernel_values(F, io, d, m, reuse):
     assert np.all(np.isposinf(to_f64(g["dV"])))
 
 
+@pytest.mark.parametrize("variant,tol_O", [("stationary", 1.18e-7), ("nonstationary", 1.09e-7)])
+def test_f32_causal_rounding(F, variant, tol_O):
+    """fp32 causal on a layer's inputs (phases of about a radian, positive row
+    sums): the rounding of O and dV stays that of sums kept per frequency slice.
+    Error against float64 on these inputs with such sums, and with one chain of
+    products per k-step over all features: stationary O 1.10e-7 and 1.27e-7, dV
+    1.29e-7 and 1.51e-7, nonstationary O 0.97e-7 and 1.16e-7, dV 1.26e-7 and
+    1.48e-7; the bounds lie in between."""
+    wl = W.Workload("rounding", 1, 4, 512, 32, 64, variant, True, "f32", True, 71)
+    x = W.generate(wl)
+    rng = np.random.default_rng(72)
+    sc = 32 ** -0.25
+    for k in ("Q", "K", "V", "dO"):
+        setattr(x, k, (rng.standard_normal((1, 4, 512, 32)) * sc).astype(np.float32))
+    x.W1 = (rng.standard_normal((4, 64, 32)) * sc).astype(np.float32)
+    if x.W2 is not None:
+        x.W2 = (rng.standard_normal((4, 64, 32)) * sc).astype(np.float32)
+    x.tau = np.full(4, np.log(2.0), np.float32)
+    t = to_device(x)
+    d = desc_of(wl)
+    O, den = F.flex_linattn_fwd(d, t["Q"], t["K"], t["V"], t["W1"], t["W2"], t["tau"])
+    g = F.flex_linattn_bwd(d, t["Q"], t["K"], t["V"], t["W1"], t["W2"], t["tau"], O, den, t["dO"])
+    ref, _ = oracle_bwd(wl, x)
+    err = {n: np.linalg.norm(to_f64(v) - ref[n]) / np.linalg.norm(ref[n]) for n, v in (("O", O), ("dV", g["dV"]))}
+    assert err["O"] <= tol_O and err["dV"] <= 1.4e-7, err
+
+
 def test_backward_deterministic(F):
     import torch
     wl = W.Workload("det", 2, 2, 300, 64, 128, "nonstationary", True, "bf16", True, 27)
