@@ -465,7 +465,7 @@ void k_bwd_dkv(BwdArgs a) {
     if (lo) {
       T* ol = reinterpret_cast<T*>(&lo[tk * WAVE + l]) + 4 * tq;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) ol[i] = (T)split_low(v[i], (float)hi[i]);
+      for (int i = 0; i < 4; ++i) ol[i] = (T)finite_low(v[i] - (float)hi[i]);
     }
   };
   // Projection fragments, reloaded per chunk (held for the whole sweep they

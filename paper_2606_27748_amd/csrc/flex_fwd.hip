@@ -397,7 +397,7 @@ void k_fwd_sweep(FwdArgs a) {
           }
         }
 #pragma unroll
-        for (int ks = 0; ks < KT; ++ks) split_pair_low<T>(at[2 * ks], at[2 * ks + 1], ap[ks], al[ks]);
+        for (int ks = 0; ks < KT; ++ks) split_pair<T>(at[2 * ks], at[2 * ks + 1], ap[ks], al[ks]);
       }
       // (fp32: the odd frequency tiles in sums of their own, shorter to round)
       constexpr int NSUM = IsBf16<T>::value ? 1 : 2;
@@ -410,6 +410,7 @@ void k_fwd_sweep(FwdArgs a) {
       }
       f32x4 (&acc)[NDT] = accs[0];
       f32x4& zn = zns[0];
+      f32x4 zl = zero4();   // den's share of the low operand
       auto intra = [&]() {
 #pragma unroll
         for (int ks = 0; ks < KT; ++ks)
@@ -420,7 +421,7 @@ void k_fwd_sweep(FwdArgs a) {
               if (IsBf16<T>::value) mma(acc[k], vf[k][ks], al[ks]);
             }
             mma_tree(zn, ones, ap[ks]);
-            if (IsBf16<T>::value) mma(zn, ones, al[ks]);
+            if (IsBf16<T>::value) mma(zl, ones, al[ks]);
           }
       };
       // fp32: the intra-chunk share first, while the sums are small (den's error
@@ -444,6 +445,7 @@ void k_fwd_sweep(FwdArgs a) {
       // acc[k]: rows = value columns, column = token r; every row of the
       // normaliser tile holds den of token r
       float dn = zn[0];
+      if (CAUSAL && IsBf16<T>::value) dn += finite_low(zl[0]);
       if (ADD) dn += old_d;
       if (ADD ? a.acc == 2 : a.acc != 0) {
         // one frequency group's share of the numerator and denominator

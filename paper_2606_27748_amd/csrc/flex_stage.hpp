@@ -287,24 +287,12 @@ __device__ __forceinline__ void split_pair(const f32x4& a, const f32x4& b, Frag<
   }
 }
 
-// The remainder x - hi of an intra-chunk kernel value x and its operand-type
-// rounding hi.  Where x overflows that type, hi is infinite and the remainder
-// infinite or NaN: one med3 keeps it finite (a NaN gives the lower limit), so
-// that the sum of the two products stays infinite, as with hi alone.  A finite
-// remainder is at most 2^-9 |x| < 7e35, below the limits.
-__device__ __forceinline__ float split_low(float x, float hi) { return __builtin_amdgcn_fmed3f(x - hi, -1e36f, 1e36f); }
-
-// split_pair with split_low
-template <class T>
-__device__ __forceinline__ void split_pair_low(const f32x4& a, const f32x4& b, Frag<T>& hi, Frag<T>& lo) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    hi.set(i, a[i]);
-    hi.set(4 + i, b[i]);
-    lo.set(i, split_low(a[i], hi.get(i)));
-    lo.set(4 + i, split_low(b[i], hi.get(4 + i)));
-  }
-}
+// A low part x - hi, or a sum of low parts, as it is added to the high one: where x
+// overflows the operand type, hi is infinite and the low part infinite or NaN, and
+// one med3 makes it finite (a NaN gives the lower limit), so that the sum stays
+// infinite, as with hi alone.  The low part of a finite x is at most 2^-9 |x|, and
+// sums of a chunk's stay below the limits unless x overflows.
+__device__ __forceinline__ float finite_low(float lo) { return __builtin_amdgcn_fmed3f(lo, -1e37f, 1e37f); }
 
 // Projection of one 16-token tile with the tokens as rows: p[pr] holds rows =
 // tokens tt*16 + 4g + i and cols = frequency (lane % 16) of projection tile
