@@ -213,7 +213,16 @@ void k_fwd_sweep(FwdArgs a) {
   __shared__ __attribute__((aligned(16))) T PT[NW][PT_N];
   __shared__ Frag<T> PQ[TT][NFT][WAVE];        // phi(Q), operand fragments
   __shared__ Frag<T> SB[SH::DVT][NFT][WAVE];   // state, operand fragments (rows = value columns)
-  __shared__ Frag<T> SZ[NFT][4];               // normaliser rows of the state, all columns alike
+  // normaliser rows of the state, all columns alike.  Where the chunks are cut short
+  // more of a row's keys reach den through this operand than through the
+  // intra-chunk matrix, and rounded once it carries more error than in chunks of
+  // 64 (up to 2.5 % at N = 512).  There the cos features, whose sums are large, have a
+  // low part too, which the waves that write den take in.  Error of den against
+  // float64 at d = 128, m = 256, N = 8192 with and without 1.24e-4 and 1.73e-4, m =
+  // 128, N = 1000 2.15e-4 and 2.78e-4; us per forward 420 and 405, 95 and 91 (with
+  // both parts of the features in every wave 461 and 101).
+  constexpr int NSZ = CAUSAL && IsBf16<T>::value && sweep_short_chunks(D, SH::M) ? 2 : 1;
+  __shared__ Frag<T> SZ[NSZ][NFT][4];
 
   // causal: one workgroup per segment; non-causal: per group of chunks (every
   // chunk reads the same total state)
@@ -289,8 +298,17 @@ void k_fwd_sweep(FwdArgs a) {
 #pragma unroll
       for (int dt = 0; dt < SH::DVT; ++dt)
         SB[dt][w * SH::FT + ft][l] = pair_tiles<T>(S[2 * ft][dt], S[2 * ft + 1][dt]);
-      const Frag<T> z = pair_tiles<T>(S[2 * ft][SH::DVT], S[2 * ft + 1][SH::DVT]);
-      if (r == 0) SZ[w * SH::FT + ft][g] = z;
+      Frag<T> z[2];   // high part; low part of the cos features
+      z[0] = pair_tiles<T>(S[2 * ft][SH::DVT], S[2 * ft + 1][SH::DVT]);
+      if constexpr (NSZ == 2) {
+        z[1].zero();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z[1].set(i, S[2 * ft][SH::DVT][i] - z[0].get(i));
+      }
+      if (r == 0) {
+        SZ[0][w * SH::FT + ft][g] = z[0];
+        if (NSZ == 2) SZ[NSZ - 1][w * SH::FT + ft][g] = z[1];
+      }
     }
   };
   if (!CAUSAL) store_state();   // ordered by the first staging barrier
@@ -410,7 +428,7 @@ void k_fwd_sweep(FwdArgs a) {
       }
       f32x4 (&acc)[NDT] = accs[0];
       f32x4& zn = zns[0];
-      f32x4 zl = zero4();   // den's share of the low operand
+      f32x4 zl = zero4();   // den's share of the low operands
       auto intra = [&]() {
 #pragma unroll
         for (int ks = 0; ks < KT; ++ks)
@@ -434,12 +452,16 @@ void k_fwd_sweep(FwdArgs a) {
 #pragma unroll
         for (int k = 0; k < NDT; ++k)
           if (SH::DVT % NDT == 0 || part * NDT + k < SH::DVT) mma(accs[ft % NSUM][k], SB[part * NDT + k][ft][l], pq[ft]);
-        mma(zns[ft % NSUM], SZ[ft][g], pq[ft]);
+        mma(zns[ft % NSUM], SZ[0][ft][g], pq[ft]);
       }
       if constexpr (NSUM == 2) {
 #pragma unroll
         for (int k = 0; k < NDT; ++k) acc[k] += accs[1][k];
         zn += zns[1];
+      }
+      if (NSZ == 2 && part == 0) {
+#pragma unroll
+        for (int ft = 0; ft < NFT; ++ft) mma(zl, SZ[NSZ - 1][ft][g], pq[ft]);
       }
       if (CAUSAL && IsBf16<T>::value) intra();
       // acc[k]: rows = value columns, column = token r; every row of the
