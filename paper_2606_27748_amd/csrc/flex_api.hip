@@ -261,11 +261,21 @@ int fwd_sub_of(const flex_desc* d, int P) {
 // the same bits.  Non-causal, every workgroup reads every state (in the
 // token-split readout every wave does), so it pays only where the launch is
 // what counts: a single state (the scan would change nothing), or at most
-// kFoldChunks chunks in all.  us per call before and after: one fp32 head of 256
-// tokens 18.7 and 15.7; but B*H = 128, N = 16384 with four states 270 and 288.
+// kFoldChunks chunks in all.  us per forward without and with the fold, two to four
+// states: one fp32 head of 256 tokens 18.7 and 15.7; d = 64, m = 128 stationary, 4
+// chunks 14.5 and 12.9, 64 chunks 19.5 and 16.2, 128 chunks 22 and 17; at 512 chunks
+// (B*H = 128, N = 256) it still gains 9, but at 32768 (N = 16384, token-split
+// readout) 270 and 288.
 constexpr int kFoldMax = 4;
 constexpr int kRFoldMax = 8;   // R' suffixes: native-layout reads, cheaper to sum
 constexpr int kFoldChunks = 128;
+// Most bytes of local states that a workgroup of the non-causal dQ sweep sums
+// itself (it reads them with a tile transpose); above, a launch sums them once.
+// The launch is 2.5 us; us per backward that sums in the sweep and with the launch:
+// d = 64, m = 64, N = 256 (160 KB), B*H = 1 26.1 and 25.3; d = 64, m = 128, N = 256 (320
+// KB) 32.7 and 29.4; d = 128, m = 128, N = 256 (288 KB), B*H = 32 101 and 77; but d = 32,
+// m = 64, N = 256 (96 KB) 19.5, and 22.3 with a scan.
+constexpr size_t kDqFoldBytes = 100 << 10;
 bool fold_noncausal(const flex_desc* d) { return (long long)nchunks_of(d) * d->B * d->H <= kFoldChunks; }
 int fwd_fold_of(const flex_desc* d, int P) {
   const long long n = (long long)pre_segs_of(d, P) * fwd_sub_of(d, P);
@@ -699,6 +709,8 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
   a.dw_stride = desc->m * desc->d;
   const PadRows pr = pad_rows_of(desc, base + ws_bytes_of(desc, FLEX_PASS_BWD));
   const int per = fwd_groups_of(desc).m / G.m;
+  const int E = (int)bwd_state_floats(ks), local = a.segments * a.fsub;
+  const bool total_first = fwd_ws && !desc->causal && a.ffold && local > 1 && (size_t)local * E * sizeof(float) > kDqFoldBytes;
   for (int g = 0; g < G.n; ++g) {
     if (!group_rows(desc, G, pr, g, W1, W2, stream, &a.W1, &a.W2, &a.w_stride, &a.fvalid))
       return FLEX_ERR_HIP;
@@ -709,7 +721,17 @@ int32_t run_bwd(const flex_desc* desc, const void* Q, const void* K, const void*
     if (fwd_ws)
       // (a forward group of 128 frequencies holds two backward groups' states in a row)
       a.fstate = reinterpret_cast<const float*>(static_cast<const char*>(fwd_ws) + g / per * fwd_group_state_bytes(desc)) +
-                 (g % per) * bwd_state_floats(ks);
+                 (g % per) * E;
+    if (total_first) {
+      // into the key-side states' place, which the backward does not use with the forward's
+      if (launch_state_sum(a.fstate, local, (int)fwd_state_floats(fwd_shape(desc)), a.sstate, a.segments * E, a.BH, E,
+                           stream) != hipSuccess)
+        return FLEX_ERR_HIP;
+      a.fstate = a.sstate;
+      a.fsub = 1;
+      a.fstride = E;
+      a.ffold = 0;
+    }
     const hipError_t e = launch_bwd(a, ks, stream);
     if (e != hipSuccess) return FLEX_ERR_HIP;
   }

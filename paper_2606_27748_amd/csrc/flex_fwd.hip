@@ -150,6 +150,20 @@ __global__ __launch_bounds__(256) void k_state_scan(float* state0, float* state1
   if (!causal) s[0] = acc;
 }
 
+// Total of the n local states of every slice, in the scan's order, into another
+// array: src blocks of src_stride floats (n of them per slice), dst one block of
+// dst_stride per slice; the first E floats of a block are summed.
+__global__ __launch_bounds__(256) void k_state_sum(const float* src, int n, int src_stride, float* dst, int dst_stride,
+                                                   int E) {
+  const int e4 = blockIdx.x * 256 + threadIdx.x;
+  if (4 * e4 >= E) return;
+  const float* s = src + (size_t)blockIdx.y * n * src_stride + 4 * e4;
+  f32x4 acc = zero4();
+#pragma unroll 4
+  for (int k = 0; k < n; ++k) acc += *reinterpret_cast<const f32x4*>(s + (size_t)k * src_stride);
+  *reinterpret_cast<f32x4*>(dst + (size_t)blockIdx.y * dst_stride + 4 * e4) = acc;
+}
+
 // ---------------------------------------------------------------------------
 // Sweep: carry-in state, then per chunk the readout (and, causal, the
 // intra-chunk term and the state update).  Writes O and den.
@@ -881,6 +895,15 @@ hipError_t launch_state_scan(float* state, float* state_rev, int BH, int P, int 
     k_state_scan<<<sgrid, 256, 0, st>>>(state, state_rev, P, sub, E, causal ? 1 : 0, 0, nread);
   else
     k_state_scan<<<sgrid, 256, 0, st>>>(state_rev, nullptr, P, sub, E, causal ? 1 : 0, 1, P * sub);
+  timing_mark(KC_SCAN, st, false);
+  return hipGetLastError();
+}
+
+hipError_t launch_state_sum(const float* src, int n, int src_stride, float* dst, int dst_stride, int BH, int E,
+                            hipStream_t st) {
+  if (E % 4 != 0 || src_stride % 4 != 0 || dst_stride % 4 != 0) return hipErrorInvalidValue;
+  timing_mark(KC_SCAN, st, true);
+  k_state_sum<<<dim3((E / 4 + 255) / 256, BH), 256, 0, st>>>(src, n, src_stride, dst, dst_stride, E);
   timing_mark(KC_SCAN, st, false);
   return hipGetLastError();
 }

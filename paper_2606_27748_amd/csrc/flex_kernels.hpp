@@ -213,6 +213,10 @@ constexpr bool sweep_short_chunks(int d, int m) { return d >= 128 && m > 64; }
 // and never read); state_rev is read in full.
 hipError_t launch_state_scan(float* state, float* state_rev, int BH, int P, int sub, int E, bool causal,
                              hipStream_t st, int nread);
+// dst[bh * dst_stride + e] = sum over k < n of src[(bh n + k) src_stride + e], e < E,
+// in the scan's order (all three multiples of 4).
+hipError_t launch_state_sum(const float* src, int n, int src_stride, float* dst, int dst_stride, int BH, int E,
+                            hipStream_t st);
 hipError_t launch_fwd(const FwdArgs& a, const KernelShape& ks, bool feature_map_only, hipStream_t st);
 // dst[h][rows][d] = the first rows_valid rows of src[h] (src_stride elements
 // apart per head), zero after them: the frequency rows of a padded group.

@@ -240,6 +240,24 @@ def test_backward_reuse_matches_recompute(F, d, m):
         assert np.linalg.norm(a[k] - b[k]) <= 1e-3 * np.linalg.norm(a[k]), k
 
 
+@pytest.mark.parametrize("N", [64, 128, 192, 256])
+@pytest.mark.parametrize("io,d,m", [("bf16", 32, 64), ("bf16", 64, 64), ("bf16", 64, 128), ("bf16", 128, 256),
+                                    ("f32", 32, 64)])
+def test_backward_noncausal_few_states(F, io, d, m, N):
+    """Non-causal calls of one to four local states, which the forward leaves
+    unscanned: the dQ sweep sums them itself, or a launch does where they are
+    large.  Against the backward that recomputes them."""
+    wl = W.Workload("few", 2, 2, N, d, m, "nonstationary", False, io, True, 31)
+    x = W.generate(wl)
+    masked_inputs(wl, x)
+    a = gpu_fwd_bwd(F, wl, x, reuse=False)
+    b = gpu_fwd_bwd(F, wl, x, reuse=True)
+    for k in ("dQ", "dK", "dV", "dW1", "dW2"):
+        # the states are summed over other chunk lengths: fp32 rounding, and where
+        # it flips the bf16 rounding of an operand
+        assert np.linalg.norm(a[k] - b[k]) <= (1e-3 if io == "bf16" else 1e-5) * np.linalg.norm(a[k]), k
+
+
 @pytest.mark.parametrize("causal", [False, True])
 def test_backward_single_token(F, causal):
     """N = 1: O_0 = V_0 whatever the features, so dV = dO and every other
