@@ -227,16 +227,18 @@ void k_fwd_sweep(FwdArgs a) {
   __shared__ __attribute__((aligned(16))) T PT[NW][PT_N];
   __shared__ Frag<T> PQ[TT][NFT][WAVE];        // phi(Q), operand fragments
   __shared__ Frag<T> SB[SH::DVT][NFT][WAVE];   // state, operand fragments (rows = value columns)
-  // normaliser rows of the state, all columns alike.  Where the chunks are cut short
-  // more of a row's keys reach den through this operand than through the
-  // intra-chunk matrix, and rounded once it carries more error than in chunks of
-  // 64 (up to 2.5 % at N = 512).  There the cos features, whose sums are large, have a
-  // low part too, which the waves that write den take in.  Error of den against
-  // float64 at d = 128, m = 256, N = 8192 with and without 1.24e-4 and 1.73e-4, m =
-  // 128, N = 1000 2.15e-4 and 2.78e-4; us per forward 420 and 405, 95 and 91 (with
-  // both parts of the features in every wave 461 and 101).
-  constexpr int NSZ = CAUSAL && IsBf16<T>::value && sweep_short_chunks(D, SH::M) ? 2 : 1;
-  __shared__ Frag<T> SZ[NSZ][NFT][4];
+  __shared__ Frag<T> SZ[NFT][4];               // normaliser rows of the state, all columns alike
+  // Where the chunks are cut short more of a row's keys reach den through SZ than
+  // through the intra-chunk matrix, and rounded once it carries more error than in
+  // chunks of 64 (up to 2.5 % at N = 512).  There the cos features, whose sums are
+  // large, have a low part too (two frequency tiles to an operand), in every wave, so
+  // that each divides by the den that is written.  Error of den against float64,
+  // nonstationary, with and without: m = 256, N = 8192 1.24e-4 and 1.78e-4, m = 128, N =
+  // 1000 1.70e-4 and 2.53e-4; us per forward 450 and 450, m = 128, B*H = 96, N = 1024
+  // 95.3 and 92.9 (as an operand of its own for each frequency tile, in the waves that
+  // write den alone, 465 and 97).
+  constexpr bool ZLOW = CAUSAL && IsBf16<T>::value && sweep_short_chunks(D, SH::M);
+  __shared__ Frag<T> SZL[ZLOW ? NFT / 2 : 1][4];
 
   // causal: one workgroup per segment; non-causal: per group of chunks (every
   // chunk reads the same total state)
@@ -312,16 +314,15 @@ void k_fwd_sweep(FwdArgs a) {
 #pragma unroll
       for (int dt = 0; dt < SH::DVT; ++dt)
         SB[dt][w * SH::FT + ft][l] = pair_tiles<T>(S[2 * ft][dt], S[2 * ft + 1][dt]);
-      Frag<T> z[2];   // high part; low part of the cos features
-      z[0] = pair_tiles<T>(S[2 * ft][SH::DVT], S[2 * ft + 1][SH::DVT]);
-      if constexpr (NSZ == 2) {
-        z[1].zero();
+      const Frag<T> z = pair_tiles<T>(S[2 * ft][SH::DVT], S[2 * ft + 1][SH::DVT]);
+      if (r == 0) SZ[w * SH::FT + ft][g] = z;
+      if constexpr (ZLOW) {
+        static_assert(SH::FT == 1 && NFT % 2 == 0, "two waves to a low operand");
+        T* o = reinterpret_cast<T*>(&SZL[w / 2][g]) + 4 * (w % 2);
+        if (r == 0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) z[1].set(i, S[2 * ft][SH::DVT][i] - z[0].get(i));
-      }
-      if (r == 0) {
-        SZ[0][w * SH::FT + ft][g] = z[0];
-        if (NSZ == 2) SZ[NSZ - 1][w * SH::FT + ft][g] = z[1];
+          for (int i = 0; i < 4; ++i) o[i] = (T)(S[0][SH::DVT][i] - z.get(i));
+        }
       }
     }
   };
@@ -466,16 +467,24 @@ void k_fwd_sweep(FwdArgs a) {
 #pragma unroll
         for (int k = 0; k < NDT; ++k)
           if (SH::DVT % NDT == 0 || part * NDT + k < SH::DVT) mma(accs[ft % NSUM][k], SB[part * NDT + k][ft][l], pq[ft]);
-        mma(zns[ft % NSUM], SZ[0][ft][g], pq[ft]);
+        mma(zns[ft % NSUM], SZ[ft][g], pq[ft]);
       }
       if constexpr (NSUM == 2) {
 #pragma unroll
         for (int k = 0; k < NDT; ++k) acc[k] += accs[1][k];
         zn += zns[1];
       }
-      if (NSZ == 2 && part == 0) {
+      if constexpr (ZLOW) {
 #pragma unroll
-        for (int ft = 0; ft < NFT; ++ft) mma(zl, SZ[NSZ - 1][ft][g], pq[ft]);
+        for (int p = 0; p < NFT / 2; ++p) {
+          Frag<T> c2;   // cos features of two frequency tiles
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            c2.v[i] = pq[2 * p].v[i];
+            c2.v[4 + i] = pq[2 * p + 1].v[i];
+          }
+          mma(zl, SZL[p][g], c2);
+        }
       }
       if (CAUSAL && IsBf16<T>::value) intra();
       // acc[k]: rows = value columns, column = token r; every row of the
