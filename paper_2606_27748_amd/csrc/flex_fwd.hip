@@ -205,7 +205,7 @@ struct SweepShape {
 };
 
 template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ADD, int CH, bool MASK = false>
-__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu(IsBf16<T>::value, D, FW * NW, CAUSAL, CH))))
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu(IsBf16<T>::value, D, FW * NW, NS, CAUSAL, CH))))
 void k_fwd_sweep(FwdArgs a) {
   typedef SweepShape<T, D, FW, NW, NS, CAUSAL, ADD, CH, MASK> SS;
   typedef typename SS::SH SH;

@@ -187,9 +187,13 @@ constexpr int state_waves_per_eu(int d, bool ns, int waves) { return (d <= 64 ||
 // from W (else they reload prepared ones per chunk).
 constexpr bool state_keeps_frags(int d, int waves) { return d <= 64 || waves >= 8; }
 int fwd_state_wgs_per_cu(const KernelShape& ks);
-// Waves per SIMD the forward sweep is compiled for.
-constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool causal, int ch) {
-  return bf16 && (m > 64 || d < 128 || ch < 64 || !causal) ? 2 : 1;
+// Waves per SIMD the forward sweep is compiled for.  The causal d = 128 group of 64
+// takes one (the plan counts one workgroup per CU, and within 256 registers the
+// nonstationary sweep of 32 tokens spills), except where it fits two: us per forward
+// with two and with one, B*H = 32, N = 4096, m = 64: chunks of 32 nonstationary 102 and
+// 92 (m = 192 396 and 292), stationary 77 and 91; of 16 nonstationary 102 and 104.5.
+constexpr int sweep_waves_per_eu(bool bf16, int d, int m, bool ns, bool causal, int ch) {
+  return bf16 && (m > 64 || d < 128 || !causal || ch < (ns ? 32 : 64)) ? 2 : 1;
 }
 
 // Waves per SIMD the backward sweeps are compiled for: two, except at d = 128 (one
