@@ -585,6 +585,13 @@ void k_bwd_dkv(BwdArgs a) {
     __syncthreads();   // phi(Q), phi(K), R' and M complete; the rows of Q and V are read
 
     // ---- interval 2
+    if constexpr (ACC && D == 64 && NW == 4 && NS && CAUSAL) {
+      // also here where the old values of an earlier group leave too few registers (10
+      // spilled, 7 so; B*H = 32, N = 2048, m = 192 training step 359 and 355 us)
+      asm volatile("" : "+v"(l));
+      r = l % 16;
+      g = l / 16;
+    }
     // an earlier group's dK and dV of this chunk (rows past N read zero)
     f32x4 old_k[ACC ? NOT : 1], old_v[ACC ? NOT : 1];
     if (ACC) {
