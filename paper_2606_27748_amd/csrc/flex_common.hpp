@@ -91,14 +91,41 @@ __device__ __forceinline__ void mma(f32x4& c, const Frag<float>& a, const Frag<f
 // 1.15e-7 and 1.12e-7 with one chain, 1.03e-7 and 0.95e-7 with partial sums; with
 // four chains and the forward's sums over the state in two halves 1.03e-7 and
 // 0.87e-7, for 1 % of the causal training step, 155 to 157 us).
+// ROWS: rows of the k-step that are not padding (of 16, slots 4 to 7 hold zeros).
+template <int ROWS = 32>
 __device__ __forceinline__ void mma_tree(f32x4& c, const Frag<__bf16>& a, const Frag<__bf16>& b) { mma(c, a, b); }
+template <int ROWS = 32>
 __device__ __forceinline__ void mma_tree(f32x4& c, const Frag<float>& a, const Frag<float>& b) {
+  if constexpr (ROWS == 16) {
+    f32x4 t[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[2 * j], b.v[2 * j], zero4(), 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[2 * j + 1], b.v[2 * j + 1], t[j], 0, 0, 0);
+    c += t[0] + t[1];
+    return;
+  }
   f32x4 t[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[2 * j], b.v[2 * j], zero4(), 0, 0, 0);
 #pragma unroll
   for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[2 * j + 1], b.v[2 * j + 1], t[j], 0, 0, 0);
   c += (t[0] + t[1]) + (t[2] + t[3]);
+}
+
+// As mma, over the first ROWS rows of the k-step (the others are padding: zeros).
+template <int ROWS>
+__device__ __forceinline__ void mma_rows(f32x4& c, const Frag<__bf16>& a, const Frag<__bf16>& b) { mma(c, a, b); }
+template <int ROWS>
+__device__ __forceinline__ void mma_rows(f32x4& c, const Frag<float>& a, const Frag<float>& b) {
+  if constexpr (ROWS == 16) {
+    f32x4 t = zero4();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j], b.v[j], t, 0, 0, 0);
+    c += t;
+  } else {
+    mma(c, a, b);
+  }
 }
 
 template <class T> struct IsBf16 { static constexpr bool value = false; };

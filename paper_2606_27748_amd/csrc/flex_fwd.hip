@@ -389,8 +389,8 @@ void k_fwd_sweep(FwdArgs a) {
         for (int fc = 0; fc < SH::FC; ++fc) {
           const Frag<T> pkt = lds_tr_frag<T>(PT[w], LDP, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, fc * 16);
 #pragma unroll
-          for (int dt = 0; dt < SH::DVT; ++dt) mma(S[fc][dt], pkt, va[dt]);
-          mma(S[fc][SH::DVT], pkt, ones);
+          for (int dt = 0; dt < SH::DVT; ++dt) mma_rows<CH>(S[fc][dt], pkt, va[dt]);
+          mma_rows<CH>(S[fc][SH::DVT], pkt, ones);
         }
       }
       // this wave's value columns for the second phase
@@ -434,15 +434,12 @@ void k_fwd_sweep(FwdArgs a) {
       }
       // (fp32: the odd frequency tiles in sums of their own, shorter to round)
       constexpr int NSUM = IsBf16<T>::value ? 1 : 2;
-      f32x4 accs[NSUM][NDT], zns[NSUM];
+      f32x4 accs[NSUM][NDT], zn = zero4();
 #pragma unroll
-      for (int p = 0; p < NSUM; ++p) {
-        zns[p] = zero4();
+      for (int p = 0; p < NSUM; ++p)
 #pragma unroll
         for (int k = 0; k < NDT; ++k) accs[p][k] = zero4();
-      }
       f32x4 (&acc)[NDT] = accs[0];
-      f32x4& zn = zns[0];
       f32x4 zl = zero4();   // den's share of the low operands
       auto intra = [&]() {
 #pragma unroll
@@ -450,11 +447,13 @@ void k_fwd_sweep(FwdArgs a) {
           if (32 * ks <= 16 * tq + 15) {
 #pragma unroll
             for (int k = 0; k < NDT; ++k) {
-              mma_tree(acc[k], vf[k][ks], ap[ks]);
+              mma_tree<CH>(acc[k], vf[k][ks], ap[ks]);
               if (IsBf16<T>::value) mma(acc[k], vf[k][ks], al[ks]);
             }
-            mma_tree(zn, ones, ap[ks]);
-            if (IsBf16<T>::value) mma(zl, ones, al[ks]);
+            if (IsBf16<T>::value) {
+              mma(zn, ones, ap[ks]);
+              mma(zl, ones, al[ks]);
+            }
           }
       };
       // fp32: the intra-chunk share first, while the sums are small (den's error
@@ -467,12 +466,11 @@ void k_fwd_sweep(FwdArgs a) {
 #pragma unroll
         for (int k = 0; k < NDT; ++k)
           if (SH::DVT % NDT == 0 || part * NDT + k < SH::DVT) mma(accs[ft % NSUM][k], SB[part * NDT + k][ft][l], pq[ft]);
-        mma(zns[ft % NSUM], SZ[ft][g], pq[ft]);
+        if (IsBf16<T>::value) mma(zn, SZ[ft][g], pq[ft]);
       }
       if constexpr (NSUM == 2) {
 #pragma unroll
         for (int k = 0; k < NDT; ++k) acc[k] += accs[1][k];
-        zn += zns[1];
       }
       if constexpr (ZLOW) {
 #pragma unroll
@@ -491,6 +489,31 @@ void k_fwd_sweep(FwdArgs a) {
       // normaliser tile holds den of token r
       float dn = zn[0];
       if (CAUSAL && IsBf16<T>::value) dn += finite_low(zl[0]);
+      if constexpr (!IsBf16<T>::value) {
+        // fp32: on the vector units, in float64.  As matrix products the waves of a token
+        // tile would each form 16 equal rows of it, 40 of a wave's 112 in chunks of 16.
+        // (In fp32 chains den lost accuracy where it cancels.)  us per forward, B*H = 32,
+        // N = 1023 nonstationary, before and after: chunks of 16, with the padding out of
+        // the k-steps, 69.3 and 63.5, of 32 56.5 and 55.5; error of den against float64
+        // 1.55e-7 and 1.38e-7.
+        double t[2] = {0.0, 0.0};
+        if (CAUSAL) {
+#pragma unroll
+          for (int ks = 0; ks < KT; ++ks)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) t[j % 2] += (double)ap[ks].get(j);
+        }
+#pragma unroll
+        for (int ft = 0; ft < NFT; ++ft) {
+          const Frag<T> z = SZ[ft][g];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) t[j % 2] = fma((double)pq[ft].get(j), (double)z.get(j), t[j % 2]);
+        }
+        double s = t[0] + t[1];
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        dn = (float)s;
+      }
       if (ADD) dn += old_d;
       if (ADD ? a.acc == 2 : a.acc != 0) {
         // one frequency group's share of the numerator and denominator

@@ -148,6 +148,29 @@ def test_forward_short_chunk_den(F, variant, tol):
     assert err <= tol, err
 
 
+@pytest.mark.parametrize("variant,tol", [("stationary", 0.9e-7), ("nonstationary", 1.46e-7)])
+@pytest.mark.parametrize("chunk", [0, 16, 32, 64])
+def test_forward_f32_den_rounding(F, variant, tol, chunk):
+    """fp32 den, a sum in float64, at every chunk length (0: not causal) on a
+    layer's inputs.  Error against float64 in fp32 matrix products: stationary 1.0 to
+    1.06e-7, nonstationary 1.53 to 1.58e-7; in float64 0.77 to 0.79e-7 and 1.36 to
+    1.39e-7 (the rounding of the features); the bounds lie in between."""
+    import torch
+    err = []
+    for seed in (1, 2, 3):
+        gen = torch.Generator().manual_seed(seed)
+        sc = 32 ** -0.25
+        Q, K, V = (torch.randn(1, 4, 1000, 32, generator=gen) * sc for _ in range(3))
+        W1 = torch.randn(4, 64, 32, generator=gen) * sc
+        W2 = torch.randn(4, 64, 32, generator=gen) * sc if variant == "nonstationary" else None
+        tau = torch.full((4,), math.log(2.0))
+        x = [None if t is None else t.cuda() for t in (Q, K, V, W1, W2, tau)]
+        _, den = F.flex_linattn_fwd(F.make_desc(1, 4, 1000, 32, 64, variant, chunk > 0, "f32", chunk=chunk), *x)
+        _, ref = orc.linattn_fwd(*(None if t is None else to_f64(t) for t in x), variant, chunk > 0)
+        err.append(np.linalg.norm(to_f64(den) - ref) / np.linalg.norm(ref))
+    assert np.mean(err) <= tol, err
+
+
 # (d, d_v) with d_v != d: run at width max(d, d_v) on zero-padded copies
 VALUE_WIDTHS = [(64, 32), (128, 64), (128, 32), (32, 64), (64, 128), (32, 128)]
 
