@@ -29,18 +29,16 @@ namespace flex {
 // Pre-pass: segment-local S'^T = sum [V;1]^T-rows x phi(K) and
 // R'^T = sum [dO;-delta]^T-rows x phi(Q)/den; per-token 1/den and delta.
 // ---------------------------------------------------------------------------
-// WITH_S: also the key-side states S' (not needed when the forward's segment
-// states are passed in).
+// Launched where the forward's segment states are not passed in (with them the dQ
+// sweep does the query-side work).
 // The pre-pass forms sums over a segment and per-token scalars only, so at
 // d <= 64 it walks the segment in 64-token chunks (a backward segment is a
 // whole number of them: it spans the forward's 64-token chunks), not the
 // sweeps' 32; at d = 128 the double-buffered staging of 64 rows would not fit
 // in LDS.
-template <class T, int D, int FW, int NW, bool NS, bool WITH_S, bool MASK = false>
+template <class T, int D, int FW, int NW, bool NS, bool MASK = false>
 __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
-  // 64-token chunks where the staging fits: at d <= 64, and at d = 128 on the
-  // query-side-only pass (K and V are not staged there)
-  constexpr int PCH = (D <= 64 || !WITH_S) ? CHUNK : BWD_CHUNK;
+  constexpr int PCH = D <= 64 ? CHUNK : BWD_CHUNK;
   typedef Shape<T, D, FW, NW, NS, PCH> SH;
   static_assert(PCH % BWD_CHUNK == 0 && CHUNK % PCH == 0, "pre-pass chunks hold whole sweep chunks");
   typedef typename Io<T>::type IO;
@@ -108,11 +106,8 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
   const Frag<T> ones = ones_col01<T>();
   constexpr int TPT = SH::NT / SH::CH;  // threads per token for the row reductions
 
-  // projection fragments: held for the whole sweep on the query-side-only
-  // pass at d <= 64, else reloaded per chunk ahead of the staging barriers
-  constexpr bool KEEP_FS = D <= 64 && !WITH_S;
+  // projection fragments, reloaded per chunk ahead of the staging barriers
   FreqSlice<T, D, FW, NS> fs;
-  if (KEEP_FS) fs.load_frags(wproj);
   for (int c = c0; c < c1; ++c) {
     // This chunk's buffers.  They need no barrier before they are written:
     // the chunk that last read them (two back) is separated from this point
@@ -130,7 +125,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
     float* SCK = SCK2[par];
     float* SCQ = SCQ2[par];
     const int tok0 = c * SH::CH;
-    if (!KEEP_FS) fs.load_frags(wproj);
+    fs.load_frags(wproj);
     if constexpr (FUSED) {
       // per-token 1/den and delta = dO . O of this thread's rows (rows past N
       // are zero vectors: delta 0)
@@ -160,16 +155,11 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
       sq.store(XQ, SSQ); sdo.store(XDO); so.store(XO);
       if (threadIdx.x < SH::CH) DEN[threadIdx.x] = dn_next[0];
     }
-    if (WITH_S) {
-      if constexpr (FUSED)
-        sk.store(XK, SCK, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tok0 + t < a.N); });
-      else
-        sk.store(XK, SSK);
-      sv.store(XV);
-    } else {   // K and V only warm the caches for the sweeps that follow
-      sk.touch();
-      sv.touch();
-    }
+    if constexpr (FUSED)
+      sk.store(XK, SCK, [&](int t, auto ssq) { return row_scale(ssq, inv_c, a.s_const, tok0 + t < a.N); });
+    else
+      sk.store(XK, SSK);
+    sv.store(XV);
     {
       const int t1 = c + 1 < c1 ? tok0 + SH::CH : tok0;   // the last chunk refetches itself (unused)
       sq.fetch(Q, t1, a.N); sk.fetch(K, t1, a.N);
@@ -189,7 +179,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
         const float inv = ok ? 1.0f / DEN[t] : 0.f;
         GS[t][0] = inv;
         GS[t][1] = ok ? s : 0.f;
-        if (WITH_S) SCK[t] = row_scale(SSK[t], inv_c, a.s_const, ok);
+        SCK[t] = row_scale(SSK[t], inv_c, a.s_const, ok);
         SCQ[t] = row_scale(SSQ[t], inv_c, a.s_const, ok) * inv;
         if (ok) { gst[(size_t)(tok0 + t) * 2] = inv; gst[(size_t)(tok0 + t) * 2 + 1] = s; }
       }
@@ -200,7 +190,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
 #pragma unroll
     for (int ks = 0; ks < SH::KT; ++ks) {
       // value-side operands: rows = value columns, k = chunk tokens
-      if constexpr (WITH_S) {
+      {
         Frag<T> vt[SH::DVT1], pk[SH::FC];
 #pragma unroll
         for (int dt = 0; dt < SH::DVT; ++dt) vt[dt] = lds_tr_frag<T>(reinterpret_cast<const T*>(XV), StV::LD, 32 * ks + 4 * g, 32 * ks + 16 + 4 * g, dt * 16);
@@ -230,7 +220,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
   for (int dt = 0; dt < SH::DVT1; ++dt)
 #pragma unroll
     for (int fc = 0; fc < SH::FC; ++fc) {
-      if (WITH_S) *reinterpret_cast<f32x4*>(so_ + state_off<SH>(w, dt, fc, l)) = ST[dt][fc];
+      *reinterpret_cast<f32x4*>(so_ + state_off<SH>(w, dt, fc, l)) = ST[dt][fc];
       *reinterpret_cast<f32x4*>(ro_ + state_off<SH>(w, dt, fc, l)) = RT[dt][fc];
     }
 }
@@ -853,21 +843,15 @@ static hipError_t run_bwd_t(const BwdArgs& a, bool causal, hipStream_t st) {
   if (masked && (!CAN_MASK || a.acc)) return hipErrorInvalidValue;
   auto scan_r = [&]() -> hipError_t {
     if (a.rfold) return hipSuccess;
-    return launch_state_scan(a.fstate ? nullptr : a.sstate, a.rstate, a.BH, a.segments, 1, SH::STATE, causal, st,
+    return launch_state_scan(wr ? nullptr : a.sstate, a.rstate, a.BH, a.segments, 1, SH::STATE, causal, st,
                              a.segments);
   };
   if (!wr) {
     timing_mark(KC_BWD_PREPASS, st, true);
     if constexpr (CAN_MASK) {
-      if (masked) {
-        if (a.fstate) k_bwd_prepass<T, D, FW, NW, NS, false, true><<<grid, SH::NT, 0, st>>>(a);
-        else k_bwd_prepass<T, D, FW, NW, NS, true, true><<<grid, SH::NT, 0, st>>>(a);
-      }
+      if (masked) k_bwd_prepass<T, D, FW, NW, NS, true><<<grid, SH::NT, 0, st>>>(a);
     }
-    if (!masked) {
-      if (a.fstate) k_bwd_prepass<T, D, FW, NW, NS, false><<<grid, SH::NT, 0, st>>>(a);
-      else k_bwd_prepass<T, D, FW, NW, NS, true><<<grid, SH::NT, 0, st>>>(a);
-    }
+    if (!masked) k_bwd_prepass<T, D, FW, NW, NS><<<grid, SH::NT, 0, st>>>(a);
     timing_mark(KC_BWD_PREPASS, st, false);
     const hipError_t e = scan_r();
     if (e != hipSuccess) return e;

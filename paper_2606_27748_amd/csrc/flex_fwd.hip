@@ -187,14 +187,8 @@ __global__ __launch_bounds__(256) void k_state_sum(const float* src, int n, int 
 // one divides, where a pass of its own took 35): 620 and 559, and 300 as two
 // groups of 128 frequencies with 8 waves.
 // ---------------------------------------------------------------------------
-// ADD: add this frequency group's numerator and denominator to the sums the
-// earlier groups stored; the old sums are loaded at the start of each chunk,
-// so their latency overlaps the chunk's work.
-// CH: tokens per chunk of the causal sweep (16, 32 or 64; the intra-chunk
-// term covers j <= i within a chunk, earlier tokens enter through the carried
-// state).  Token contractions run in 32-token MFMA k-steps; a 16-token chunk
-// pads its k-step with zero rows (staged once, never written).
-template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ADD, int CH, bool MASK = false>
+// The work split of the second phase.
+template <class T, int D, int FW, int NW, bool NS, int CH>
 struct SweepShape {
   typedef Shape<T, D, FW, NW, NS, CH> SH;
   static constexpr int TT = CH / 16;                  // token tiles per chunk
@@ -204,15 +198,22 @@ struct SweepShape {
   static_assert(TT <= NW && NW % TT == 0, "whole token tiles per wave");
 };
 
+// ADD: add this frequency group's numerator and denominator to the sums the
+// earlier groups stored; the old sums are loaded at the start of each chunk,
+// so their latency overlaps the chunk's work.
+// CH: tokens per chunk of the causal sweep (16, 32 or 64; the intra-chunk
+// term covers j <= i within a chunk, earlier tokens enter through the carried
+// state).  Token contractions run in 32-token MFMA k-steps; a 16-token chunk
+// pads its k-step with zero rows (staged once, never written).
 template <class T, int D, int FW, int NW, bool NS, bool CAUSAL, bool ADD, int CH, bool MASK = false>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu(IsBf16<T>::value, D, FW * NW, NS, CAUSAL, CH))))
 void k_fwd_sweep(FwdArgs a) {
-  typedef SweepShape<T, D, FW, NW, NS, CAUSAL, ADD, CH, MASK> SS;
+  typedef SweepShape<T, D, FW, NW, NS, CH> SS;
   typedef typename SS::SH SH;
   typedef typename Io<T>::type IO;
   typedef RowStage<IO, D, SH::NT, CH> StX;
   typedef RowStage<IO, SH::DV, SH::NT, CH> StV;
-  constexpr int TT = SS::TT, NFT = SS::NFT, NDT = SS::NDT, WPT = SS::WPT;
+  constexpr int TT = SS::TT, NFT = SS::NFT, NDT = SS::NDT;
   constexpr int KT = (CH + 31) / 32;           // 32-token k-steps per chunk
   constexpr int ROWS = KT * 32;                // token rows of the k-step operands
   static_assert(CH == 16 || CH == 32 || CH == 64, "chunk of 16, 32 or 64 tokens");

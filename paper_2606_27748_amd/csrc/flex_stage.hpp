@@ -88,12 +88,6 @@ struct RowStage {
     for (int i = 0; i < PER; ++i) r[i] = b.load16((tid() + i * NT) * 16);
   }
   __device__ __forceinline__ uint4 vec(int i) const { return r[i]; }
-  // keeps the fetched rows' loads without storing them anywhere (loads whose
-  // only purpose is to bring the rows into the caches for a later kernel)
-  __device__ __forceinline__ void touch() const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) asm volatile("" ::"v"(r[i].x), "v"(r[i].y), "v"(r[i].z), "v"(r[i].w));
-  }
   // whether vector index v (of thread tid()) is part of the chunk
   static __device__ __forceinline__ bool mine(int v) { return NV % NT == 0 || v < NV; }
   __device__ __forceinline__ void store(IO* lds) const {
