@@ -91,8 +91,11 @@ typedef struct {
   int32_t m;            /* frequencies per matrix (the paper's n); d' = 2m          */
   int32_t variant;      /* flex_variant                                             */
   int32_t causal;       /* 0: all j; 1: j <= i                                      */
-  int32_t chunk;        /* causal chunk length C in {16, 32, 64}; 0 selects 64.  The
-                           causal forward forms tril(phi(Q_c) phi(K_c)^T)[V_c ; 1]
+  int32_t chunk;        /* causal chunk length C in {16, 32, 64}; 0 selects 64.  A
+                           bf16 forward of max(d, dv) = 128 with m a multiple of
+                           128 takes at most 32: there 64, and so 0, run as 32
+                           (the operands of 64 tokens do not fit LDS).  The causal
+                           forward forms tril(phi(Q_c) phi(K_c)^T)[V_c ; 1]
                            inside each C-token chunk and carries earlier tokens
                            in the running state; results agree across C up to
                            rounding.  The non-causal forward, the backward and

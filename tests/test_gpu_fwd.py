@@ -171,6 +171,19 @@ def test_forward_f32_den_rounding(F, variant, tol, chunk):
     assert np.mean(err) <= tol, err
 
 
+@pytest.mark.parametrize("d,dv,m", [(128, 128, 128), (64, 128, 256)])
+def test_forward_chunk_of_wide_groups(F, d, dv, m):
+    """bf16 max(d, d_v) = 128 with m a multiple of 128: 64-token chunks run as 32."""
+    import torch
+    wl, x = small("bf16", d, m, "nonstationary", True, N=150)
+    x.V = np.concatenate([x.V] * (dv // d), -1)
+    t = to_device(x)
+    out = [F.flex_linattn_fwd(F.make_desc(wl.B, wl.H, wl.N, d, m, wl.variant, True, "bf16", dv=dv, chunk=c),
+                              t["Q"], t["K"], t["V"], t["W1"], t["W2"], t["tau"]) for c in (32, 64, 0)]
+    for O, den in out[1:]:
+        assert torch.equal(O.view(torch.int16), out[0][0].view(torch.int16)) and torch.equal(den, out[0][1])
+
+
 # (d, d_v) with d_v != d: run at width max(d, d_v) on zero-padded copies
 VALUE_WIDTHS = [(64, 32), (128, 64), (128, 32), (32, 64), (64, 128), (32, 128)]
 
