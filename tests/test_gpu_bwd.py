@@ -127,6 +127,19 @@ def test_backward_value_width(F, d, dv, variant, causal, reuse):
     check_rows(wl, x, got, ref, kap)
 
 
+@pytest.mark.parametrize("d,dv,causal", [(64, 32, True), (64, 32, False), (32, 64, True)])
+def test_backward_value_width_two_workgroups(F, d, dv, causal):
+    """d_v != d in groups of 64 frequencies at a size where the segments are planned
+    for two workgroups per CU (7 of them here, 4 for one)."""
+    wl = W.Workload("dv2", 7, 8, 1300, d, 64, "nonstationary", causal, "bf16", True, 65, value_dim=dv)
+    x = W.generate(wl)
+    kap = masked_inputs(wl, x)
+    got = gpu_fwd_bwd(F, wl, x, reuse=True)
+    ref, sc = oracle_bwd(wl, x)
+    check_grads("bf16", got, ref, names_of(wl), sc)
+    check_rows(wl, x, got, ref, kap)
+
+
 @pytest.mark.parametrize("reuse", [False, True])
 @pytest.mark.parametrize("segments", [1, 2, 3])
 @pytest.mark.parametrize("causal", [False, True])
