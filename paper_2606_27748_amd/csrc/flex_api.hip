@@ -118,7 +118,9 @@ KernelShape kshape(const flex_desc* d) {
 // 81 and 56; m = 80 (one group of 128 with 48 padding rows, against two of 64 with
 // as many): B*H = 64, N = 2000 causal d = 64 386 and 230, d = 32 260 and 182.
 // Of 64: the others (at d = 128 the backward's states and frequency-gradient
-// partials of 64 fit registers and LDS, those of 128 would not).
+// partials of 64 fit registers and LDS, those of 128 would not), and m = 144
+// to 192 at d <= 64: B*H = 32, N = 8192, m = 192 a forward alone takes 238 as three
+// groups of 64 and 254 as two of 128, a training step 908 and 851.
 // When the width does not divide m, the first group holds the first `last`
 // frequencies and zero rows after them, whose features the kernels mask to
 // zero (it runs first, so only write variants need masking).
@@ -140,7 +142,7 @@ Groups groups_of(const flex_desc* d) {
 // First frequency row of group g (the padded group, if any, is group 0).
 int group_off(const Groups& G, int g) { return g == 0 ? 0 : G.last + (g - 1) * G.m; }
 
-// Padded frequency rows of a first group that 64 does not fill: [H][group][d]
+// Padded frequency rows of a first group that m does not fill: [H][group][d]
 // per matrix, at the end of the forward and backward workspaces.
 size_t pad_bytes(const flex_desc* d) {
   const Groups G = groups_of(d);
@@ -285,7 +287,10 @@ int fwd_fold_of(const flex_desc* d, int P) {
 
 // Workgroups of the attention sweeps that run on one CU at a time: the bf16
 // shapes of 64 frequencies at d <= 64 (4 waves, within 256 registers and 80 KB
-// of LDS) run two, the others one.
+// of LDS) run two, the others one.  Some non-causal sweeps of 128 frequencies would
+// fit twice, but gain nothing by it (us with one and with two: stationary forward d =
+// 64, B*H = 96, N = 1024 43.1 and 45.2, training step d = 32, B*H = 64, N = 4000 164 and
+// 167; nonstationary forward d = 64, N = 4096 116 and 117).
 int resident_wgs(const flex_desc* d) {
   const KernelShape ks = attn_shape(d);
   return ks.bf16 && ks.d <= 64 && ks.m == 64 ? 2 : 1;
