@@ -182,7 +182,7 @@ void k_awd_fwd(AwdArgs a) {
   // MASKED: a last tile that the keys do not fill; whole tiles take no masks (a
   // third of the vector instructions; us per step of B*H = 256, N = 512, d = m =
   // 64 with both passes' masks gone and the chain-rule pass counting its units:
-  // 233 before, 206 after)
+  // 233 before, 208 after)
   auto key_tile = [&](int kt, auto masked) {
     constexpr bool MASKED = decltype(masked)::value;
     __syncthreads();   // the previous tile's LDS reads are done

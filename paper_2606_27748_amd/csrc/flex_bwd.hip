@@ -242,7 +242,7 @@ __global__ __launch_bounds__(NW * WAVE) void k_bwd_prepass(BwdArgs a) {
 // waves; dW' stays in registers for the whole sweep.
 //
 // Bound by latency and LDS traffic: matrix and vector issue each take a third
-// of the time, and leaving any one product out gains about 7 %.  So what counts
+// of the time, and leaving any one product out gains 3 to 8 %.  So what counts
 // is two waves per SIMD (8 waves of 16 frequencies at d = 64, m = 128; two
 // workgroups of 4 at m = 64) within 256 registers, and few LDS accesses.  us per
 // pass before (dV partials of every wave summed through LDS, dW' there too, 4
